@@ -202,6 +202,7 @@ int init_ctx(skew_ctx **ctx, Plan &p, skew_tensor_desc *d, int n, void *state, s
     x.n = tp.n;
     x.m = tp.m;
     x.ld = tp.ld;
+    x.ldp = tp.ldp;
     x.tr = tp.tr;
     x.cw = tp.cw;
     x.ntc = tp.ntc;
@@ -214,17 +215,12 @@ int init_ctx(skew_ctx **ctx, Plan &p, skew_tensor_desc *d, int n, void *state, s
     x.vec = !tp.fp32 && aligned16(x.w) && aligned16(x.g) && (tp.ld % 8 == 0) && (tp.m % 8 == 0);
     x.tensor_id = dd.tensor_id;
   }
-  // row-band pass items by kernel variant (16-byte aligned rows or element loads is known
-  // only here, from the pointers). The aligned variants without momentum and up to two
-  // chunks per wave address a block of rows by 32-bit byte offsets; a row stride that makes a
-  // block span 2^31 bytes or more takes the element-load variant instead.
+  // row-band pass items by variant (16-byte aligned rows are known only here, from the pointers)
   std::vector<Item> zv[kZVariants];
   for (const Item &it : p.z) {
     const DevTensor &x = table[it.tensor];
     const int lg = x.nseg == 1 ? 0 : (x.nseg == 2 ? 1 : (x.nseg == 4 ? 2 : 3));
-    const bool wide_span = (int64_t)x.zrpi * x.zrb * x.ld * 2 > 0x7FFFFFFF;
-    const bool vec = x.vec && !(wide_span && !x.momentum && x.nseg <= 2);
-    zv[lg * 4 + (vec ? 0 : 2) + (x.momentum ? 1 : 0)].push_back(it);
+    zv[lg * 4 + (x.vec ? 0 : 2) + (x.momentum ? 1 : 0)].push_back(it);
   }
   skew_ctx *c = new (std::nothrow) skew_ctx;
   if (c == nullptr) return SKEW_ENOMEM;
@@ -240,7 +236,9 @@ int init_ctx(skew_ctx **ctx, Plan &p, skew_tensor_desc *d, int n, void *state, s
     items.insert(items.end(), v.begin(), v.end());
   };
   add(c->p1, p.p1);
-  for (int v = 0; v < kZVariants; v++) add(c->z[v], zv[v]);
+  // (the variants share a launch: the momentum ones, whose bands take longest, go first)
+  for (int mom = 1; mom >= 0; mom--)
+    for (int v = mom; v < kZVariants; v += 2) add(c->z[v], zv[v]);
   add(c->fold, p.fold);
   add(c->p2, p.p2);
   add(c->p3, p.p3);
@@ -296,6 +294,10 @@ int skew_state_init_static(skew_ctx **ctx, skew_tensor_desc *d, int n, void *sta
   Plan p;
   int rc = plan_build(d, n, &p);
   if (rc != SKEW_OK) return rc;
+  if (p.ws_bytes > static_workspace_bytes()) {
+    rc = plan_build(d, n, &p, true);
+    if (rc != SKEW_OK) return rc;
+  }
   if (p.ws_bytes > static_workspace_bytes()) return SKEW_ETOOBIG;
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return SKEW_EHIP;
@@ -347,9 +349,24 @@ int skew_step(skew_ctx *ctx, const skew_hparams *hp, void *stream) {
   const DevTensor *T = ctx->d_table;
   const int nt = (int)p.t.size();
   RecheckLists *L = ctx->lists;
+  k.zlast = -1;
+  k.zcount = 0;
+  k.zitems = nullptr;
+  for (int v = 0; v < kZVariants; v++) {
+    if (ctx->z[v].n == 0) continue;
+    if (k.zitems == nullptr || ctx->z[v].d < k.zitems) k.zitems = ctx->z[v].d;
+    k.zcount += (int32_t)ctx->z[v].n;
+    k.zlast = v;
+  }
   auto rowband = [&](int mode) {
-    for (int v = 0; v < kZVariants; v++)
-      if (ctx->z[v].n > 0) run(v & 1, [&] { return launch_p1z(T, ctx->z[v].d, ctx->z[v].n, k, v, mode, s); });
+    for (int v = 0; v < kZVariants; v++) {
+      if (ctx->z[v].n == 0) continue;
+      auto launch = [&] { return launch_p1z(T, ctx->z[v].d, ctx->z[v].n, k, v, mode, s); };
+      if (v == k.zlast)
+        run(0, launch);
+      else if (e == 0)
+        e = launch();   // launched with the last variant's
+    }
   };
   if (!k.gclip) {
     // statistics: the row-band pass, pass 1 of wide factored tensors, the fold

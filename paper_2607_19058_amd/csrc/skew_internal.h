@@ -18,18 +18,18 @@ constexpr int kFold = 256;              // rows (or columns) folded by one work-
 constexpr int64_t kTileElems = 1 << 16; // target elements per tile: 128 KiB of bf16 gradient
 constexpr size_t kAlign = 256;
 
-// Row-band pass (pass 1 of factored matrices up to kZMaxCols columns): a work-group of
+// Row-band pass (pass 1 of factored matrices of kZMinCols to 16384 columns): a work-group of
 // kZThreads threads owns whole rows, so it knows each R_i as soon as the row is summed.
 constexpr int kSub = 2;                  // update-sum passes: work-groups (row interleaves) per tile
-constexpr int kZThreads = 512;           // 8 wave64 (up to 256 VGPRs each: nothing is held in flight)
+constexpr int kZThreads = 512;           // 8 wave64, up to 256 VGPRs each: a work-group fills a compute unit
 constexpr int kZWaves = kZThreads / 64;
 constexpr int kZMaxSeg = 4;              // 512-column chunks per wave and row
-constexpr int64_t kZBandElems = 1 << 21; // elements per row band, at most: 4 MiB of bf16 gradient
-constexpr int64_t kZMinBandElems = 1 << 19;   // ... and at least (unless a row is longer)
-constexpr double kZTargetBands = 1024.0;      // bands per row-band launch class, about
-constexpr int kZVariants = 16;           // kernel variants: lg(nseg) * 4 + (element loads ? 2 : 0) + momentum,
+constexpr int kZMinCols = 8;             // the lane at a row's end loads the row's last 8 columns
+constexpr int64_t kZBandElems = 1 << 22; // elements per row band, at most: 8 MiB of bf16 gradient
+constexpr int64_t kZMinBandElems = 1 << 14;   // ... and at least (unless one block of rows is longer)
+constexpr int kZVariants = 16;           // item lists: lg(nseg) * 4 + (unaligned rows ? 2 : 0) + momentum,
                                          // lg = 0, 1, 2, 3 for nseg = 1, 2, 4, 3 (3: no momentum)
-constexpr int kZLdsBytes = 64 * 1024;    // one LDS staging buffer of the row-band pass (two per work-group)
+constexpr int kZLdsBytes = 96 * 1024;    // bytes of one staged block of rows, at most
 constexpr int kZMaxBlockRows = 64;       // rows staged per block, at most
 constexpr int kZMaxBandRows = 2048;      // rows per band, at most (their R are staged in LDS)
 
@@ -106,11 +106,11 @@ struct DevTensor {
   const uint16_t *g;
   float *M, *V, *R, *C;   // state (NULL where the tier keeps none)
   double *rowpart;        // [ntc][n]   partial row sums of g^2, one per column strip
-  double *colpart;        // [ntr][m]   partial column sums of g^2, one per row band (row-band pass: [nzb][m])
+  double *colpart;        // [ntr][ldp] partial column sums of g^2, one per row band (row-band pass: [nzb][ldp])
   double *ainv;           // [n]        1/sqrt(R_i) after the step's EMA
   double *rsum;           // [nfr]      sums of R_i over each fold chunk of rows (row-band
                           //            tensors: [ceil(n / kFold)], in the gradient-norm mode)
-  double *zpart;          // [nzb][m]   row-band pass: partial column sums of (s x)^2 / R_i
+  double *zpart;          // [nzb][ldp] row-band pass: partial column sums of (s x)^2 / R_i
   BandStats *bst;         // [nzb]      row-band pass: per band
   ColStats *cst;          // [nfc]      row-band pass: per fold chunk of columns; wide factored
                           //            tensors: [nfr + nfc] extremes and equal neighbours of R, C
@@ -119,6 +119,7 @@ struct DevTensor {
   TensorScalars *sc;      // this step's clip factor and reconstruction clamp
   const uint16_t *zeros;  // 256 zero bytes (never written): the source of padding loads
   int64_t n, m, ld;       // rows, columns, row stride (elements)
+  int64_t ldp;            // row stride of colpart and zpart (elements)
   int64_t tr;             // rows per tile
   int32_t cw;             // 512-column chunks per tile (1, 2 or 4)
   int32_t ntc, ntr;       // column strips, row bands
@@ -160,6 +161,9 @@ struct StepConsts {
   int32_t pad;
   float *gscale;            // device: the factor c (written by the norm stage)
   double *gsq;              // device [ntensors]: each tensor's sum of g^2 (norm stage)
+  const Item *zitems;       // device: the row-band items of all variants, and their count
+  int32_t zcount;
+  int32_t zlast;            // the last variant with items: its call launches all of them
 };
 
 // Host-side plan of a descriptor table.
@@ -167,7 +171,7 @@ struct TensorPlan {
   int32_t desc = 0;            // descriptor this sub-tensor comes from
   int32_t grp0 = 0, ngrp = 1;  // the sub-tensors sharing its clip factor (a stacked tensor's slices)
   int64_t idx0 = 0;            // element index of its first element in the descriptor's tensor
-  int64_t n = 0, m = 0, ld = 0, N = 0;
+  int64_t n = 0, m = 0, ld = 0, ldp = 0, N = 0;
   int32_t tier = 0, kind = 0, momentum = 0, fp32 = 0;
   int64_t tr = 0;
   int32_t cw = 0, ntc = 0, ntr = 0, nfr = 0, nfc = 0;
@@ -204,7 +208,8 @@ struct Plan {
 inline size_t align_up(size_t x, size_t a = kAlign) { return (x + a - 1) / a * a; }
 
 // Validates the table and computes sizes, offsets and the work-item lists.
-int plan_build(const skew_tensor_desc *d, int n, Plan *out);
+// `compact`: the plan with the least workspace (large bands, no padding), for the static workspace.
+int plan_build(const skew_tensor_desc *d, int n, Plan *out, bool compact = false);
 
 // The library's static workspace (skew_state_init_static): the device address of the
 // file-scope array on the current device, looked up once per device (skew_kernels.hip).
@@ -214,7 +219,7 @@ constexpr size_t static_workspace_bytes() { return (size_t)SKEW_STATIC_WORKSPACE
 
 // Kernel launchers (skew_kernels.hip). Return a hipError_t value.
 int launch_p1(const DevTensor *T, const Item *items, int64_t count, void *stream);
-// row-band pass, kernel variant lg(nseg) * 4 + (element loads ? 2 : 0) + (momentum ? 1 : 0)
+// row-band pass, the items of variant lg(nseg) * 4 + (unaligned rows ? 2 : 0) + (momentum ? 1 : 0)
 // mode 0: the whole pass; 1: sums of g^2 only (row sums to ainv); 2: z, floored sum and
 // band statistics from the R already folded (the gradient-norm mode's two passes)
 int launch_p1z(const DevTensor *T, const Item *items, int64_t count, const StepConsts &k, int variant, int mode,

@@ -374,12 +374,12 @@ __global__ __launch_bounds__(kThreads) void p1_kernel(const DevTensor *__restric
     double s = 0.0;
     for (int w = q; w < kWaves; w += cw) s += colsh[w][cc];
     const int64_t col = tl.c0 + c;
-    if (col < t.m) stg(t.colpart + (int64_t)tl.band * t.m + col, s);
+    if (col < t.m) stg(t.colpart + (int64_t)tl.band * t.ldp + col, s);
   }
 }
 
 // --------------------------------------------------------------------------------------------
-// Row-band pass: pass 1 of factored matrices whose staged rows fit (Eq. 1 and the update
+// Row-band pass: pass 1 of factored matrices of 8 to 16384 columns (Eq. 1 and the update
 // sum of Alg. 1 in one read of G).
 //
 // A work-group owns a band of whole rows, so R_i <- b2 R_i + a2 mean_j g_ij^2 is final as
@@ -397,94 +397,62 @@ __global__ __launch_bounds__(kThreads) void p1_kernel(const DevTensor *__restric
 // remaining difference from the oracle's sum is the free roundings of R_i c'_j, the
 // square root and the quotient; the per-band maximum of (s x)^2 / R_i bounds their spread.
 //
-// Staging: blocks of zrpi * zrb whole rows (bf16 gradient, and fp32 momentum on the
-// backbone). Aligned rows without momentum and with one or two chunks per wave (the normal
-// step, and the gradient-norm mode's two passes) stage in registers: each wave loads its own
-// pieces of the next block by buffer loads while it sums the current one. The other variants
-// move a block into one of two LDS buffers while the other is being summed: with the direct
-// global-to-LDS loads (16 bytes per lane) when rows are 16-byte aligned, through registers
-// otherwise; no register holds their data in flight, so a 512-thread work-group with up to
-// 256 VGPRs per wave keeps a whole block (up to 64 KiB) of loads outstanding.
+// Staging: every wave loads its own pieces of the next block of rows (bf16 gradient, and
+// fp32 momentum on the backbone) straight into registers, by buffer loads of 16 bytes per
+// lane, while it sums the current one: a whole block (up to 96 KiB a work-group) is in
+// flight and no wave waits for another's loads. Rows may start at any 2-byte position (the
+// hardware takes unaligned 16-byte loads); where the row is no multiple of 8 columns, the
+// lane that holds its end loads the row's last 8 elements and shifts the ones before its
+// own out.
 //
 // Layout: zcw 512-column chunks per row; a group of wpr = ceil(zcw / NSEG) waves shares a
 // row, wave w of the group taking chunks w, w + wpr, ...; zrpi = 8 / wpr groups work on
 // different rows. The column partials of the groups are added in group order through LDS.
 // --------------------------------------------------------------------------------------------
-__device__ __forceinline__ uint4 load_bf8(const uint16_t *base, int64_t ld, int64_t m, int64_t i, int64_t col) {
-  const uint16_t *row = base + i * ld;
-  uint32_t v[4];
-#pragma unroll
-  for (int e2 = 0; e2 < 4; e2++) {
-    const uint32_t lo = (col + 2 * e2 < m) ? (uint32_t)ldg(row + col + 2 * e2) : 0u;
-    const uint32_t hi = (col + 2 * e2 + 1 < m) ? (uint32_t)ldg(row + col + 2 * e2 + 1) : 0u;
-    v[e2] = lo | (hi << 16);
-  }
-  return make_uint4(v[0], v[1], v[2], v[3]);
-}
-
-typedef __attribute__((address_space(3))) void lds_void_t;
-typedef const __attribute__((address_space(1))) void gbl_void_t;
-__device__ __forceinline__ void dma16(const void *g, void *lds) {
-  __builtin_amdgcn_global_load_lds((gbl_void_t *)g, (lds_void_t *)lds, 16, 0, 0);
-}
-__device__ __forceinline__ void dma4(const void *g, void *lds) {
-  __builtin_amdgcn_global_load_lds((gbl_void_t *)g, (lds_void_t *)lds, 4, 0, 0);
-}
-// s_waitcnt immediates (gfx9 encoding): vmcnt(0) and lgkmcnt(0); only lgkmcnt(0)
-constexpr int kWaitVmLgkm0 = 0x0070;
+// s_waitcnt immediate (gfx9 encoding): lgkmcnt(0) only
 constexpr int kWaitLgkm0 = 0xC07F;
-
-// Inline reads of a staging buffer (the momentum variants, where plain loads would raise
-// their registers): opaque to the compiler's wait insertion, so no wait for the block
-// loading into the other buffer is added; the staged data is known to be complete from the
-// wait and barrier that open each block. N reads are in flight together, then one wait.
-__device__ __forceinline__ uint32_t lds_addr(const unsigned char *p) {
-  return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) unsigned char *)p;
-}
 __device__ __forceinline__ uint4 to_uint4(const u32x4_t &v) { return make_uint4(v.x, v.y, v.z, v.w); }
-template <int N>
-__device__ __forceinline__ void lds_read16_n(const unsigned char *const (&p)[N], uint4 (&u)[N]) {
-  u32x4_t v[N > 4 ? 8 : 4];
-  if constexpr (N == 1) {
-    asm volatile("ds_read_b128 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(v[0]) : "v"(lds_addr(p[0])) : "memory");
-  } else if constexpr (N == 2) {
-    asm volatile("ds_read_b128 %0, %2\n\tds_read_b128 %1, %3\n\ts_waitcnt lgkmcnt(0)"
-                 : "=&v"(v[0]), "=&v"(v[1])
-                 : "v"(lds_addr(p[0])), "v"(lds_addr(p[1]))
-                 : "memory");
-  } else if constexpr (N == 4) {
-    asm volatile(
-        "ds_read_b128 %0, %4\n\tds_read_b128 %1, %5\n\tds_read_b128 %2, %6\n\tds_read_b128 %3, %7\n\t"
-        "s_waitcnt lgkmcnt(0)"
-        : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3])
-        : "v"(lds_addr(p[0])), "v"(lds_addr(p[1])), "v"(lds_addr(p[2])), "v"(lds_addr(p[3]))
-        : "memory");
-  } else {
-    static_assert(N == 8, "1, 2, 4 or 8 reads");
-    asm volatile(
-        "ds_read_b128 %0, %8\n\tds_read_b128 %1, %9\n\tds_read_b128 %2, %10\n\tds_read_b128 %3, %11\n\t"
-        "ds_read_b128 %4, %12\n\tds_read_b128 %5, %13\n\tds_read_b128 %6, %14\n\tds_read_b128 %7, %15\n\t"
-        "s_waitcnt lgkmcnt(0)"
-        : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]), "=&v"(v[4]), "=&v"(v[5]), "=&v"(v[6]), "=&v"(v[7])
-        : "v"(lds_addr(p[0])), "v"(lds_addr(p[1])), "v"(lds_addr(p[2])), "v"(lds_addr(p[3])),
-          "v"(lds_addr(p[4])), "v"(lds_addr(p[5])), "v"(lds_addr(p[6])), "v"(lds_addr(p[7]))
-        : "memory");
+
+// v shifted down by sh elements (0..7), zeros entering at the top: of 8 packed bf16 values,
+// and of 8 floats in two halves
+__device__ __forceinline__ void shift_down(u32x4_t &v, int sh) {
+  const u32x4_t z4 = {v.z, v.w, 0u, 0u};
+  if (sh & 4) v = z4;
+  const u32x4_t z2 = {v.y, v.z, v.w, 0u};
+  if (sh & 2) v = z2;
+  const u32x4_t z1 = {__builtin_amdgcn_alignbit(v.y, v.x, 16), __builtin_amdgcn_alignbit(v.z, v.y, 16),
+                      __builtin_amdgcn_alignbit(v.w, v.z, 16), v.w >> 16};
+  if (sh & 1) v = z1;
+}
+__device__ __forceinline__ void shift_down(u32x4_t &a, u32x4_t &b, int sh) {
+  const u32x4_t zero = {0u, 0u, 0u, 0u};
+  if (sh & 4) {
+    a = b;
+    b = zero;
   }
-#pragma unroll
-  for (int j = 0; j < N; j++) u[j] = to_uint4(v[j]);
+  const u32x4_t a2 = {a.z, a.w, b.x, b.y}, b2 = {b.z, b.w, 0u, 0u};
+  if (sh & 2) {
+    a = a2;
+    b = b2;
+  }
+  const u32x4_t a1 = {a.y, a.z, a.w, b.x}, b1 = {b.y, b.z, b.w, 0u};
+  if (sh & 1) {
+    a = a1;
+    b = b1;
+  }
 }
-__device__ __forceinline__ uint4 lds_read16(const unsigned char *p) {
-  const u32x4_t v = *reinterpret_cast<const __attribute__((address_space(3))) u32x4_t *>(
-      (const __attribute__((address_space(3))) unsigned char *)p);
-  return to_uint4(v);
-}
-__device__ __forceinline__ void lds_write16(unsigned char *p, uint4 u) {
-  *reinterpret_cast<__attribute__((address_space(3))) u32x4_t *>(
-      (__attribute__((address_space(3))) unsigned char *)p) = u32x4_t{u.x, u.y, u.z, u.w};
+
+// bytes of a buffer's range (0 where a band has no block at all)
+__device__ __forceinline__ int clamp_span(int64_t bytes) {
+  return bytes <= 0 ? 0 : (bytes < 0x7FFFFFFF ? (int)bytes : 0x7FFFFFFF);
 }
 
 constexpr int kZRowSlots = kZMaxBlockRows * kZWaves;   // row partials of one block: [row][wave in group]
-
+// column partials in LDS: 16 chunks of 512 columns (over the groups) at a time, element e of lane l's 8 columns at
+// e * kColPad + l of its chunk (the writes of a wave and the reads of 64 consecutive columns
+// both spread over all banks)
+constexpr int kColPad = 72, kColChunks = 16;
+constexpr int kZStats = 7;   // values of a band reduced over its work-group
 
 // Cross-lane moves of doubles without LDS: DPP within 16-lane rows (quad permutes, half
 // and full row mirrors) and the gfx950 lane-half swaps. Each reduction step adds two
@@ -557,44 +525,30 @@ __device__ __forceinline__ double rsq_d(double x) {
   return y * fma(-0.5 * x * y, y, 1.5);
 }
 
-template <int NSEG, int RB, bool MOM, bool VEC, bool GN, int FIXED = 0>
-__device__ __forceinline__ void p1z_body(const DevTensor &t, int band, const StepConsts &k, int mode,
-                                         unsigned char *bufA, unsigned char *bufB, float *rbA, float *rbB,
+// MODE 0: the whole pass; 1: the sums of g^2 alone (row sums to ainv; no momentum needed);
+// 2: z, the floored sum and the band statistics of the scaled gradient, with R folded
+template <int NSEG, int RB, bool MOM, int MODE>
+__device__ __forceinline__ void p1z_body(const DevTensor &t, int band, const StepConsts &k, double *colbuf,
                                          double *rowsh, double *sh, float *rstash) {
+  static_assert(MODE != 1 || !MOM, "the sums pass reads no momentum");
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int64_t m = t.m, ld = t.ld;
   const int zcw = t.zcw;
-  // Register staging (aligned rows, no momentum, up to two chunks per wave; the normal step
-  // or a gradient-norm pass with its mode fixed at compile time): each wave loads its own
-  // pieces of the next block straight into registers by buffer loads while it sums the
-  // current one. Lanes past the row's end and rows past the band's end take an offset beyond
-  // the buffer's range, so the hardware returns zeros for them. The planner keeps a block's
-  // byte span below 2^31 for these tensors.
-  constexpr bool REG = VEC && !MOM && NSEG <= 2 && (!GN || FIXED != 0);
   const int wpr = (zcw + NSEG - 1) / NSEG;   // waves per row
   const int grp = wave / wpr;
   const int wg = wave - grp * wpr;           // wave within the group
   const int rpi = t.zrpi;
-  constexpr int rb = RB;                     // rows per group and block
-  const int br = rpi * rb;                   // rows per block
+  const int br = rpi * RB;                   // rows per block: RB per group
   const bool active = grp < rpi;
   const int grp_c = active ? grp : 0;        // idle waves read (and discard) group 0's rows
   int P = 1;                                 // wpr rounded up to a power of two
   while (P < wpr) P <<= 1;
-  bool sok[NSEG];
-  int chs[NSEG];
-  int64_t col[NSEG];
-#pragma unroll
-  for (int s = 0; s < NSEG; s++) {
-    chs[s] = wg + s * wpr;
-    col[s] = (int64_t)chs[s] * kChunk + lane * 8;
-    sok[s] = active && chs[s] < zcw && col[s] < m;
-  }
-  const int64_t r0 = (int64_t)band * t.zrows;
-  const int64_t r1 = (t.n - r0 < t.zrows) ? t.n : r0 + t.zrows;
-  const int64_t nblk = (r1 - r0 + br - 1) / br;
-  const int npieces = br * zcw;          // 1 KiB pieces of gradient per block
-  const int goff_m = npieces * 1024;     // momentum pieces follow (2 KiB each)
+  // The band's blocks of rows are band, band + nzb, ...: the work-groups that run at the same time
+  // read neighbouring blocks, which spreads them over the memory channels (whole bands at power of
+  // two distances do not)
+  const int nzb = t.nzb;
+  const int64_t nblk = ((t.n + br - 1) / br - band + nzb - 1) / nzb;
+  auto first_row = [&](int64_t blk) { return (blk * nzb + band) * br; };
   const float sc = MOM ? k.s_m : k.s_0;
   const float deps = sqrtf(k.eps);                  // the oracle's D on the floor
   const float reps = (float)(1.0 / (double)deps);   // correctly rounded 1/D
@@ -603,337 +557,203 @@ __device__ __forceinline__ void p1z_body(const DevTensor &t, int band, const Ste
   const int regime = __builtin_amdgcn_readfirstlane(ldg(&t.sc->regime));
   const bool want_z = regime != kRegimeFloor, want_y = regime != kRegimeAbove;
 
+  // The lane's pieces: byte offsets from the block's first row, fixed for the whole band. Lanes
+  // past the row's end take 2^31, beyond any block's range (the planner keeps a block's span
+  // below 2^31), and rows past the matrix's end lie beyond the buffer's range by themselves: the
+  // hardware returns zeros for both, so neither sweep masks anything. `tail` is the shift of the
+  // lane whose 8 columns pass the row's end (its load moves back by as many columns).
+  int chs[NSEG];
+  constexpr bool VM = MOM && NSEG < 4;   // (rows over all waves: M's offsets are twice G's)
+  uint32_t vo[RB][NSEG], vm[VM ? RB : 1][VM ? NSEG : 1];
+  int tail = 0;
+#pragma unroll
+  for (int s = 0; s < NSEG; s++) {
+    chs[s] = wg + s * wpr;
+    const int64_t col = (int64_t)chs[s] * kChunk + lane * 8;
+    const bool ok = active && chs[s] < zcw && col < m;
+    const int64_t over = col + 8 > m ? col + 8 - m : 0;
+    if (ok && over) tail = (int)over;
+#pragma unroll
+    for (int b = 0; b < RB; b++) {
+      const int64_t row = (int64_t)grp_c * RB + b;
+      vo[b][s] = ok ? (uint32_t)((row * ld + col - over) * 2) : 0x80000000u;
+      if constexpr (VM) vm[b][s] = ok ? (uint32_t)((row * m + col - over) * 4) : 0x80000000u;
+    }
+  }
+  const bool ragged = (m & 7) != 0;
+
   double cacc[NSEG][8], zacc[NSEG][8];
 #pragma unroll
   for (int s = 0; s < NSEG; s++)
 #pragma unroll
     for (int e = 0; e < 8; e++) cacc[s][e] = zacc[s][e] = 0.0;
   double ysum = 0.0, ysum2 = 0.0, umax = 0.0;   // the floored sum in two chains
-  // mode 1 (sums only): the band's sum of g^2, kept by lane b * P of each group's first wave
-  double rs_l = 0.0;
+  double rs_l = 0.0;   // mode 1: the band's sum of g^2, kept by lane b * P of each group's first wave
   // mode 2: the gradient scale of the gradient-norm mode (elements enter as fl(c g))
-  const bool scaled = mode == 2;
-  const float gc = scaled ? ldg(k.gscale) : 1.f;
+  const float gc = MODE == 2 ? ldg(k.gscale) : 1.f;
   // a row with R_i == 0 but a nonzero sum (flagged by lane b * P of the group's first wave)
   int bad_l = 0;
 
-  // Block loads: piece p = (row r, chunk c) of the block goes to wave p % 8. Rows past
-  // the band's end and lanes past the row's end load zeros (from a zero block in global
-  // memory), so they add nothing to any sum and the sweeps need no masks. Wave 0 also
-  // stages the block's old R values.
-  const int pr0 = wave / zcw, pc0 = wave - pr0 * zcw;                   // piece `wave`: (row, chunk)
-  const int dr = kZWaves / zcw, dc = kZWaves - (kZWaves / zcw) * zcw;   // step of 8 pieces
-  // Direct loads (the lean loop): the lane's source moves by a fixed step from piece to
-  // piece, and bit c of cmask says whether its 8 columns of chunk c lie in the row (zcw <= 32:
-  // at most 8 waves of 4 chunks). The base pointers are held in registers for the whole band
-  // (read once, not per piece). With momentum, the fp32 row of M follows in two 1 KiB halves
-  // per piece (masks cm0, cm1). The momentum variants with four chunks per wave or in the
-  // gradient-norm passes keep the general loop: the registers of the lean one would spill.
-  constexpr bool LEAN = !REG && VEC && (!MOM || (NSEG <= 2 && !GN));
-  uint32_t cmask = 0, cm0 = 0, cm1 = 0;
-  const uint16_t *gptr = t.g, *zptr = t.zeros;
-  const float *mptr = t.M, *rptr = t.R;
-  if constexpr (LEAN) {
-    for (int c = 0; c < zcw; c++) {
-      if ((int64_t)c * kChunk + lane * 8 < m) cmask |= 1u << c;
-      if ((int64_t)c * kChunk + lane * 4 < m) cm0 |= 1u << c;
-      if ((int64_t)c * kChunk + lane * 4 + 256 < m) cm1 |= 1u << c;
-    }
-    asm volatile("" : "+v"(gptr), "+v"(zptr), "+v"(rptr));
-    if constexpr (MOM) asm volatile("" : "+v"(mptr));
-  }
-  const int64_t off_step = (int64_t)dr * ld + (int64_t)dc * kChunk;
-  const int64_t off_wrap = ld - (int64_t)zcw * kChunk;
-  auto issue = [&](int64_t blk, unsigned char *buf, float *rbuf) {
-    const int64_t rbase = r0 + blk * br;
-    int r = pr0, c = pc0;
-    if constexpr (LEAN) {
-      int64_t off = (rbase + pr0) * ld + (int64_t)pc0 * kChunk + lane * 8;   // elements of G
-      int64_t moff = (rbase + pr0) * m + (int64_t)pc0 * kChunk + lane * 4;   // elements of M
-      for (int p = wave; p < npieces; p += kZWaves) {
-        const bool rok = rbase + r < r1;
-        dma16((rok && ((cmask >> c) & 1u)) ? (const void *)(gptr + off) : (const void *)zptr,
-              buf + (size_t)p * 1024);
-        if constexpr (MOM) {
-          dma16((rok && ((cm0 >> c) & 1u)) ? (const void *)(mptr + moff) : (const void *)zptr,
-                buf + goff_m + (size_t)p * 2048);
-          dma16((rok && ((cm1 >> c) & 1u)) ? (const void *)(mptr + moff + 256) : (const void *)zptr,
-                buf + goff_m + (size_t)p * 2048 + 1024);
-          moff += (int64_t)dr * m + (int64_t)dc * kChunk;
-        }
-        r += dr;
-        c += dc;
-        off += off_step;
-        if (c >= zcw) {
-          c -= zcw;
-          r++;
-          off += off_wrap;
-          if constexpr (MOM) moff += m - (int64_t)zcw * kChunk;
-        }
-      }
-    } else
-    for (int p = wave; p < npieces; p += kZWaves) {
-      const bool rok = rbase + r < r1;   // wave-uniform
-      const int64_t i = rok ? rbase + r : r1 - 1;
-      const int64_t cg = (int64_t)c * kChunk + lane * 8;
-      if (VEC) {
-        dma16((rok && cg < m) ? (const void *)(t.g + i * ld + cg) : (const void *)t.zeros, buf + (size_t)p * 1024);
-      } else {
-        lds_write16(buf + (size_t)p * 1024 + lane * 16, rok ? load_bf8(t.g, ld, m, i, cg) : make_uint4(0u, 0u, 0u, 0u));
-      }
-      if (MOM) {
-        const float *mrow = t.M + i * m;
-        const int64_t c0 = (int64_t)c * kChunk + lane * 4, c1 = c0 + 256;
-        if (VEC) {
-          dma16((rok && c0 < m) ? (const void *)(mrow + c0) : (const void *)t.zeros, buf + goff_m + (size_t)p * 2048);
-          dma16((rok && c1 < m) ? (const void *)(mrow + c1) : (const void *)t.zeros,
-                buf + goff_m + (size_t)p * 2048 + 1024);
-        } else {
-          uint32_t mv[8];
-#pragma unroll
-          for (int e = 0; e < 4; e++) {
-            mv[e] = (rok && c0 + e < m) ? __float_as_uint(ldg(mrow + c0 + e)) : 0u;
-            mv[4 + e] = (rok && c1 + e < m) ? __float_as_uint(ldg(mrow + c1 + e)) : 0u;
-          }
-          lds_write16(buf + goff_m + (size_t)p * 2048 + lane * 16, make_uint4(mv[0], mv[1], mv[2], mv[3]));
-          lds_write16(buf + goff_m + (size_t)p * 2048 + 1024 + lane * 16, make_uint4(mv[4], mv[5], mv[6], mv[7]));
-        }
-      }
-      r += dr;
-      c += dc;
-      if (c >= zcw) {
-        c -= zcw;
-        r++;
-      }
-    }
-    if (wave == 0) {
-      const int64_t i = rbase + (lane < br ? lane : br - 1);
-      const int64_t ic = i < r1 ? i : r1 - 1;
-      if (LEAN)
-        dma4(rptr + ic, rbuf);
-      else if (VEC)
-        dma4(t.R + ic, rbuf);
-      else
-        rbuf[lane] = ldg(t.R + ic);
-    }
-  };
-  // register staging: byte offsets of the lane's pieces from the block's first row (the
-  // sentinel 2^31 lies beyond any block's range), the block's buffer descriptor, and the old
-  // R of the row whose fold the lane takes part in (lane b * P + w: row b of its group)
-  uint32_t vo[RB][NSEG];
+  // the old R of the row whose fold the lane takes part in (lane b * P + w: row b of its group)
   const int rfold = grp_c * RB + ((lane / P) < RB ? (lane / P) : 0);
-  if constexpr (REG) {
-#pragma unroll
-    for (int b = 0; b < RB; b++)
-#pragma unroll
-      for (int s = 0; s < NSEG; s++)
-        vo[b][s] = sok[s] ? (uint32_t)((((int64_t)grp_c * RB + b) * ld + col[s]) * 2) : 0x80000000u;
-  }
-  auto issue_reg = [&](int64_t blk, u32x4_t (&dst)[RB][NSEG], float &rold) {
-    const int64_t rbase = r0 + blk * br;
-    const int64_t span = (r1 - rbase) * ld * 2;
+  auto issue_g = [&](int64_t blk, u32x4_t (&dst)[RB][NSEG], float &rold) {
+    const int64_t rbase = first_row(blk);
     const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
-        (void *)(t.g + rbase * ld), (short)0, (int)(span < 0x7FFFFFFF ? span : 0x7FFFFFFF), 0x00020000);
+        (void *)(t.g + rbase * ld), (short)0, clamp_span((t.n - rbase) * ld * 2), 0x00020000);
 #pragma unroll
     for (int b = 0; b < RB; b++)
 #pragma unroll
-      for (int s = 0; s < NSEG; s++) {
-        dst[b][s] = __builtin_amdgcn_raw_buffer_load_b128(rs, vo[b][s], 0, 0);
-      }
-    const int64_t i = rbase + rfold;
-    rold = ldg(t.R + (i < r1 ? i : r1 - 1));
+      for (int s = 0; s < NSEG; s++) dst[b][s] = __builtin_amdgcn_raw_buffer_load_b128(rs, vo[b][s], 0, 0);
+    if constexpr (MODE != 1) {
+      const int64_t i = rbase + rfold;
+      rold = ldg(t.R + (i < t.n ? i : t.n - 1));
+    }
   };
-  // The lane's NSEG pieces of RB block rows are read from LDS in batches of RBB rows into
-  // uk[b0 .. b0 + RBB). Staged padding is zero; a segment past the row's last chunk
-  // (wave-uniform) reads the buffer's zero area instead. Every address lies in the buffer
-  // being read, which the compiler can tell from the one the next block is loading into,
-  // so plain reads wait for the LDS alone (lgkmcnt), never for that load. The momentum
-  // variants keep one inline batch with its wait: plain reads there raise the registers
-  // the compiler holds (and spills).
-  constexpr int RBB = (8 / NSEG < RB ? 8 / NSEG : RB) > 0 ? (8 / NSEG < RB ? 8 / NSEG : RB) : 1;
-  // the block's staged gradient stays in registers from the first sweep to the second where
-  // it fits (no momentum, up to three chunks per wave; the other variants would spill)
-  constexpr bool KEEP = !MOM && NSEG <= 3;
-  auto read_rows = [&](const unsigned char *buf, int b0, uint4 (&uk)[RB][NSEG]) {
-    const unsigned char *ptr[RBB * NSEG];
+  constexpr int MB = MOM ? RB : 1, MS = MOM ? NSEG : 1;
+  auto issue_m = [&](int64_t blk, u32x4_t (&dst)[MB][MS][2]) {
+    if constexpr (MOM) {
+      const int64_t rbase = first_row(blk);
+      const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+          (void *)(t.M + rbase * m), (short)0, clamp_span((t.n - rbase) * m * 4), 0x00020000);
 #pragma unroll
-    for (int b = 0; b < RBB; b++)
+      for (int b = 0; b < RB; b++)
+#pragma unroll
+        for (int s = 0; s < NSEG; s++) {
+          uint32_t o;
+          if constexpr (VM) {
+            o = vm[b][s];
+          } else {
+            o = vo[b][s];
+            asm volatile("" : "+v"(o));   // formed here, not kept in a register of its own
+            o = (o << 1) | (o & 0x80000000u);
+          }
+          dst[b][s][0] = __builtin_amdgcn_raw_buffer_load_b128(rs, o, 0, 0);
+          dst[b][s][1] = __builtin_amdgcn_raw_buffer_load_b128(rs, o + 16u, 0, 0);
+        }
+    }
+  };
+  // With one chunk per wave the momentum of the next block is in flight beside its gradient;
+  // with more the registers hold one block of it, loaded at the start of its own step (it is
+  // needed in the second sweep only)
+  constexpr bool MDB = MOM && NSEG == 1;
+  auto step = [&](int64_t blk, u32x4_t (&regc)[RB][NSEG], float rold, u32x4_t (&momc)[MB][MS][2],
+                  u32x4_t (&regn)[RB][NSEG], float &rnold, u32x4_t (&momn)[MB][MS][2], auto zc, auto yc) {
+    // the next block's loads go out first; the compiler waits for this block's registers
+    // where they are first used
+    if constexpr (MOM && !MDB) issue_m(blk, momc);
+    if (blk + 1 < nblk) {
+      issue_g(blk + 1, regn, rnold);
+      if constexpr (MDB) issue_m(blk + 1, momn);
+    }
+    if (ragged) {   // the wave with the row's last chunk: the end's lane drops the elements before its own
 #pragma unroll
       for (int s = 0; s < NSEG; s++)
-        ptr[b * NSEG + s] =
-            buf + (chs[s] < zcw ? (size_t)((grp_c * RB + b0 + b) * zcw + chs[s]) * 1024 : (size_t)kZLdsBytes) +
-            lane * 16;
-    if constexpr (KEEP) {
+        if (chs[s] == zcw - 1)
 #pragma unroll
-      for (int b = 0; b < RBB; b++)
-#pragma unroll
-        for (int s = 0; s < NSEG; s++) uk[b0 + b][s] = lds_read16(ptr[b * NSEG + s]);
-    } else {
-      uint4 u[RBB * NSEG];
-      lds_read16_n<RBB * NSEG>(ptr, u);
-#pragma unroll
-      for (int b = 0; b < RBB; b++)
-#pragma unroll
-        for (int s = 0; s < NSEG; s++) uk[b0 + b][s] = u[b * NSEG + s];
+          for (int b = 0; b < RB; b++) {
+            shift_down(regc[b][s], tail);
+            if constexpr (MOM) shift_down(momc[b][s][0], momc[b][s][1], tail);
+          }
     }
-  };
-  auto step = [&](int64_t blk, unsigned char *cur, float *rcur, unsigned char *nxt, float *rnxt,
-                  u32x4_t (&regc)[RB][NSEG], float rold, u32x4_t (&regn)[RB][NSEG], float &rnold, auto zc, auto yc) {
-    if constexpr (REG) {
-      // the next block's loads go out first; the compiler waits for this block's registers
-      // where they are first used
-      if (blk + 1 < nblk) issue_reg(blk + 1, regn, rnold);
-    } else {
-      __builtin_amdgcn_s_waitcnt(kWaitVmLgkm0);   // this block's loads (issued one block earlier)
-      __builtin_amdgcn_s_barrier();               // ... by every wave; the other buffer is free
-      if (blk + 1 < nblk) issue(blk + 1, nxt, rnxt);
-    }
-    const int64_t rbase = r0 + blk * br;
+    const int64_t rbase = first_row(blk);
     double *slot = rowsh + (blk & 1) * kZRowSlots;   // [block row][wave in group]
-    // the lane's staged gradient of the block (the second sweep reads it again unless KEEP)
-    uint4 uk[RB][NSEG];
     // row and column sums of g^2 (bf16 squares are exact in double); an idle wave's
     // accumulators are never used. Mode 2 has them from the first pass.
-    if (mode != 2) {
+    if constexpr (MODE != 2) {
       double rp[RB];
 #pragma unroll
-      for (int b0 = 0; b0 < RB; b0 += RBB) {
-        if constexpr (REG) {
+      for (int b = 0; b < RB; b++) {
+        double ra = 0.0, rb2 = 0.0;   // two chains per row
 #pragma unroll
-          for (int bb = 0; bb < RBB; bb++)
+        for (int s = 0; s < NSEG; s++) {
+          // one 8-element group at a time (the scheduler would otherwise convert every
+          // staged element to double at once)
+          __builtin_amdgcn_sched_barrier(0);
+          float x[8];
+          unpack8(to_uint4(regc[b][s]), x);
 #pragma unroll
-            for (int s = 0; s < NSEG; s++) uk[b0 + bb][s] = to_uint4(regc[b0 + bb][s]);
-        } else {
-          read_rows(cur, b0, uk);
-        }
-#pragma unroll
-        for (int bb = 0; bb < RBB; bb++) {
-          const int b = b0 + bb;
-          double ra = 0.0, rb2 = 0.0;   // two chains per row
-#pragma unroll
-          for (int s = 0; s < NSEG; s++) {
-            // one 8-element group at a time (the scheduler would otherwise convert every
-            // staged element to double at once)
-            __builtin_amdgcn_sched_barrier(0);
-            float x[8];
-            unpack8(uk[b][s], x);
-#pragma unroll
-            for (int e = 0; e < 8; e++) {
-              const double xd = (double)x[e];
-              if (e & 1)
-                rb2 = fma(xd, xd, rb2);
-              else
-                ra = fma(xd, xd, ra);
-              cacc[s][e] = fma(xd, xd, cacc[s][e]);
-            }
-            // the column sums are formed here, not sunk towards the loop's end (which
-            // would keep every converted element live across the block)
-#pragma unroll
-            for (int e = 0; e < 8; e++) asm volatile("" : "+v"(cacc[s][e]));
+          for (int e = 0; e < 8; e++) {
+            const double xd = (double)x[e];
+            if (e & 1)
+              rb2 = fma(xd, xd, rb2);
+            else
+              ra = fma(xd, xd, ra);
+            cacc[s][e] = fma(xd, xd, cacc[s][e]);
           }
-          rp[b] = ra + rb2;
+          // the column sums are formed here, not sunk towards the loop's end (which
+          // would keep every converted element live across the block)
+#pragma unroll
+          for (int e = 0; e < 8; e++) asm volatile("" : "+v"(cacc[s][e]));
         }
+        rp[b] = ra + rb2;
       }
       __builtin_amdgcn_sched_barrier(0);
       const double rsum = wave_sum_rows<RB>(rp);
       if (active && (lane & (64 / RB - 1)) == 0) slot[(grp * RB + lane / (64 / RB)) * kZWaves + wg] = rsum;
+      __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
+      __builtin_amdgcn_s_barrier();
     }
-    __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
-    __builtin_amdgcn_s_barrier();
-    // R_i after the EMA (Eq. 1) for the group's rb rows, lane-parallel: lane b * P + w
+    // R_i after the EMA (Eq. 1) for the group's RB rows, lane-parallel: lane b * P + w
     // takes the partial of wave w of row b; after the segment sum lane b * P holds the row
     double winv_l = 0.0;
-    if (mode == 2) {
-      // R_i folded this step (staged with the block)
+    {
       const int b = lane / P, w = lane - b * P;
-      const int r = grp_c * rb + (b < rb ? b : 0);
+      const int r = grp_c * RB + (b < RB ? b : 0);
       const int64_t i = rbase + r;
-      const float R = REG ? rold : rcur[r];   // (REG: the folded R of the lane's row r)
-      const double Rd = (double)R;
-      const bool normal = R > 0.f && R < __builtin_inff();
-      winv_l = (normal && i < r1) ? rcp_d(Rd) : 0.0;   // (1/R is 0 for R = +inf)
-      if (active && wg == 0 && b < rb && w == 0 && i < r1) {
-        rstash[i - r0] = R;
-        if (R != R) bad_l = 1;
+      const bool keeper = active && wg == 0 && b < RB && w == 0 && i < t.n;
+      float R = rold;   // (mode 2: folded this step)
+      double x = 0.0;
+      if constexpr (MODE != 2) {
+        x = (active && b < RB && w < wpr) ? slot[r * kZWaves + w] : 0.0;
+        if (P >= 2) x += dpp_d<kDppXor1>(x);
+        if (P >= 4) x += dpp_d<kDppXor2>(x);
+        if (P >= 8) x += dpp_d<kDppHalfMirror>(x);
+        if constexpr (MODE == 0) R = fmaf(k.a2, div_to_float(x, dm, rdm), __fmul_rn(k.b2, rold));
       }
-    } else {
-      const int b = lane / P, w = lane - b * P;
-      const int r = grp_c * rb + (b < rb ? b : 0);
-      double x = (active && b < rb && w < wpr) ? slot[r * kZWaves + w] : 0.0;
-      if (P >= 2) x += dpp_d<kDppXor1>(x);
-      if (P >= 4) x += dpp_d<kDppXor2>(x);
-      if (P >= 8) x += dpp_d<kDppHalfMirror>(x);
-      const int64_t i = rbase + r;
-      if (mode == 1) {
+      if constexpr (MODE == 1) {
         // the row's sum of g^2: R is folded once the gradient scale is known
-        if (active && wg == 0 && b < rb && w == 0 && i < r1) {
+        if (keeper) {
           stg(t.ainv + i, x);
           rs_l += x;
         }
       } else {
-      const float ri = div_to_float(x, dm, rdm);
-      const float Rold = REG ? rold : rcur[r];   // (REG: the lane's row is r)
-      const float R = fmaf(k.a2, ri, __fmul_rn(k.b2, Rold));
-      const double Rd = (double)R;
-      const bool normal = R > 0.f && R < __builtin_inff();
-      winv_l = (normal && i < r1) ? rcp_d(Rd) : 0.0;   // (1/R is 0 for R = +inf)
-      if (active && wg == 0 && b < rb && w == 0 && i < r1) {
-        // staged for the band's end: a global store here would hold up the next block's
-        // wait for its staged rows until the store completes
-        rstash[i - r0] = R;
-        if (R != R || (!(R > 0.f) && x > 0.0)) bad_l = 1;
-      }
+        const bool normal = R > 0.f && R < __builtin_inff();
+        winv_l = (normal && i < t.n) ? rcp_d((double)R) : 0.0;   // (1/R is 0 for R = +inf)
+        if (keeper) {
+          // staged for the band's end: a global store here would hold up the next block's
+          // wait for its staged rows until the store completes
+          rstash[blk * br + r] = R;
+          if (R != R || (MODE == 0 && !(R > 0.f) && x > 0.0)) bad_l = 1;
+        }
       }
     }
     // z_j, the floored sum and the bound (the sums the prediction asks for)
     auto sweep2 = [&](auto zc, auto yc) {
       constexpr bool Z = decltype(zc)::value, Y = decltype(yc)::value;
 #pragma unroll
-      for (int b0 = 0; b0 < RB; b0 += RBB) {
-      if constexpr (!REG) {
-        if (!KEEP || mode == 2) read_rows(cur, b0, uk);   // (mode 2: the first sweep did not run)
-      } else {
-        // the packed block is unpacked again here, from its own registers (not needed after
-        // this sweep, so the empty asm may claim to change them: no copy is made); keeping
-        // sweep 1's floats beside the next block's registers would spill
-#pragma unroll
-        for (int bb = 0; bb < RBB; bb++)
-#pragma unroll
-          for (int s = 0; s < NSEG; s++) {
-            asm volatile("" : "+v"(regc[b0 + bb][s]));
-            uk[b0 + bb][s] = to_uint4(regc[b0 + bb][s]);
-          }
-      }
-#pragma unroll
-      for (int bb = 0; bb < RBB; bb++) {
-        const int b = b0 + bb;
-        const int r = grp_c * rb + b;
+      for (int b = 0; b < RB; b++) {
         const int src = b * P;
         const double winv = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(winv_l), src),
                                              __builtin_amdgcn_readlane(__double2loint(winv_l), src));
         float amax = 0.f;   // max |s x| over the lane's elements of the row
 #pragma unroll
         for (int s = 0; s < NSEG; s++) {
-          // one 8-element group at a time where the block is read from LDS here; with the
-          // block in registers the scheduler may interleave the groups (1% faster, no spills)
-          if constexpr (!KEEP) __builtin_amdgcn_sched_barrier(0);
+          // one 8-element group at a time where registers are short
+          if constexpr (MOM || NSEG > 2) __builtin_amdgcn_sched_barrier(0);
           float x[8];
-          unpack8(uk[b][s], x);
-          if (scaled) {
+          // the packed block is unpacked again here, from its own registers (not needed after
+          // this sweep, so the empty asm may claim to change them: no copy is made); keeping
+          // sweep 1's floats beside the next block's registers would spill
+          asm volatile("" : "+v"(regc[b][s]));
+          unpack8(to_uint4(regc[b][s]), x);
+          if constexpr (MODE == 2) {
 #pragma unroll
             for (int e = 0; e < 8; e++) x[e] = gc * x[e];
           }
-          if (MOM) {
-            const unsigned char *mp =
-                cur + (chs[s] < zcw ? goff_m + (size_t)(r * zcw + chs[s]) * 2048 : (size_t)kZLdsBytes) + lane * 32;
-            const unsigned char *mpp[2] = {mp, mp + 16};
-            uint4 mv[2];
-            lds_read16_n<2>(mpp, mv);
-            const float mo[8] = {__uint_as_float(mv[0].x), __uint_as_float(mv[0].y), __uint_as_float(mv[0].z),
-                                 __uint_as_float(mv[0].w), __uint_as_float(mv[1].x), __uint_as_float(mv[1].y),
-                                 __uint_as_float(mv[1].z), __uint_as_float(mv[1].w)};
+          if constexpr (MOM) {
 #pragma unroll
-            for (int e = 0; e < 8; e++) x[e] = fmaf(k.a1, x[e], __fmul_rn(k.b1, mo[e]));
+            for (int e = 0; e < 8; e++)
+              x[e] = fmaf(k.a1, x[e], __fmul_rn(k.b1, __uint_as_float(momc[b][s][e / 4][e % 4])));
           }
 #pragma unroll
           for (int e = 0; e < 8; e++) {
@@ -955,143 +775,156 @@ __device__ __forceinline__ void p1z_body(const DevTensor &t, int band, const Ste
         }
         if (Z) umax = fmax(umax, ((double)amax * (double)amax) * winv);
         // a row with R_i == 0 but nonzero elements (mode 0 tests its sum instead)
-        if (Z && scaled && winv == 0.0 && amax > 0.f) bad_l = 1;
-      }
+        if (Z && MODE == 2 && winv == 0.0 && amax > 0.f) bad_l = 1;
       }
       __builtin_amdgcn_sched_barrier(0);
     };
     // an idle wave (its rows are group 0's) adds nothing; mode 1 forms no update sums
-    if (active && mode != 1) sweep2(zc, yc);
+    if constexpr (MODE != 1)
+      if (active) sweep2(zc, yc);
   };
-  u32x4_t regA[RB][NSEG], regB[RB][NSEG];
+  u32x4_t regA[RB][NSEG], regB[RB][NSEG], momA[MB][MS][2], momB[MB][MS][2];
   float roldA = 0.f, roldB = 0.f;
-  if constexpr (REG)
-    issue_reg(0, regA, roldA);
-  else
-    issue(0, bufA, rbA);
+  issue_g(0, regA, roldA);
+  if constexpr (MDB) issue_m(0, momA);
   // the band's loop, specialised for the sums it forms (the regime is the same for the band)
   auto band_loop = [&](auto zc, auto yc) {
     for (int64_t blk = 0; blk < nblk; blk += 2) {
-      step(blk, bufA, rbA, bufB, rbB, regA, roldA, regB, roldB, zc, yc);
+      step(blk, regA, roldA, momA, regB, roldB, momB, zc, yc);
       if (blk + 1 >= nblk) break;
-      step(blk + 1, bufB, rbB, bufA, rbA, regB, roldB, regA, roldA, zc, yc);
+      if constexpr (MDB)
+        step(blk + 1, regB, roldB, momB, regA, roldA, momA, zc, yc);
+      else
+        step(blk + 1, regB, roldB, momA, regA, roldA, momA, zc, yc);
     }
   };
-  if (want_z && want_y)
+  if (MODE == 1 || (want_z && want_y))
     band_loop(std::true_type(), std::true_type());
   else if (want_z)
     band_loop(std::true_type(), std::false_type());
   else
     band_loop(std::false_type(), std::true_type());
-  __builtin_amdgcn_s_waitcnt(kWaitVmLgkm0);
-  __syncthreads();
-  // column partials: groups 1.. add theirs into group 0's through LDS, in group order
-  double *colbuf = reinterpret_cast<double *>(bufA);   // zcw * 512 doubles: groups > 1 only when zcw <= 8
-  for (int gsrc = 1; gsrc < rpi; gsrc++) {
-#pragma unroll
-    for (int half = 0; half < 2; half++) {
-      if (grp == gsrc) {
+  // column partials: the groups' sums added in group order through LDS, 16 chunks at a time,
+  // then stored by consecutive threads
+  auto store_cols = [&](const double (&acc)[NSEG][8], double *dst) {
+    const int per = kColChunks / rpi;
+    for (int c0 = 0; c0 < zcw; c0 += per) {
+      const int nc = zcw - c0 < per ? zcw - c0 : per;
+      __syncthreads();
+      if (active) {
 #pragma unroll
         for (int s = 0; s < NSEG; s++)
-          if (chs[s] < zcw)
+          if (chs[s] >= c0 && chs[s] < c0 + nc)
 #pragma unroll
-            for (int e = 0; e < 8; e++) colbuf[chs[s] * kChunk + lane * 8 + e] = half ? zacc[s][e] : cacc[s][e];
+            for (int e = 0; e < 8; e++)
+              colbuf[((grp * nc + chs[s] - c0) * 8 + e) * kColPad + lane] = acc[s][e];
       }
       __syncthreads();
-      if (grp == 0) {
-#pragma unroll
-        for (int s = 0; s < NSEG; s++)
-          if (chs[s] < zcw)
-#pragma unroll
-            for (int e = 0; e < 8; e++) {
-              const double v = colbuf[chs[s] * kChunk + lane * 8 + e];
-              if (half) zacc[s][e] += v; else cacc[s][e] += v;
-            }
-      }
-      __syncthreads();
-    }
-  }
-  if (grp == 0) {
-    const int64_t prow = (int64_t)band * m;
-#pragma unroll
-    for (int s = 0; s < NSEG; s++) {
-      if (!sok[s]) continue;
-#pragma unroll
-      for (int e = 0; e < 8; e++) {
-        if (VEC || col[s] + e < m) {
-          if (mode != 2) stg(t.colpart + prow + col[s] + e, cacc[s][e]);
-          if (mode != 1) stg(t.zpart + prow + col[s] + e, zacc[s][e]);
-        }
+      const int64_t cend = m - (int64_t)c0 * kChunk < (int64_t)nc * kChunk ? m - (int64_t)c0 * kChunk
+                                                                          : (int64_t)nc * kChunk;
+      for (int c = threadIdx.x; c < (int)cend; c += kZThreads) {
+        const double *p = colbuf + ((c >> 9) * 8 + (c & 7)) * kColPad + ((c >> 3) & 63);
+        double v = p[0];
+        for (int g = 1; g < rpi; g++) v += p[g * nc * 8 * kColPad];
+        stg(dst + (int64_t)band * t.ldp + (int64_t)c0 * kChunk + c, v);
       }
     }
-  }
+  };
+  if constexpr (MODE != 2) store_cols(cacc, t.colpart);
+  if constexpr (MODE != 1) store_cols(zacc, t.zpart);
+  __syncthreads();   // every wave's rstash rows are there
   // the band's R and 1/sqrt(R) (coalesced), and its statistics: fixed-order reductions
   // (mode 1: the band's sum of g^2 instead; mode 2: R was written by the fold)
-  const int64_t nrows = r1 - r0;
+  // (rdup: equal neighbours within a block)
   double rs = rs_l, rdup = 0.0;
   float rmn = __builtin_inff(), rmx = 0.f;
-  for (int64_t j = threadIdx.x; mode != 1 && j < nrows; j += kZThreads) {
-    const float R = rstash[j];
-    if (j > 0 && R > 0.f && R == rstash[j - 1]) rdup += 1.0;
-    const double Rd = (double)R;
-    const bool normal = R > 0.f && R < __builtin_inff();
-    if (mode == 0) {
-      stg(t.R + r0 + j, R);
-      stg(t.ainv + r0 + j, normal ? rsq_d(Rd) : 1.0 / sqrt(Rd));
+  if constexpr (MODE != 1)
+    for (int j = threadIdx.x; j < (int)nblk * br; j += kZThreads) {
+      const int64_t i = first_row(j / br) + j % br;
+      if (i >= t.n) continue;
+      const float R = rstash[j];
+      if (j % br > 0 && R > 0.f && R == rstash[j - 1]) rdup += 1.0;
+      const double Rd = (double)R;
+      const bool normal = R > 0.f && R < __builtin_inff();
+      if (MODE == 0) {
+        stg(t.R + i, R);
+        stg(t.ainv + i, normal ? rsq_d(Rd) : 1.0 / sqrt(Rd));
+      }
+      rs += Rd;
+      if (R > 0.f) rmn = fminf(rmn, R);
+      rmx = fmaxf(rmx, R);
     }
-    rs += Rd;
-    if (R > 0.f) rmn = fminf(rmn, R);
-    rmx = fmaxf(rmx, R);
+  // each wave reduces its values, thread 0 adds the waves in order (one barrier for all)
+  const double ys = wave_sum_d(ysum + ysum2), um = wave_max_d(umax), rw = wave_sum_d(rs), rd = wave_sum_d(rdup);
+  const float rmin = wave_min_f(rmn), rmax = wave_max_f(rmx);
+  const int bd = wave_or(bad_l);
+  if (lane == 0) {
+    double *o = sh + wave * kZStats;
+    o[0] = ys;
+    o[1] = um;
+    o[2] = rw;
+    o[3] = rd;
+    o[4] = (double)rmin;
+    o[5] = (double)rmax;
+    o[6] = (double)bd;
   }
-  const double ys = wg_sum_w<kZWaves>(ysum + ysum2, sh);
-  const double um = wg_max_w<kZWaves>(umax, sh);
-  const double rsum = wg_sum_w<kZWaves>(rs, sh);
-  const float rmin = wg_min_wf<kZWaves>(rmn, sh);
-  const float rmax = wg_max_wf<kZWaves>(rmx, sh);
-  const int bd = wg_or_w<kZWaves>(bad_l, sh);
-  const double rd = wg_sum_w<kZWaves>(rdup, sh);
+  __syncthreads();
   if (threadIdx.x == 0) {
-    stg(&t.bst[band].rdup, (int32_t)rd);
-    stg(&t.bst[band].rsum, rsum);
-    stg(&t.bst[band].ysum, ys);
-    stg(&t.bst[band].umax, um);
-    stg(&t.bst[band].rmin, rmin);
-    stg(&t.bst[band].rmax, rmax);
-    stg(&t.bst[band].bad, bd);
+    double a[kZStats];
+    for (int q = 0; q < kZStats; q++) a[q] = sh[q];
+    for (int w = 1; w < kZWaves; w++) {
+      const double *o = sh + w * kZStats;
+      a[0] += o[0];
+      a[1] = fmax(a[1], o[1]);
+      a[2] += o[2];
+      a[3] += o[3];
+      a[4] = fmin(a[4], o[4]);
+      a[5] = fmax(a[5], o[5]);
+      a[6] = fmax(a[6], o[6]);
+    }
+    stg(&t.bst[band].ysum, a[0]);
+    stg(&t.bst[band].umax, a[1]);
+    stg(&t.bst[band].rsum, a[2]);
+    stg(&t.bst[band].rdup, (int32_t)a[3]);
+    stg(&t.bst[band].rmin, (float)a[4]);
+    stg(&t.bst[band].rmax, (float)a[5]);
+    stg(&t.bst[band].bad, (int32_t)(a[6] != 0.0));
     stg(&t.bst[band].regime, (int32_t)regime);
   }
 }
 
-// GN: the gradient-norm mode's passes (mode 1, the sums of g^2 alone, or mode 2, z and the
-// floored sum of the scaled gradient once R is folded); without it the mode is 0 at compile
-// time. FIXED: one of those passes (1 or 2) with its mode fixed at compile time, staged in
-// registers.
-template <int NSEG, bool MOM, bool VEC, bool GN, int FIXED = 0>
+// One launch covers the bands of every shape: a work-group fills a compute unit in all of
+// them (two waves of up to 256 VGPRs per SIMD), so the variants share a launch at no cost in
+// occupancy, and the bands of a few small tensors run beside the others instead of after them.
+// Rows per group and block (RB) are as many as the registers hold without spills.
+template <int MODE>
 __global__ __launch_bounds__(kZThreads) void p1z_kernel(const DevTensor *__restrict__ TT,
-                                                        const Item *__restrict__ items, StepConsts k, int mode_arg) {
-  __shared__ __attribute__((aligned(16))) unsigned char bufA[kZLdsBytes + 2048];
-  __shared__ __attribute__((aligned(16))) unsigned char bufB[kZLdsBytes + 2048];
-  __shared__ float rbA[64], rbB[64];
+                                                        const Item *__restrict__ items, StepConsts k) {
+  __shared__ double colbuf[kColChunks * 8 * kColPad];
   __shared__ double rowsh[2 * kZRowSlots];
-  __shared__ double sh[5 * kZWaves];
-  __shared__ float rstash[kZMaxBandRows];
-  // each buffer ends in a zero area of 32 bytes per lane, cleared before the first block's wait
-  reinterpret_cast<uint32_t *>(bufA + kZLdsBytes)[threadIdx.x] = 0u;
-  reinterpret_cast<uint32_t *>(bufB + kZLdsBytes)[threadIdx.x] = 0u;
-  static_assert(kZThreads * 4 == 2048, "one word per thread");
-  const int mode = FIXED != 0 ? FIXED : GN ? mode_arg : 0;
+  __shared__ double sh[kZWaves * kZStats];
+  __shared__ float rstash[kZMaxBandRows + kZMaxBlockRows];
   const Item it = items[blockIdx.x];
   const DevTensor &t = TT[it.tensor];
-  // rows per group and block: the planner keeps 4 at most with one or two chunks per wave,
-  // 2 with three and 1 with four, which keeps every variant's loop free of register spills
-  // (the gradient-norm mode's register-staged z pass takes 2: with 4 its registers spill)
-  constexpr int RB4 = FIXED == 2 ? 2 : 4;
-  if (NSEG <= 2 && t.zrb >= 4)
-    p1z_body<NSEG, NSEG <= 2 ? RB4 : 1, MOM, VEC, GN, FIXED>(t, it.tile, k, mode, bufA, bufB, rbA, rbB, rowsh, sh, rstash);
-  else if (NSEG <= 3 && t.zrb >= 2)
-    p1z_body<NSEG, NSEG <= 3 ? 2 : 1, MOM, VEC, GN, FIXED>(t, it.tile, k, mode, bufA, bufB, rbA, rbB, rowsh, sh, rstash);
-  else
-    p1z_body<NSEG, 1, MOM, VEC, GN, FIXED>(t, it.tile, k, mode, bufA, bufB, rbA, rbB, rowsh, sh, rstash);
+  if (MODE != 1 && t.momentum) {
+    constexpr bool M = MODE != 1;
+    if (t.nseg == 1)
+      p1z_body<1, MODE == 2 ? 2 : 4, M, MODE>(t, it.tile, k, colbuf, rowsh, sh, rstash);
+    else if (t.nseg == 2)
+      p1z_body<2, 2, M, MODE>(t, it.tile, k, colbuf, rowsh, sh, rstash);
+    else
+      p1z_body<4, 1, M, MODE>(t, it.tile, k, colbuf, rowsh, sh, rstash);
+  } else {
+    constexpr int RB2 = MODE == 2 ? 2 : 4;
+    if (t.nseg == 1)
+      p1z_body<1, 4, false, MODE>(t, it.tile, k, colbuf, rowsh, sh, rstash);
+    else if (t.nseg == 2)
+      p1z_body<2, RB2, false, MODE>(t, it.tile, k, colbuf, rowsh, sh, rstash);
+    else if (t.nseg == 3)
+      p1z_body<3, 2, false, MODE>(t, it.tile, k, colbuf, rowsh, sh, rstash);
+    else
+      p1z_body<4, 1, false, MODE>(t, it.tile, k, colbuf, rowsh, sh, rstash);
+  }
 }
 
 // Reductions of the clip stage, over the whole work-group (a tensor of its own) or over one
@@ -1146,29 +979,123 @@ __device__ __forceinline__ float mean_r_clamped(const DevTensor &t, const StepCo
   return mean_r_of(t, k, RedGroup{sh});
 }
 
-// Extremes of the positive values and equal neighbours within one fold chunk (v of this
-// thread's row or column, 0 past the end), for the clip stage's test of repeated factors;
-// every thread of the work-group calls it
-__device__ __forceinline__ void chunk_repeats(ColStats *out, float v, float *nb, double *sh) {
-  nb[threadIdx.x] = v;
+// --------------------------------------------------------------------------------------------
+// fold: R_i <- b2 R_i + a2 r_i, C_j <- b2 C_j + a2 c_j (Eq. 1), 1/sqrt(R_i), sums of R
+//
+// A chain of dependent loads bounds it, not their bytes: a thread that adds the partials of
+// every band by itself waits for them a few at a time (786 bands of a 50304-row embedding). So
+// kFoldParts groups of threads each add a quarter of the partials (bands or strips) of a
+// chunk of kFold rows or columns, two per thread, and the quarters are added in order through
+// LDS. Each wave reduces its statistics and thread 0 adds the waves' in order: one barrier for
+// all of them.
+// --------------------------------------------------------------------------------------------
+constexpr int kFoldParts = 4;
+constexpr int kFoldThreads = kFold / 2 * kFoldParts;
+
+struct FoldShared {
+  double part[2][kFoldParts][kFold];
+  double stat[kFoldThreads / 64][8];
+  float nb[kFold];
+  float q;
+};
+// The sums of a[p * stride + x0 + c] over p = 0 .. n - 1 (and of b) for the columns x0 + c < xn of
+// a chunk: two columns per thread (16-byte loads), the p split in kFoldParts runs of their own,
+// added in order through LDS. Thread c < kFold gets its column's totals. Every thread calls it.
+typedef double f64x2_t __attribute__((ext_vector_type(2), aligned(8)));
+template <bool TWO>
+__device__ __forceinline__ void fold_sum(const double *a, const double *b, int n, int64_t stride, int64_t x0,
+                                         int64_t xn, FoldShared &f, double &as, double &bs) {
+  constexpr int half = kFold / 2, U = 4;
+  const int c = (threadIdx.x & (half - 1)) * 2, part = threadIdx.x / half;
+  const int per = (n + kFoldParts - 1) / kFoldParts, p0 = part * per, p1 = p0 + per < n ? p0 + per : n;
+  f64x2_t x = {0.0, 0.0}, y = {0.0, 0.0};
+  if (x0 + c < xn) {
+    // (the last column of an odd row is loaded with the one before it)
+    const int64_t at0 = x0 + c + 1 < xn || x0 + c == 0 ? x0 + c : x0 + c - 1;
+    const bool back = at0 != x0 + c;
+    const bool one = xn == 1;
+    auto load = [&](const double *p) {
+      f64x2_t v = {0.0, 0.0};
+      if (one)
+        v.x = ldg(p);
+      else
+        v = ldg(reinterpret_cast<const f64x2_t *>(p));
+      if (back) v.x = v.y;
+      return v;
+    };
+    // loads of several bands in flight (past the last, of the last again: not added); the sums
+    // run in band order
+    for (int p = p0; p < p1; p += U) {
+      f64x2_t va[U], vb[U];
+#pragma unroll
+      for (int u = 0; u < U; u++) {
+        const int64_t at = (int64_t)(p + u < p1 ? p + u : p1 - 1) * stride + at0;
+        va[u] = load(a + at);
+        if constexpr (TWO) vb[u] = load(b + at);
+      }
+#pragma unroll
+      for (int u = 0; u < U; u++)
+        if (p + u < p1) {
+          x += va[u];
+          if constexpr (TWO) y += vb[u];
+        }
+    }
+  }
+  f.part[0][part][c] = x.x;
+  f.part[0][part][c + 1] = x.y;
+  if constexpr (TWO) {
+    f.part[1][part][c] = y.x;
+    f.part[1][part][c + 1] = y.y;
+  }
   __syncthreads();
-  const double dup = (threadIdx.x > 0 && v > 0.f && v == nb[threadIdx.x - 1]) ? 1.0 : 0.0;
-  const double d = block_sum(dup, sh);
-  const float mn = wg_min_wf<kWaves>(v > 0.f ? v : __builtin_inff(), sh);
-  const float mx = wg_max_wf<kWaves>(v, sh);
+  as = bs = 0.0;
+  if (threadIdx.x < kFold)
+#pragma unroll
+    for (int q = 0; q < kFoldParts; q++) {
+      as += f.part[0][q][threadIdx.x];
+      if constexpr (TWO) bs += f.part[1][q][threadIdx.x];
+    }
+}
+// Extremes of the positive values and equal neighbours within one fold chunk (v of this
+// thread's row or column, 0 past the end), for the clip stage's test of repeated factors, and
+// the sum of s; every thread calls it, those of part 0 with their values
+__device__ __forceinline__ void chunk_stats(ColStats *out, double *sum_out, float v, double s, FoldShared &f) {
+  const int c = threadIdx.x & (kFold - 1);
+  const bool own = threadIdx.x < kFold;
+  if (own) f.nb[c] = v;
+  __syncthreads();
+  if (own) {
+    const double dup = wave_sum_d((c > 0 && v > 0.f && v == f.nb[c - 1]) ? 1.0 : 0.0), tot = wave_sum_d(s);
+    const float mn = wave_min_f(v > 0.f ? v : __builtin_inff()), mx = wave_max_f(v);
+    if ((threadIdx.x & 63) == 0) {
+      double *o = f.stat[threadIdx.x >> 6];
+      o[0] = dup;
+      o[1] = tot;
+      o[2] = (double)mn;
+      o[3] = (double)mx;
+    }
+  }
+  __syncthreads();
   if (threadIdx.x == 0) {
-    stg(&out->cmin, mn);
-    stg(&out->cmax, mx);
-    stg(&out->cdup, (int32_t)d);
+    double d = 0.0, tot = 0.0, mn = __builtin_inf(), mx = 0.0;
+    for (int w = 0; w < kFold / 64; w++) {
+      d += f.stat[w][0];
+      tot += f.stat[w][1];
+      mn = fmin(mn, f.stat[w][2]);
+      mx = fmax(mx, f.stat[w][3]);
+    }
+    if (out != nullptr) {
+      stg(&out->cmin, (float)mn);
+      stg(&out->cmax, (float)mx);
+      stg(&out->cdup, (int32_t)d);
+    }
+    if (sum_out != nullptr) stg(sum_out, tot);
   }
 }
 
-// --------------------------------------------------------------------------------------------
-// fold: R_i <- b2 R_i + a2 r_i, C_j <- b2 C_j + a2 c_j (Eq. 1), 1/sqrt(R_i), sums of R
-// --------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(kThreads) void fold_kernel(const DevTensor *__restrict__ TT,
-                                                        const Item *__restrict__ items, StepConsts k, int phase) {
-  __shared__ double sh[kThreads];
+__global__ __launch_bounds__(kFoldThreads) __attribute__((amdgpu_waves_per_eu(8))) void fold_kernel(const DevTensor *__restrict__ TT,
+                                                            const Item *__restrict__ items, StepConsts k, int phase) {
+  __shared__ FoldShared f;
   const Item it = items[blockIdx.x];
   const DevTensor &t = TT[it.tensor];
   // gradient-norm mode: the statistics of the scaled gradient are c^2 times the exact sums
@@ -1177,18 +1104,14 @@ __global__ __launch_bounds__(kThreads) void fold_kernel(const DevTensor *__restr
   // where their row sums of g^2 wait in ainv
   const int nrows = t.zpath ? (phase == 1 ? (int)((t.n + kFold - 1) / kFold) : 0) : t.nfr;
   if (phase == 2 && !t.zpath) return;
-  __shared__ float nb[kThreads];
+  const int c = threadIdx.x & (kFold - 1);   // the row or column of the chunk that an `own` thread ends with
+  const bool own = threadIdx.x < kFold;
   if (it.tile < nrows) {
-    const int64_t i = (int64_t)it.tile * kFold + threadIdx.x;
-    double rn = 0.0;
+    const int64_t i = (int64_t)it.tile * kFold + c;
+    double s, none, rn = 0.0;
+    fold_sum<false>(t.zpath ? t.ainv : t.rowpart, nullptr, t.zpath ? 1 : t.ntc, t.n, i - c, t.n, f, s, none);
     float Rv = 0.f;
-    if (i < t.n) {
-      double s = 0.0;
-      if (t.zpath)
-        s = ldg(t.ainv + i);
-      else
-#pragma unroll 8
-        for (int q = 0; q < t.ntc; q++) s += ldg(t.rowpart + (int64_t)q * t.n + i);
+    if (own && i < t.n) {
       const float ri = (float)((phase == 1 ? c2 * s : s) / (double)t.m);
       const float R = fmaf(k.a2, ri, __fmul_rn(k.b2, ldg(t.R + i)));
       stg(t.R + i, R);
@@ -1196,40 +1119,34 @@ __global__ __launch_bounds__(kThreads) void fold_kernel(const DevTensor *__restr
       rn = (double)R;
       Rv = R;
     }
-    const double tot = block_sum(rn, sh);
-    if (threadIdx.x == 0) stg(t.rsum + it.tile, tot);
-    if (!t.zpath) chunk_repeats(t.cst + it.tile, Rv, nb, sh);
+    chunk_stats(t.zpath ? nullptr : t.cst + it.tile, t.rsum + it.tile, Rv, rn, f);
   } else if (!t.zpath || phase == 1) {
     // C_j from the column partials ([row bands][m] of either pass 1)
-    const int64_t j = (int64_t)(it.tile - nrows) * kFold + threadIdx.x;
+    const int64_t j = (int64_t)(it.tile - nrows) * kFold + c;
+    double s, none;
+    fold_sum<false>(t.colpart, nullptr, t.zpath ? t.nzb : t.ntr, t.ldp, j - c, t.m, f, s, none);
     float Cv = 0.f;
-    if (j < t.m) {
-      double s = 0.0;
-      const int nb = t.zpath ? t.nzb : t.ntr;
-#pragma unroll 8
-      for (int b = 0; b < nb; b++) s += ldg(t.colpart + (int64_t)b * t.m + j);
+    if (own && j < t.m) {
       const float cj = (float)((phase == 1 ? c2 * s : s) / (double)t.n);
       Cv = fmaf(k.a2, cj, __fmul_rn(k.b2, ldg(t.C + j)));
       stg(t.C + j, Cv);
     }
-    if (!t.zpath) chunk_repeats(t.cst + t.nfr + (it.tile - nrows), Cv, nb, sh);
+    if (!t.zpath) chunk_stats(t.cst + t.nfr + (it.tile - nrows), nullptr, Cv, 0.0, f);
   } else {
     // row-band tensor: C_j (phase 0; phase 2 has it from phase 1), c'_j = C_j / max(mean R,
-    // eps) and sum_j z_j / c'_j over the chunk
-    __shared__ float cprev[kThreads];
-    const float q = mean_r_clamped(t, k, sh);
-    const int64_t j = (int64_t)it.tile * kFold + threadIdx.x;
+    // eps) and sum_j z_j / c'_j over the chunk; wave 0 forms q while the partials load
+    if (threadIdx.x < 64) {
+      const float q0 = mean_r_of(t, k, RedWave{});
+      if (threadIdx.x == 0) f.q = q0;
+    }
+    const int64_t j = (int64_t)it.tile * kFold + c;
+    double cs, zs;
+    fold_sum<true>(t.colpart, t.zpart, t.nzb, t.ldp, j - c, t.m, f, cs, zs);
+    const float q = f.q;
     double sj = 0.0, sj2 = 0.0;
     float cmn = __builtin_inff(), cmx = 0.f, Cj = 0.f;
     int bad = 0;
-    if (j < t.m) {
-      double cs = 0.0, zs = 0.0;
-      // loads of several bands in flight; the sums still run in band order
-#pragma unroll 8
-      for (int p = 0; p < t.nzb; p++) {
-        cs += ldg(t.colpart + (int64_t)p * t.m + j);
-        zs += ldg(t.zpart + (int64_t)p * t.m + j);
-      }
+    if (own && j < t.m) {
       float C;
       if (phase == 0) {
         const float cj = (float)(cs / (double)t.n);
@@ -1254,22 +1171,42 @@ __global__ __launch_bounds__(kThreads) void fold_kernel(const DevTensor *__restr
       }
     }
     // repeated column factors: C_j equal to the previous column's (within the chunk)
-    cprev[threadIdx.x] = Cj;
+    if (own) f.nb[c] = Cj;
     __syncthreads();
-    const double dup = (threadIdx.x > 0 && Cj > 0.f && Cj == cprev[threadIdx.x - 1]) ? 1.0 : 0.0;
-    const double S = block_sum(sj, sh);
-    const double S2 = block_sum(sj2, sh);
-    const double cdup = block_sum(dup, sh);
-    const float cmin = wg_min_wf<kWaves>(cmn, sh);
-    const float cmax = wg_max_wf<kWaves>(cmx, sh);
-    const int b = wg_or_w<kWaves>(bad, sh);
+    if (own) {
+      const double S = wave_sum_d(sj), S2 = wave_sum_d(sj2);
+      const double dup = wave_sum_d((c > 0 && Cj > 0.f && Cj == f.nb[c - 1]) ? 1.0 : 0.0);
+      const float mn = wave_min_f(cmn), mx = wave_max_f(cmx);
+      const int b = wave_or(bad);
+      if ((threadIdx.x & 63) == 0) {
+        double *o = f.stat[threadIdx.x >> 6];
+        o[0] = S;
+        o[1] = S2;
+        o[2] = dup;
+        o[3] = (double)mn;
+        o[4] = (double)mx;
+        o[5] = (double)b;
+      }
+    }
+    __syncthreads();
     if (threadIdx.x == 0) {
-      stg(&t.cst[it.tile].cdup, (int32_t)cdup);
-      stg(&t.cst[it.tile].s2, S2);
-      stg(&t.cst[it.tile].s, S);
-      stg(&t.cst[it.tile].cmin, cmin);
-      stg(&t.cst[it.tile].cmax, cmax);
-      stg(&t.cst[it.tile].bad, b);
+      double S = 0.0, S2 = 0.0, dup = 0.0, mn = __builtin_inf(), mx = 0.0, b = 0.0;
+      for (int w = 0; w < kFold / 64; w++) {
+        const double *o = f.stat[w];
+        S += o[0];
+        S2 += o[1];
+        dup += o[2];
+        mn = fmin(mn, o[3]);
+        mx = fmax(mx, o[4]);
+        b = fmax(b, o[5]);
+      }
+      ColStats *o = t.cst + it.tile;
+      stg(&o->cdup, (int32_t)dup);
+      stg(&o->s2, S2);
+      stg(&o->s, S);
+      stg(&o->cmin, (float)mn);
+      stg(&o->cmax, (float)mx);
+      stg(&o->bad, (int32_t)(b != 0.0));
     }
   }
 }
@@ -2274,47 +2211,19 @@ int launch_p1(const DevTensor *T, const Item *items, int64_t count, void *stream
   hipLaunchKernelGGL(p1_kernel, dim3((uint32_t)count), dim3(kThreads), 0, (hipStream_t)stream, T, items);
   return (int)hipGetLastError();
 }
-int launch_p1z(const DevTensor *T, const Item *items, int64_t count, const StepConsts &k, int variant, int mode,
+// The items of all variants lie one after another in the device's list (k.zitems): the call of
+// the step's last variant launches them together.
+int launch_p1z(const DevTensor *T, const Item *, int64_t count, const StepConsts &k, int variant, int mode,
                void *stream) {
-  if (count <= 0) return hipSuccess;
-  const dim3 grid((uint32_t)count), block(kZThreads);
-  hipStream_t s = (hipStream_t)stream;
-  switch (variant) {
-#define SKEW_P1Z_CASE(V, NSEG, VEC, MOM)                                                          \
-  case V:                                                                                          \
-    if (mode == 1)                                                                                 \
-      hipLaunchKernelGGL((p1z_kernel<NSEG, MOM, VEC, true, (NSEG <= 2 && VEC && !MOM) ? 1 : 0>), grid, \
-                         block, 0, s, T, items, k, 1);                                            \
-    else if (mode == 2)                                                                            \
-      hipLaunchKernelGGL((p1z_kernel<NSEG, MOM, VEC, true, (NSEG <= 2 && VEC && !MOM) ? 2 : 0>), grid, \
-                         block, 0, s, T, items, k, 2);                                            \
-    else if (mode != 0)                                                                            \
-      hipLaunchKernelGGL((p1z_kernel<NSEG, MOM, VEC, true>), grid, block, 0, s, T, items, k, mode); \
-    else                                                                                           \
-      hipLaunchKernelGGL((p1z_kernel<NSEG, MOM, VEC, false>), grid, block, 0, s, T, items, k, 0);  \
-    break;
-    SKEW_P1Z_CASE(0, 1, true, false)
-    SKEW_P1Z_CASE(1, 1, true, true)
-    SKEW_P1Z_CASE(2, 1, false, false)
-    SKEW_P1Z_CASE(3, 1, false, true)
-    SKEW_P1Z_CASE(4, 2, true, false)
-    SKEW_P1Z_CASE(5, 2, true, true)
-    SKEW_P1Z_CASE(6, 2, false, false)
-    SKEW_P1Z_CASE(7, 2, false, true)
-    SKEW_P1Z_CASE(8, 4, true, false)
-    SKEW_P1Z_CASE(9, 4, true, true)
-    SKEW_P1Z_CASE(10, 4, false, false)
-    SKEW_P1Z_CASE(11, 4, false, true)
-    SKEW_P1Z_CASE(12, 3, true, false)
-    SKEW_P1Z_CASE(14, 3, false, false)
-#undef SKEW_P1Z_CASE
-    default: return (int)hipErrorInvalidValue;
-  }
+  if (count <= 0 || variant != k.zlast) return hipSuccess;
+  const dim3 grid((uint32_t)k.zcount), block(kZThreads);
+  auto *kern = mode == 0 ? p1z_kernel<0> : (mode == 1 ? p1z_kernel<1> : p1z_kernel<2>);
+  hipLaunchKernelGGL(kern, grid, block, 0, (hipStream_t)stream, T, k.zitems, k);
   return (int)hipGetLastError();
 }
 int launch_fold(const DevTensor *T, const Item *items, int64_t count, const StepConsts &k, int phase, void *stream) {
   if (count <= 0) return hipSuccess;
-  hipLaunchKernelGGL(fold_kernel, dim3((uint32_t)count), dim3(kThreads), 0, (hipStream_t)stream, T, items, k, phase);
+  hipLaunchKernelGGL(fold_kernel, dim3((uint32_t)count), dim3(kFoldThreads), 0, (hipStream_t)stream, T, items, k, phase);
   return (int)hipGetLastError();
 }
 int launch_gsq(const DevTensor *T, const Item *items, int64_t count, void *stream) {

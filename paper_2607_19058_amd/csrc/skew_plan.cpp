@@ -12,29 +12,99 @@ namespace skew {
 
 static int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
-// Row-band pass for factored matrices whose staged rows fit: zcw 512-column chunks per
-// row, nseg (1, 2, 3 or 4) of them per wave, so wpr = ceil(zcw / nseg) <= 8 waves share a
-// row and rpi = 8 / wpr rows are side by side. Three chunks per wave (rows of 8193 to
-// 12288 columns, e.g. 11008) keep the lean loads and the block in registers; they are
-// used without momentum only (with it, the general loop's four chunks per wave). A block of rpi * zrb rows (bf16 gradient,
-// plus fp32 momentum on the backbone) fills at most one LDS buffer. zrb = 0: no row band.
+// Row-band pass: zcw 512-column chunks per row, nseg of them per wave, so wpr = ceil(zcw /
+// nseg) <= 8 waves share a row and rpi = 8 / wpr rows are side by side. One chunk per wave
+// only for rows of one chunk; two up to 16 chunks; three without momentum up to 24; else
+// four. A block is rpi * zrb rows, zrb (rows per group) as many as the registers hold: two
+// blocks (bf16 gradient, and fp32 momentum where kept) beside the band's double sums.
+// zrb = 0: no row band.
 struct RowBandShape {
   int64_t zcw, nseg, rpi, zrb;
 };
-static RowBandShape rowband_shape(int64_t m, bool momentum) {
+static RowBandShape rowband_shape(int64_t m, int64_t ld, bool momentum) {
   RowBandShape r;
   r.zcw = ceil_div(m, kChunk);
   r.nseg = r.zcw <= 1 ? 1 : (r.zcw <= 2 * kZWaves ? 2 : (!momentum && r.zcw <= 3 * kZWaves ? 3 : 4));
   const int64_t wpr = ceil_div(r.zcw, r.nseg);
-  const int64_t row_kb = r.zcw * (momentum ? 3 : 1);   // staged KiB per row
   r.rpi = wpr <= kZWaves ? kZWaves / wpr : 0;
-  r.zrb = r.rpi > 0 ? std::min<int64_t>(r.nseg <= 2 ? 4 : (r.nseg == 3 ? 2 : 1), kZLdsBytes / (r.rpi * row_kb * 1024))
-                    : 0;
-  while (r.zrb & (r.zrb - 1)) r.zrb &= r.zrb - 1;   // a power of two: 1, 2 or 4
+  r.zrb = r.nseg == 1 ? 4 : (r.nseg == 2 ? (momentum ? 2 : 4) : (r.nseg == 3 ? 2 : 1));
+  // rows too short for the row's end to be one 16-byte load, too long for the work-group, or so
+  // far apart that a block's byte offsets pass 31 bits take the tiled passes
+  if (m < kZMinCols || r.rpi < 1 || ld > 0x7FFFFFFF / 2 / (r.rpi * r.zrb)) r.zrb = 0;
   return r;
 }
 
-int plan_build(const skew_tensor_desc *d, int n, Plan *out) {
+// Rows per band for bands of about `band_elems` elements (fewer with momentum, whose elements
+// take kMomCost times as long): whole blocks, at most kZMaxBandRows
+constexpr double kMomCost = 3.3;
+static int64_t band_rows(const RowBandShape &r, int64_t m, bool momentum, int64_t band_elems) {
+  const int64_t rows_block = r.rpi * r.zrb;
+  const int64_t e = momentum ? (int64_t)((double)band_elems / kMomCost) : band_elems;
+  const int64_t rows = ceil_div(std::max<int64_t>(1, e / m), rows_block) * rows_block;
+  return std::min<int64_t>(rows, kZMaxBandRows / rows_block * rows_block);
+}
+
+// Row-band size: the one with the least estimated time of the row-band pass and its fold. A
+// work-group fills a compute unit, so the bands run in rounds of kCus: many small bands waste
+// less of the last round, and fill the chip when the table is small; each costs its start and
+// end (kBandUs) and a row of column partials that the fold reads back (kFoldBytesPerUs for both).
+// Measured on one MI355X: 1.07e-4 us per element and compute unit (3.3 times that with
+// momentum), 3 us per band, 4 TB/s. 1.1e9 elements in bands of 2^21 / 2^20 / 2^19: 2.2, 4.4 and
+// 8.75 rounds, 724 / 608 / 561 us for the pass and 24 / 27 / 42 us for the fold. The partials of a
+// table with gradients of 2 GiB or more stay below 1/40 of them.
+constexpr double kCus = 256.0, kElemUs = 1.07e-4, kBandUs = 3.0, kFoldBytesPerUs = 2.0e6;
+static int64_t choose_band_elems(const skew_tensor_desc *d, int n) {
+  struct Shape {
+    RowBandShape r;
+    int64_t n, m;
+    bool mom;
+    double count;
+  };
+  double grad_bytes = 0.0;
+  std::vector<Shape> shapes;   // the distinct shapes (runs of the table), counted
+  double cost = 0.0;
+  for (int i = 0; i < n; i++) {
+    const skew_tensor_desc &x = d[i];
+    if (x.ndim == 1 || x.rows <= 0 || x.cols <= 0 || (x.ndim == 3 && x.batch <= 0)) continue;
+    if (x.tier == SKEW_TIER_ROUTER && !(x.state_flags & SKEW_STATE_FACTORED)) continue;
+    const bool mom = x.tier == SKEW_TIER_BACKBONE || (x.state_flags & SKEW_STATE_MOMENTUM) != 0;
+    const RowBandShape r = rowband_shape(x.cols, x.ld, mom);
+    if (r.zrb < 1) continue;
+    const double E = x.ndim == 3 ? (double)x.batch : 1.0;
+    cost += E * (double)x.rows * (double)x.cols * (mom ? kMomCost : 1.0) * kElemUs;
+    grad_bytes += E * (double)x.rows * (double)x.cols * 2.0;
+    bool found = false;
+    for (size_t j = shapes.size(); j-- > 0 && j + 8 >= shapes.size() && !found;) {
+      Shape &s = shapes[j];
+      if (s.n == x.rows && s.m == x.cols && s.mom == mom && s.r.zrb == r.zrb) {
+        s.count += E;
+        found = true;
+      }
+    }
+    if (!found) shapes.push_back({r, x.rows, x.cols, mom, E});
+  }
+  int64_t best = kZBandElems;
+  double best_us = HUGE_VAL;
+  for (int step = 0;; step++) {
+    const int64_t b = (int64_t)((double)kZBandElems * std::exp2(-step / 8.0));
+    if (b < kZMinBandElems) break;
+    double bands = 0.0, bytes = 0.0;
+    for (const Shape &s : shapes) {
+      const double nb = s.count * (double)ceil_div(s.n, band_rows(s.r, s.m, s.mom, b));
+      bands += nb;
+      bytes += nb * 16.0 * (double)s.m;
+    }
+    if (bands <= 0.0 || (step > 0 && grad_bytes >= 2147483648.0 && bytes > grad_bytes / 40.0)) break;
+    const double us = std::ceil(bands / kCus) * (cost / bands + kBandUs) + bytes / kFoldBytesPerUs;
+    if (us < best_us) {
+      best_us = us;
+      best = b;
+    }
+  }
+  return best;
+}
+
+int plan_build(const skew_tensor_desc *d, int n, Plan *out, bool compact) {
   if (n < 0 || (n > 0 && d == nullptr) || out == nullptr) return SKEW_EINVAL;
   Plan p;
   // descriptors -> sub-tensors: a stacked (ndim 3) descriptor of E matrices becomes E
@@ -58,27 +128,7 @@ int plan_build(const skew_tensor_desc *d, int n, Plan *out) {
     if (nsub > INT32_MAX / 4) return SKEW_EINVAL;
   }
   p.t.resize((size_t)nsub);
-  // Row-band size per launch class (with and without momentum, the row-band pass's two
-  // kinds of launch): about kZTargetBands bands over the class, so that a class of few
-  // tensors still fills the chip, between kZMinBandElems and kZBandElems elements
-  int64_t band_elems[2] = {kZBandElems, kZBandElems};
-  {
-    double cls[2] = {0.0, 0.0};
-    for (int i = 0; i < n; i++) {
-      const skew_tensor_desc &x = d[i];
-      if (x.ndim == 1 || x.rows <= 0 || x.cols <= 0) continue;
-      if (x.tier == SKEW_TIER_ROUTER && !(x.state_flags & SKEW_STATE_FACTORED)) continue;
-      const bool mom = x.tier == SKEW_TIER_BACKBONE || (x.state_flags & SKEW_STATE_MOMENTUM) != 0;
-      if (rowband_shape(x.cols, mom).zrb < 1) continue;
-      const double E = (x.ndim == 3) ? (double)x.batch : 1.0;
-      cls[mom ? 1 : 0] += E * (double)x.rows * (double)x.cols;
-    }
-    for (int c = 0; c < 2; c++) {
-      int64_t b = kZBandElems;
-      while (b > kZMinBandElems && (double)b * kZTargetBands > cls[c]) b >>= 1;
-      band_elems[c] = b;
-    }
-  }
+  const int64_t band_elems = compact ? kZBandElems : choose_band_elems(d, n);
   size_t st = 0;        // state bytes
   size_t ws_part = 0;   // partial-sum bytes (offsets relative to the partial region)
   int64_t items_total = 0;
@@ -164,8 +214,11 @@ int plan_build(const skew_tensor_desc *d, int n, Plan *out) {
     tp.off_sc = ws_part; ws_part = align_up(ws_part + sizeof(TensorScalars));
     if (e == 0) p.clip.push_back({i, 0});   // one clip item per group (its first slice)
     if (E > 1) p.clip_slices.push_back({i, 0});
+    // Column partials of successive bands lie 256 bytes off a multiple of 4 KiB: the fold reads a few
+    // columns of every band, which at a power of two distance all fall on the same memory channels
+    tp.ldp = tp.m + (!compact && tp.m % 512 == 0 ? 32 : 0);
     // the row-band pass (see rowband_shape)
-    const RowBandShape rbs = rowband_shape(tp.m, tp.momentum != 0);
+    const RowBandShape rbs = rowband_shape(tp.m, tp.ld, tp.momentum != 0);
     const int64_t zcw = rbs.zcw, nseg = rbs.nseg, rpi = rbs.rpi, zrb = rbs.zrb;
     tp.zpath = (tp.kind == kFactored && rpi > 0 && zrb >= 1) ? 1 : 0;
     if (tp.zpath) {
@@ -173,17 +226,14 @@ int plan_build(const skew_tensor_desc *d, int n, Plan *out) {
       tp.nseg = (int32_t)nseg;
       tp.zrpi = (int32_t)rpi;
       tp.zrb = (int32_t)zrb;
-      const int64_t rows_block = rpi * zrb;
-      tp.zrows = ceil_div(std::max<int64_t>(1, ceil_div(band_elems[tp.momentum ? 1 : 0], tp.m)), rows_block) *
-                 rows_block;
-      tp.zrows = std::min<int64_t>(tp.zrows, kZMaxBandRows / rows_block * rows_block);
+      tp.zrows = band_rows(rbs, tp.m, tp.momentum != 0, band_elems);
       const int64_t nzb = ceil_div(tp.n, tp.zrows), nfc = ceil_div(tp.m, kFold);
       if (nzb > INT32_MAX / 2 || nfc > INT32_MAX / 2) return SKEW_EINVAL;
       tp.nzb = (int32_t)nzb;
       tp.nfr = 0;
       tp.nfc = (int32_t)nfc;
-      tp.off_colpart = ws_part; ws_part = align_up(ws_part + (size_t)nzb * tp.m * 8);
-      tp.off_zpart = ws_part; ws_part = align_up(ws_part + (size_t)nzb * tp.m * 8);
+      tp.off_colpart = ws_part; ws_part = align_up(ws_part + (size_t)nzb * tp.ldp * 8);
+      tp.off_zpart = ws_part; ws_part = align_up(ws_part + (size_t)nzb * tp.ldp * 8);
       tp.off_ainv = ws_part; ws_part = align_up(ws_part + (size_t)tp.n * 8);
       tp.off_bst = ws_part; ws_part = align_up(ws_part + (size_t)nzb * sizeof(BandStats));
       tp.off_cst = ws_part; ws_part = align_up(ws_part + (size_t)nfc * sizeof(ColStats));
@@ -200,7 +250,7 @@ int plan_build(const skew_tensor_desc *d, int n, Plan *out) {
       tp.nfr = (int32_t)nfr;
       tp.nfc = (int32_t)nfc;
       tp.off_rowpart = ws_part; ws_part = align_up(ws_part + (size_t)ntc * tp.n * 8);
-      tp.off_colpart = ws_part; ws_part = align_up(ws_part + (size_t)ntr * tp.m * 8);
+      tp.off_colpart = ws_part; ws_part = align_up(ws_part + (size_t)ntr * tp.ldp * 8);
       tp.off_ainv = ws_part; ws_part = align_up(ws_part + (size_t)tp.n * 8);
       tp.off_rsum = ws_part; ws_part = align_up(ws_part + (size_t)nfr * 8);
       tp.off_cst = ws_part; ws_part = align_up(ws_part + (size_t)(nfr + nfc) * sizeof(ColStats));

@@ -1,0 +1,68 @@
+"""Row widths, strides and positions at which the kernels change their way of working, against
+the CPU oracle: rows that start at any 2-byte position and are no multiple of 8 columns (the
+row-band pass loads 8 elements at a time and shifts at the row's end), the first and last
+widths of each number of 512-column chunks per wave, and widths outside the row-band pass on
+both sides (below 8 columns, above 16384). Every tensor is a view of a wider buffer whose other
+elements are NaN in the gradient, so that a value read past a row's end would show in the
+results, and must keep their values in the weights."""
+import pytest
+import torch
+
+import oracle
+from paper_2607_19058_amd import workloads as W
+
+from parity_util import ParityRun, bits, log
+
+pytestmark = pytest.mark.gpu
+
+WIDTHS = (7, 8, 9, 15, 511, 513, 1029, 2730, 3077, 4099, 8192, 8193, 12291, 16381, 16390)
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _gpu():
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests need a HIP device")
+    torch.cuda.init()
+
+
+def _views(specs, pad, shift):
+    """Weights and gradients as views at a row stride `pad` above the width, `shift` elements into
+    their buffers; weights drawn as the workloads draw them."""
+    wl = W.Workload("views", specs, 1)
+    ws, gs, bufs = [], [], []
+    for s in specs:
+        ld = s.shape[-1] + pad
+        rows = s.shape[0] * s.shape[1] if len(s.shape) == 3 else s.shape[0]
+        strides = (s.shape[1] * ld, ld, 1) if len(s.shape) == 3 else (ld, 1)
+        wb = torch.full((rows * ld + shift + 8,), 3.0, dtype=torch.bfloat16, device="cuda")
+        gb = torch.full_like(wb, float("nan"))
+        w, g = (b.as_strided(s.shape, strides, shift) for b in (wb, gb))
+        w.copy_(W.init_weight(s, wl, torch.device("cuda")))
+        g.zero_()
+        ws.append(w)
+        gs.append(g)
+        bufs.append((wb, w))
+    return ws, gs, bufs
+
+
+@pytest.mark.parametrize("hp", [oracle.DEFAULTS, dict(oracle.DEFAULTS, weight_decay=0.05, max_grad_norm=1e-2)],
+                         ids=["plain", "gnorm+decay"])
+@pytest.mark.parametrize("pad,shift", [(0, 0), (3, 1), (16, 8)], ids=["dense", "unaligned", "aligned_views"])
+@pytest.mark.parametrize("tier", [W.BACKBONE, W.EXPERT], ids=["momentum", "expert"])
+def test_row_widths_and_positions(tier, pad, shift, hp):
+    specs = [W.Spec(f"w{m}", tier, (37 if m > 600 else 530, m), k) for k, m in enumerate(WIDTHS)]
+    specs.append(W.Spec("stack", tier, (3, 41, 523), len(specs)))
+    specs.append(W.Spec("one_row", tier, (1, 2055), len(specs)))
+    ws, gs, bufs = _views(specs, pad, shift)
+    log(f"[parity] widths {WIDTHS}, tier {tier}, row stride width + {pad}, {hp}; 3 steps")
+    pr = ParityRun(W.Workload("widths", specs, 3), weights=ws, grads=gs, hp=hp)
+    for t in (1, 2, 3):
+        pr.step(t)
+    assert pr.stats.ok(), pr.stats
+    for s, (wb, w) in zip(specs, bufs):   # nothing outside the views was written
+        keep = wb.clone()
+        w_now = w.clone()
+        w.fill_(3.0)
+        assert bool((wb == 3.0).all()), s.name
+        wb.copy_(keep)
+        assert (bits(w) == bits(w_now)).all()
