@@ -33,6 +33,7 @@ struct skew_ctx {
   DevTensor *d_table = nullptr;
   RecheckLists *lists = nullptr;
   ItemList p1, fold, p2, p3, clip, clip_slices, fold_rows;
+  int ragged = 0;            // a factored tensor has unaligned rows
   float *gscale = nullptr;   // device: the gradient-norm mode's scale
   double *gsq = nullptr;     // device: per-tensor sums of g^2
   ItemList z[kZVariants];    // row-band pass items, one list per kernel variant
@@ -250,6 +251,8 @@ int init_ctx(skew_ctx **ctx, Plan &p, skew_tensor_desc *d, int n, void *state, s
     delete c;
     return SKEW_EINVAL;
   }
+  for (int i = 0; i < nt; i++)
+    if (!p.t[i].empty && p.t[i].kind == kFactored && !table[i].vec) c->ragged = 1;
   c->gscale = reinterpret_cast<float *>(ws + p.off_gscale);
   c->gsq = reinterpret_cast<double *>(ws + p.off_gsq);
 
@@ -324,6 +327,7 @@ int skew_step(skew_ctx *ctx, const skew_hparams *hp, void *stream) {
   StepConsts k = make_consts(*hp);
   k.gscale = ctx->gscale;
   k.gsq = ctx->gsq;
+  k.ragged = ctx->ragged;
   const Plan &p = ctx->plan;
   hipStream_t s = static_cast<hipStream_t>(stream);
   std::vector<skew_ctx::Timed> *rec = nullptr;

@@ -15,7 +15,7 @@ constexpr int kWaves = kThreads / 64;
 constexpr int kChunk = 512;             // columns one wave covers with one 16-byte load per lane
 constexpr int kMaxCw = 4;               // chunks per tile row: 1, 2 or 4 (at most 2048 columns)
 constexpr int kFold = 256;              // rows (or columns) folded by one work-group
-constexpr int64_t kTileElems = 1 << 16; // target elements per tile: 128 KiB of bf16 gradient
+constexpr int64_t kTileElems = 1 << 16; // elements per update tile, at most: 128 KiB of bf16 gradient
 constexpr size_t kAlign = 256;
 
 // Row-band pass (pass 1 of factored matrices of kZMinCols to 16384 columns): a work-group of
@@ -158,7 +158,7 @@ struct StepConsts {
   float wd;                 // lr * lambda of the decoupled weight decay, rounded once (0: off)
   float max_grad_norm;      // > 0: gradients scaled by the global norm's factor
   int32_t gclip;            // max_grad_norm > 0
-  int32_t pad;
+  int32_t ragged;           // a factored tensor of the table has unaligned rows (DevTensor::vec == 0)
   float *gscale;            // device: the factor c (written by the norm stage)
   double *gsq;              // device [ntensors]: each tensor's sum of g^2 (norm stage)
   const Item *zitems;       // device: the row-band items of all variants, and their count

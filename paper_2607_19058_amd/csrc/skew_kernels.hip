@@ -43,10 +43,6 @@ __device__ __forceinline__ void stg(T *p, T v) {
 }
 typedef unsigned u32x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ uint4 ldg(const uint4 *p) {
-  const u32x4_t v = ldg(reinterpret_cast<const u32x4_t *>(p));
-  return make_uint4(v.x, v.y, v.z, v.w);
-}
 __device__ __forceinline__ float4 ldg(const float4 *p) {
   const f32x4_t v = ldg(reinterpret_cast<const f32x4_t *>(p));
   return make_float4(v.x, v.y, v.z, v.w);
@@ -78,12 +74,6 @@ __device__ __forceinline__ void stg_nt(uint4 *p, uint4 v) {
 
 __device__ __forceinline__ float bf_lo(uint32_t u) { return __uint_as_float(u << 16); }
 __device__ __forceinline__ float bf_hi(uint32_t u) { return __uint_as_float(u & 0xFFFF0000u); }
-__device__ __forceinline__ float bf_one(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
-// element idx of a weight or gradient array: bf16, or float32 for float32 masters
-__device__ __forceinline__ float elem(const uint16_t *p, int64_t idx, bool fp32) {
-  return fp32 ? ldg(reinterpret_cast<const float *>(p) + idx) : bf_one(ldg(p + idx));
-}
-
 // max(a, b) that returns `a` when it is NaN (b is a finite constant): NaN propagates.
 __device__ __forceinline__ float max_nan(float a, float b) { return (a < b) ? b : a; }
 
@@ -113,7 +103,6 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float a, float b) {
   f32x2 v = {a, b};
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
-__device__ __forceinline__ uint16_t to_bf16(float a) { return __builtin_bit_cast(uint16_t, (__bf16)a); }
 
 // SplitMix64 output function (Steele, Lea, Flood, OOPSLA 2014).
 __device__ __forceinline__ uint64_t mix64(uint64_t z) {
@@ -155,7 +144,29 @@ struct Dither {
 __device__ __forceinline__ float dither_u16(uint32_t u) { return fmaf((float)u, 0x1p-23f, -65535.0f * 0x1p-24f); }
 __device__ __forceinline__ float dither_lo(uint32_t h) { return dither_u16(h & 0xFFFFu); }
 __device__ __forceinline__ float dither_hi(uint32_t h) { return dither_u16(h >> 16); }
-__device__ __forceinline__ float dither_of(uint32_t h, uint64_t idx) { return (idx & 1u) ? dither_hi(h) : dither_lo(h); }
+
+// Dither values of 8 elements from index idx on (any parity; `wide`: pair indices may pass 32 bits,
+// else the pairs share their high word). An odd start takes the high half of its first pair, so
+// the half-words of 5 pairs are shifted by one.
+__device__ __forceinline__ void dither8(const Dither &dz, uint64_t idx, bool wide, float *d) {
+  const uint64_t p0 = idx >> 1;
+  const bool odd = (idx & 1u) != 0;
+  uint32_t h[5];
+#pragma unroll
+  for (int e = 0; e < 5; e++) {
+    if (e == 4 && !odd) {
+      h[e] = 0u;
+      continue;
+    }
+    h[e] = wide ? dz.pair(p0 + e) : fmix32(((uint32_t)p0 + (uint32_t)e) ^ dz.klo ^ dz.inner0);
+  }
+#pragma unroll
+  for (int e = 0; e < 4; e++) {
+    const uint32_t w = odd ? __builtin_amdgcn_alignbit(h[e + 1], h[e], 16) : h[e];
+    d[2 * e] = dither_lo(w);
+    d[2 * e + 1] = dither_hi(w);
+  }
+}
 
 // The noise added before the cast is the product of two exact factors: e 2^-24 and |w|
 // (ulp(w) taken as 2^-7 |w|, Sec. 3), or, in the exact-ulp mode, e 2^-24 and 2^7 times the
@@ -299,18 +310,128 @@ struct WaveMap {
   }
 };
 
-__device__ __forceinline__ void load_g8(const DevTensor &t, int64_t i, int64_t col, float *g) {
-  const uint16_t *row = t.g + i * t.ld;
-  if (t.vec) {
-    if (col < t.m) {
-      unpack8(ldg(reinterpret_cast<const uint4 *>(row + col)), g);
-    } else {
+__device__ __forceinline__ uint4 to_uint4(const u32x4_t &v) { return make_uint4(v.x, v.y, v.z, v.w); }
+// v shifted down by sh elements (0..7), zeros entering at the top: of 8 packed bf16 values,
+// and of 8 floats in two halves
+__device__ __forceinline__ void shift_down(u32x4_t &v, int sh) {
+  const u32x4_t z4 = {v.z, v.w, 0u, 0u};
+  if (sh & 4) v = z4;
+  const u32x4_t z2 = {v.y, v.z, v.w, 0u};
+  if (sh & 2) v = z2;
+  const u32x4_t z1 = {__builtin_amdgcn_alignbit(v.y, v.x, 16), __builtin_amdgcn_alignbit(v.z, v.y, 16),
+                      __builtin_amdgcn_alignbit(v.w, v.z, 16), v.w >> 16};
+  if (sh & 1) v = z1;
+}
+__device__ __forceinline__ void shift_down(u32x4_t &a, u32x4_t &b, int sh) {
+  const u32x4_t zero = {0u, 0u, 0u, 0u};
+  if (sh & 4) {
+    a = b;
+    b = zero;
+  }
+  const u32x4_t a2 = {a.z, a.w, b.x, b.y}, b2 = {b.z, b.w, 0u, 0u};
+  if (sh & 2) {
+    a = a2;
+    b = b2;
+  }
+  const u32x4_t a1 = {a.y, a.z, a.w, b.x}, b1 = {b.y, b.z, b.w, 0u};
+  if (sh & 1) {
+    a = a1;
+    b = b1;
+  }
+}
+
+// Rows at any position: 16-byte loads and stores of 8 bf16 values at a 2-byte position, and of 4
+// floats at a 4-byte position (the hardware takes both; on aligned addresses at full speed)
+// (types of their own, not template arguments, which would drop the alignment)
+typedef unsigned u32x4_u2_t __attribute__((ext_vector_type(4), aligned(2)));
+typedef float f32x4_u4_t __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ u32x4_t ldg_u(const uint16_t *p) {
+  return __builtin_nontemporal_load((const __attribute__((address_space(1))) u32x4_u2_t *)p);
+}
+__device__ __forceinline__ u32x4_t ldg_u(const float *p) {
+  return __builtin_bit_cast(u32x4_t, (f32x4_t)*(const __attribute__((address_space(1))) f32x4_u4_t *)p);
+}
+__device__ __forceinline__ void stg_u(uint16_t *p, u32x4_t v) {
+  __builtin_nontemporal_store((u32x4_u2_t)v, (__attribute__((address_space(1))) u32x4_u2_t *)p);
+}
+__device__ __forceinline__ void stg_u(float *p, f32x4_t v) {
+  *(__attribute__((address_space(1))) f32x4_u4_t *)p = v;
+}
+
+// The lane's 8 columns of a row of m: how many of them lie past its end (0 for all lanes but
+// the last). Such a lane loads the row's last 8 elements and shifts the ones before its own
+// out; a row of fewer than 8 is loaded element by element. Elements past the end read as 0.
+struct Cols8 {
+  int64_t col;
+  int over;      // columns past the row's end
+  bool narrow;   // m < 8
+  __device__ __forceinline__ Cols8(int64_t m, int64_t c)
+      : col(c), over(c + 8 > m ? (int)(c + 8 - m) : 0), narrow(m < 8) {}
+  __device__ __forceinline__ int count() const { return 8 - over; }
+};
+__device__ __forceinline__ u32x4_t load8(const uint16_t *row, const Cols8 &c) {
+  u32x4_t v = {0u, 0u, 0u, 0u};
+  if (c.narrow) {
 #pragma unroll
-      for (int e = 0; e < 8; e++) g[e] = 0.f;
-    }
+    for (int e = 0; e < 8; e++)
+      if (e < c.count()) v[e >> 1] |= (uint32_t)ldg(row + c.col + e) << (16 * (e & 1));
+  } else {
+    v = ldg_u(row + c.col - c.over);
+    if (c.over) shift_down(v, c.over);
+  }
+  return v;
+}
+__device__ __forceinline__ void load8(const float *row, const Cols8 &c, float *o) {
+  u32x4_t a = {0u, 0u, 0u, 0u}, b = a;
+  if (c.narrow) {
+#pragma unroll
+    for (int e = 0; e < 8; e++)
+      if (e < c.count()) (e < 4 ? a : b)[e & 3] = __float_as_uint(ldg(row + c.col + e));
+  } else {
+    a = ldg_u(row + c.col - c.over);
+    b = ldg_u(row + c.col - c.over + 4);
+    if (c.over) shift_down(a, b, c.over);
+  }
+#pragma unroll
+  for (int e = 0; e < 4; e++) {
+    o[e] = __uint_as_float(a[e]);
+    o[4 + e] = __uint_as_float(b[e]);
+  }
+}
+__device__ __forceinline__ void store8(float *row, const Cols8 &c, const float *v) {
+  if (c.over == 0) {
+    stg_u(row + c.col, f32x4_t{v[0], v[1], v[2], v[3]});
+    stg_u(row + c.col + 4, f32x4_t{v[4], v[5], v[6], v[7]});
   } else {
 #pragma unroll
-    for (int e = 0; e < 8; e++) g[e] = (col + e < t.m) ? bf_one(ldg(row + col + e)) : 0.f;
+    for (int e = 0; e < 8; e++)
+      if (e < c.count()) stg(row + c.col + e, v[e]);
+  }
+}
+__device__ __forceinline__ void store8(uint16_t *row, const Cols8 &c, const uint4 &v) {
+  if (c.over == 0) {
+    stg_u(row + c.col, u32x4_t{v.x, v.y, v.z, v.w});
+  } else {
+    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int e = 0; e < 8; e++)
+      if (e < c.count()) stg(row + c.col + e, (uint16_t)(w[e >> 1] >> (16 * (e & 1))));
+  }
+}
+// 8 elements of a weight or gradient row, bf16 or float32 (float32 masters)
+__device__ __forceinline__ void load_elems8(const uint16_t *base, int64_t row_off, const Cols8 &c, bool fp32, float *o) {
+  if (fp32)
+    load8(reinterpret_cast<const float *>(base) + row_off, c, o);
+  else
+    unpack8(to_uint4(load8(base + row_off, c)), o);
+}
+
+__device__ __forceinline__ void load_g8(const DevTensor &t, int64_t i, int64_t col, float *g) {
+  if (col < t.m) {
+    unpack8(to_uint4(load8(t.g + i * t.ld, Cols8(t.m, col))), g);
+  } else {
+#pragma unroll
+    for (int e = 0; e < 8; e++) g[e] = 0.f;
   }
 }
 
@@ -411,36 +532,6 @@ __global__ __launch_bounds__(kThreads) void p1_kernel(const DevTensor *__restric
 // --------------------------------------------------------------------------------------------
 // s_waitcnt immediate (gfx9 encoding): lgkmcnt(0) only
 constexpr int kWaitLgkm0 = 0xC07F;
-__device__ __forceinline__ uint4 to_uint4(const u32x4_t &v) { return make_uint4(v.x, v.y, v.z, v.w); }
-
-// v shifted down by sh elements (0..7), zeros entering at the top: of 8 packed bf16 values,
-// and of 8 floats in two halves
-__device__ __forceinline__ void shift_down(u32x4_t &v, int sh) {
-  const u32x4_t z4 = {v.z, v.w, 0u, 0u};
-  if (sh & 4) v = z4;
-  const u32x4_t z2 = {v.y, v.z, v.w, 0u};
-  if (sh & 2) v = z2;
-  const u32x4_t z1 = {__builtin_amdgcn_alignbit(v.y, v.x, 16), __builtin_amdgcn_alignbit(v.z, v.y, 16),
-                      __builtin_amdgcn_alignbit(v.w, v.z, 16), v.w >> 16};
-  if (sh & 1) v = z1;
-}
-__device__ __forceinline__ void shift_down(u32x4_t &a, u32x4_t &b, int sh) {
-  const u32x4_t zero = {0u, 0u, 0u, 0u};
-  if (sh & 4) {
-    a = b;
-    b = zero;
-  }
-  const u32x4_t a2 = {a.z, a.w, b.x, b.y}, b2 = {b.z, b.w, 0u, 0u};
-  if (sh & 2) {
-    a = a2;
-    b = b2;
-  }
-  const u32x4_t a1 = {a.y, a.z, a.w, b.x}, b1 = {b.y, b.z, b.w, 0u};
-  if (sh & 1) {
-    a = a1;
-    b = b1;
-  }
-}
 
 // bytes of a buffer's range (0 where a band has no block at all)
 __device__ __forceinline__ int clamp_span(int64_t bytes) {
@@ -1019,7 +1110,7 @@ __device__ __forceinline__ void fold_sum(const double *a, const double *b, int n
       if (one)
         v.x = ldg(p);
       else
-        v = ldg(reinterpret_cast<const f64x2_t *>(p));
+        v = *(const __attribute__((address_space(1))) f64x2_t *)p;
       if (back) v.x = v.y;
       return v;
     };
@@ -1222,15 +1313,14 @@ __global__ __launch_bounds__(kThreads) void gsq_kernel(const DevTensor *__restri
   const Tile tl = tile_of(t, it.tile / kSub);
   const WaveMap wm(t, tl);
   const int64_t r0 = wm.wr + (int64_t)(it.tile % kSub) * wm.rpi, rs = (int64_t)wm.rpi * kSub;
+  const Cols8 cols(t.m, wm.col);
   double acc = 0.0;
-  for (int64_t lr = r0; lr < tl.nr; lr += rs) {
+  for (int64_t lr = r0; wm.col < t.m && lr < tl.nr; lr += rs) {
     const int64_t i = tl.row(lr);
+    float g[8];
+    load_elems8(t.g, i * t.ld, cols, t.fp32, g);
 #pragma unroll
-    for (int e = 0; e < 8; e++) {
-      if (wm.col + e >= t.m) continue;
-      const double g = (double)elem(t.g, i * t.ld + wm.col + e, t.fp32);
-      acc += g * g;
-    }
+    for (int e = 0; e < 8; e++) acc += (double)g[e] * (double)g[e];   // (0 past the row's end)
   }
   const double s = block_sum(acc, sh);
   if (threadIdx.x == 0) stg(t.ssum + it.tile, s);
@@ -1299,11 +1389,12 @@ __device__ __forceinline__ SumPair p2_factored(const DevTensor &t, const Tile &t
   const float gc = k.gclip ? ldg(k.gscale) : 1.f;     // gradient-norm mode: elements are fl(c g)
   SumPair acc = {0.0, 0.0};
   if (col >= m) return acc;
-  float cp[8];    // c'_j = C_j / q, rounded as the oracle
+  const Cols8 cols(m, col);
+  float cp[8];    // c'_j = C_j / q, rounded as the oracle (1 past the row's end, where x is 0)
   double bd[8];   // 1/sqrt(c'_j) to about 2^-50 (it scales the unrounded estimate only)
 #pragma unroll
   for (int e = 0; e < 8; e++) {
-    cp[e] = (col + e < m) ? ldg(t.C + col + e) / q : 0.f;
+    cp[e] = (col + e < m) ? ldg(t.C + col + e) / q : 1.f;
     const double cd = (double)cp[e];
     bd[e] = (cp[e] > 0.f && cp[e] < __builtin_inff()) ? rsq_d(cd) : 1.0 / sqrt(cd);
   }
@@ -1318,62 +1409,45 @@ __device__ __forceinline__ SumPair p2_factored(const DevTensor &t, const Tile &t
     const double u2 = floored ? 0.0 : ud * ud;
     a.q4 = fma(u2, u2, a.q4);
   };
-  if (t.vec) {
-    for (int64_t lr = r0; lr < tl.nr; lr += 2 * rs) {
-      const bool two = lr + rs < tl.nr;
-      const int64_t i = tl.row(lr), i2 = two ? tl.row(lr + rs) : i;
-      const uint4 ga = ldg(reinterpret_cast<const uint4 *>(t.g + i * ld + col));
-      const uint4 gb = ldg(reinterpret_cast<const uint4 *>(t.g + i2 * ld + col));
-      float ma[8], mb[8];
-      if (mom) {
-        load_m8(t.M + i * m + col, ma);
-        load_m8(t.M + i2 * m + col, mb);
-      }
-      const float Ra = ldg(t.R + i), Rb = ldg(t.R + i2);
-      const double aa = ldg(t.ainv + i), ab = ldg(t.ainv + i2);
-      float xa[8], xb[8];
-      unpack8(ga, xa);
-      unpack8(gb, xb);
-      if (k.gclip) {
-#pragma unroll
-        for (int e = 0; e < 8; e++) {
-          xa[e] = gc * xa[e];
-          xb[e] = gc * xb[e];
-        }
-      }
-      if (mom) {
-#pragma unroll
-        for (int e = 0; e < 8; e++) {
-          xa[e] = fmaf(k.a1, xa[e], __fmul_rn(k.b1, ma[e]));
-          xb[e] = fmaf(k.a1, xb[e], __fmul_rn(k.b1, mb[e]));
-        }
-      }
-      SumPair sa = {0.0, 0.0}, sb = {0.0, 0.0};
+  for (int64_t lr = r0; lr < tl.nr; lr += 2 * rs) {
+    const bool two = lr + rs < tl.nr;
+    const int64_t i = tl.row(lr), i2 = two ? tl.row(lr + rs) : i;
+    const u32x4_t ga = load8(t.g + i * ld, cols), gb = load8(t.g + i2 * ld, cols);
+    float ma[8], mb[8];
+    if (mom) {
+      load8(t.M + i * m, cols, ma);
+      load8(t.M + i2 * m, cols, mb);
+    }
+    const float Ra = ldg(t.R + i), Rb = ldg(t.R + i2);
+    const double aa = ldg(t.ainv + i), ab = ldg(t.ainv + i2);
+    float xa[8], xb[8];
+    unpack8(to_uint4(ga), xa);
+    unpack8(to_uint4(gb), xb);
+    if (k.gclip) {
 #pragma unroll
       for (int e = 0; e < 8; e++) {
-        elem(xa[e], Ra, aa, e, sa);
-        elem(xb[e], Rb, ab, e, sb);
-      }
-      acc.s += sa.s;
-      acc.q4 += sa.q4;
-      if (two) {
-        acc.s += sb.s;
-        acc.q4 += sb.q4;
+        xa[e] = gc * xa[e];
+        xb[e] = gc * xb[e];
       }
     }
-  } else {
-    for (int64_t lr = r0; lr < tl.nr; lr += rs) {
-      const int64_t i = tl.row(lr);
-      const float Ri = ldg(t.R + i);
-      const double ai = ldg(t.ainv + i);
+    if (mom) {
 #pragma unroll
       for (int e = 0; e < 8; e++) {
-        if (col + e >= m) continue;
-        float x = bf_one(ldg(t.g + i * ld + col + e));
-        if (k.gclip) x = gc * x;
-        if (mom) x = fmaf(k.a1, x, __fmul_rn(k.b1, ldg(t.M + i * m + col + e)));
-        elem(x, Ri, ai, e, acc);
+        xa[e] = fmaf(k.a1, xa[e], __fmul_rn(k.b1, ma[e]));
+        xb[e] = fmaf(k.a1, xb[e], __fmul_rn(k.b1, mb[e]));
       }
+    }
+    SumPair sa = {0.0, 0.0}, sb = {0.0, 0.0};
+#pragma unroll
+    for (int e = 0; e < 8; e++) {
+      elem(xa[e], Ra, aa, e, sa);
+      elem(xb[e], Rb, ab, e, sb);
+    }
+    acc.s += sa.s;
+    acc.q4 += sa.q4;
+    if (two) {
+      acc.s += sb.s;
+      acc.q4 += sb.q4;
     }
   }
   return acc;
@@ -1391,37 +1465,22 @@ __device__ __forceinline__ double p2_factored_exact(const DevTensor &t, const Ti
   const float gc = k.gclip ? ldg(k.gscale) : 1.f;
   double acc = 0.0;
   if (col >= m) return 0.0;
-  float cp[8];
+  const Cols8 cols(m, col);
+  float cp[8];   // (1 past the row's end, where x is 0)
 #pragma unroll
-  for (int e = 0; e < 8; e++) cp[e] = (col + e < m) ? ldg(t.C + col + e) / q : 0.f;
-  if (t.vec) {   // 16-byte rows: 8 elements per load
-    for (int64_t lr = r0; lr < tl.nr; lr += rs) {
-      const int64_t i = tl.row(lr);
-      const float Ri = ldg(t.R + i);
-      float x[8], mo[8];
-      unpack8(ldg(reinterpret_cast<const uint4 *>(t.g + i * ld + col)), x);
-      if (mom) load_m8(t.M + i * m + col, mo);
-#pragma unroll
-      for (int e = 0; e < 8; e++) {
-        // the momentum update takes the scaled gradient (as in the update pass)
-        const float xs = k.gclip ? gc * x[e] : x[e];
-        const float xm = mom ? fmaf(k.a1, xs, __fmul_rn(k.b1, mo[e])) : xs;
-        const float u = __fmul_rn(s, xm) / sqrtf(max_nan(__fmul_rn(Ri, cp[e]), k.eps));
-        acc = fma((double)u, (double)u, acc);
-      }
-    }
-    return acc;
-  }
+  for (int e = 0; e < 8; e++) cp[e] = (col + e < m) ? ldg(t.C + col + e) / q : 1.f;
   for (int64_t lr = r0; lr < tl.nr; lr += rs) {
     const int64_t i = tl.row(lr);
     const float Ri = ldg(t.R + i);
+    float x[8], mo[8];
+    unpack8(to_uint4(load8(t.g + i * ld, cols)), x);
+    if (mom) load8(t.M + i * m, cols, mo);
 #pragma unroll
     for (int e = 0; e < 8; e++) {
-      if (col + e >= m) continue;
-      float x = bf_one(ldg(t.g + i * ld + col + e));
-      if (k.gclip) x = gc * x;
-      if (mom) x = fmaf(k.a1, x, __fmul_rn(k.b1, ldg(t.M + i * m + col + e)));
-      const float u = __fmul_rn(s, x) / sqrtf(max_nan(__fmul_rn(Ri, cp[e]), k.eps));
+      // the momentum update takes the scaled gradient (as in the update pass)
+      const float xs = k.gclip ? gc * x[e] : x[e];
+      const float xm = mom ? fmaf(k.a1, xs, __fmul_rn(k.b1, mo[e])) : xs;
+      const float u = __fmul_rn(s, xm) / sqrtf(max_nan(__fmul_rn(Ri, cp[e]), k.eps));
       acc = fma((double)u, (double)u, acc);
     }
   }
@@ -1435,18 +1494,20 @@ __device__ __forceinline__ double p2_exact(const DevTensor &t, const Tile &tl, i
   const int64_t m = t.m, ld = t.ld, col = wm.col;
   const bool mom = t.momentum != 0;
   const float gc = k.gclip ? ldg(k.gscale) : 1.f;
+  const Cols8 cols(m, col);
   double acc = 0.0;
-  for (int64_t lr = r0; lr < tl.nr; lr += rs) {
+  for (int64_t lr = r0; col < m && lr < tl.nr; lr += rs) {
     const int64_t i = tl.row(lr);
+    float g[8], v[8], mo[8];
+    load_elems8(t.g, i * ld, cols, t.fp32, g);
+    load8(t.V + i * m, cols, v);
+    if (mom) load8(t.M + i * m, cols, mo);
 #pragma unroll
-    for (int e = 0; e < 8; e++) {
-      if (col + e >= m) continue;
-      const int64_t sidx = i * m + col + e;
-      float g = elem(t.g, i * ld + col + e, t.fp32);
-      if (k.gclip) g = gc * g;
-      const float vn = fmaf(k.a2, __fmul_rn(g, g), __fmul_rn(k.b2, ldg(t.V + sidx)));
+    for (int e = 0; e < 8; e++) {   // (0 past the row's end)
+      if (k.gclip) g[e] = gc * g[e];
+      const float vn = fmaf(k.a2, __fmul_rn(g[e], g[e]), __fmul_rn(k.b2, v[e]));
       const float dd = sqrtf(max_nan(vn, k.eps));
-      const float num = mom ? __fmul_rn(k.s_m, fmaf(k.a1, g, __fmul_rn(k.b1, ldg(t.M + sidx)))) : __fmul_rn(k.s_0, g);
+      const float num = mom ? __fmul_rn(k.s_m, fmaf(k.a1, g[e], __fmul_rn(k.b1, mo[e]))) : __fmul_rn(k.s_0, g[e]);
       const float u = num / dd;
       acc += (double)u * (double)u;
     }
@@ -1989,14 +2050,16 @@ struct P3Scalars {
   double lsk;
 };
 
-// one row segment of 8 elements (vector path): momentum, update, dither, bf16 store.
-// The fast path forms 1/D from per-row and per-column factors; the few elements whose
-// result might round to the other bf16 neighbour take the oracle's exact sequence.
-template <bool XU, bool DEC, bool GC>
+// one row segment of 8 elements: momentum, update, dither, bf16 store. The fast path forms 1/D
+// from per-row and per-column factors; the few elements whose result might round to the other
+// bf16 neighbour take the oracle's exact sequence. RAG: the row may start at any position and
+// end within the 8 columns.
+template <bool XU, bool DEC, bool GC, bool RAG>
 __device__ __forceinline__ void p3_row8(const DevTensor &t, const StepConsts &k, const P3Scalars &c,
-                                        const Dither &dz, int64_t i, int64_t col, const float *bf, uint4 gw,
+                                        const Dither &dz, int64_t i, const Cols8 &cols, const float *bf, uint4 gw,
                                         uint4 ww, const float *mv) {
   const bool mom = t.momentum != 0;
+  const int64_t col = cols.col;
   float x[8], w[8];
   unpack8(gw, x);
   unpack8(ww, w);
@@ -2007,21 +2070,29 @@ __device__ __forceinline__ void p3_row8(const DevTensor &t, const StepConsts &k,
   if (mom) {
 #pragma unroll
     for (int e = 0; e < 8; e++) x[e] = fmaf(k.a1, x[e], __fmul_rn(k.b1, mv[e]));
-    store_m8(t.M + i * t.m + col, x);
+    if constexpr (RAG)
+      store8(t.M + i * t.m, cols, x);
+    else
+      store_m8(t.M + i * t.m + col, x);
   }
   const float alpha = (float)(c.lsk * ldg(t.ainv + i));
-  // pairs p0 .. p0 + 3: m and col are multiples of 8, so p0 is a multiple of 4 and the
-  // four pairs share their high word and differ only in the low two bits
-  const uint64_t p0 = ((uint64_t)t.idx0 + (uint64_t)i * (uint64_t)t.m + (uint64_t)col) >> 1;
   // pair indices reach 2^32 only in tensors of more than 2^33 elements (a uniform test)
-  const uint32_t base =
-      (t.idx0 + t.n * t.m > (int64_t(1) << 33)) ? dz.pair_base(p0) : ((uint32_t)p0 ^ dz.klo ^ dz.inner0);
+  const bool wide = t.idx0 + t.n * t.m > (int64_t(1) << 33);
+  const uint64_t idx = (uint64_t)t.idx0 + (uint64_t)i * (uint64_t)t.m + (uint64_t)col;
   float y[8], dith[8];
+  if constexpr (RAG) {
+    dither8(dz, idx, wide, dith);
+  } else {
+    // pairs p0 .. p0 + 3: m and col are multiples of 8, so p0 is a multiple of 4 and the
+    // four pairs share their high word and differ only in the low two bits
+    const uint64_t p0 = idx >> 1;
+    const uint32_t base = wide ? dz.pair_base(p0) : ((uint32_t)p0 ^ dz.klo ^ dz.inner0);
 #pragma unroll
-  for (int e2 = 0; e2 < 4; e2++) {
-    const uint32_t h = fmix32(base ^ (uint32_t)e2);
-    dith[2 * e2] = dither_lo(h);
-    dith[2 * e2 + 1] = dither_hi(h);
+    for (int e2 = 0; e2 < 4; e2++) {
+      const uint32_t h = fmix32(base ^ (uint32_t)e2);
+      dith[2 * e2] = dither_lo(h);
+      dith[2 * e2 + 1] = dither_hi(h);
+    }
   }
   const bool dec = DEC && t.decay;
   constexpr bool xu = XU;
@@ -2037,23 +2108,27 @@ __device__ __forceinline__ void p3_row8(const DevTensor &t, const StepConsts &k,
 #pragma unroll
     for (int e = 0; e < 8; e++) {
       const float F = fminf(alpha * bf[e], c.cap3);
-      if (near_boundary(y[e], x[e] * F, w[e]))
+      if ((!RAG || e < cols.count()) && near_boundary(y[e], x[e] * F, w[e]))
         y[e] = exact_factored_y(x[e], w[e], decayed(w[e], dec, k.wd), Ri, ldg(t.C + col + e) / c.q, c.s, c.kc,
                                 c.eps, c.lr, dith[e], xu);
     }
   }
-  stg_nt(reinterpret_cast<uint4 *>(t.w + i * t.ld + col),
-         make_uint4(pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3]), pack_bf16x2(y[4], y[5]),
-                    pack_bf16x2(y[6], y[7])));
+  const uint4 out = make_uint4(pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3]), pack_bf16x2(y[4], y[5]),
+                               pack_bf16x2(y[6], y[7]));
+  if constexpr (RAG)
+    store8(t.w + i * t.ld, cols, out);
+  else
+    stg_nt(reinterpret_cast<uint4 *>(t.w + i * t.ld + col), out);
 }
 
-template <bool XU, bool DEC, bool GC>
+template <bool XU, bool DEC, bool GC, bool RAG>
 __device__ __forceinline__ void p3_factored(const DevTensor &t, const Tile &tl, const StepConsts &k, float kc,
                                             float q, const Dither &dz) {
   const WaveMap wm(t, tl);
   const int64_t m = t.m, ld = t.ld, col = wm.col;
   const bool mom = t.momentum != 0;
   if (col >= m) return;
+  const Cols8 cols(m, col);
   P3Scalars c;
   c.q = q;
   c.s = mom ? k.s_m : k.s_0;
@@ -2063,51 +2138,36 @@ __device__ __forceinline__ void p3_factored(const DevTensor &t, const Tile &tl, 
   c.lsk = (double)k.lr * (double)c.s * (double)kc;   // lr * s * k
   c.gc = GC ? ldg(k.gscale) : 1.f;             // gradient-norm mode: elements are fl(c g)
   c.cap3 = (float)(c.lsk / (double)sqrtf(k.eps));
-  if (t.vec) {
-    float bf[8];
+  float bf[8];
 #pragma unroll
-    for (int e = 0; e < 8; e++) bf[e] = (float)col_factor(t, col + e, c.q);
-    for (int64_t lr = wm.wr; lr < tl.nr; lr += 2 * wm.rpi) {
-      const bool two = lr + wm.rpi < tl.nr;
-      const int64_t i = tl.row(lr), i2 = two ? tl.row(lr + wm.rpi) : i;
-      const uint4 ga = ldg_nt(reinterpret_cast<const uint4 *>(t.g + i * ld + col));
-      const uint4 wa = ldg_nt(reinterpret_cast<const uint4 *>(t.w + i * ld + col));
-      const uint4 gb = ldg_nt(reinterpret_cast<const uint4 *>(t.g + i2 * ld + col));
-      const uint4 wb = ldg_nt(reinterpret_cast<const uint4 *>(t.w + i2 * ld + col));
-      float ma[8], mb[8];
-      if (mom) {
+  for (int e = 0; e < 8; e++) bf[e] = !RAG || e < cols.count() ? (float)col_factor(t, col + e, c.q) : 0.f;
+  for (int64_t lr = wm.wr; lr < tl.nr; lr += 2 * wm.rpi) {
+    const bool two = lr + wm.rpi < tl.nr;
+    const int64_t i = tl.row(lr), i2 = two ? tl.row(lr + wm.rpi) : i;
+    uint4 ga, wa, gb, wb;
+    float ma[8], mb[8];
+    if constexpr (RAG) {
+      ga = to_uint4(load8(t.g + i * ld, cols));
+      wa = to_uint4(load8(t.w + i * ld, cols));
+      gb = to_uint4(load8(t.g + i2 * ld, cols));
+      wb = to_uint4(load8(t.w + i2 * ld, cols));
+    } else {
+      ga = ldg_nt(reinterpret_cast<const uint4 *>(t.g + i * ld + col));
+      wa = ldg_nt(reinterpret_cast<const uint4 *>(t.w + i * ld + col));
+      gb = ldg_nt(reinterpret_cast<const uint4 *>(t.g + i2 * ld + col));
+      wb = ldg_nt(reinterpret_cast<const uint4 *>(t.w + i2 * ld + col));
+    }
+    if (mom) {
+      if constexpr (RAG) {
+        load8(t.M + i * m, cols, ma);
+        load8(t.M + i2 * m, cols, mb);
+      } else {
         load_m8(t.M + i * m + col, ma);
         load_m8(t.M + i2 * m + col, mb);
       }
-      p3_row8<XU, DEC, GC>(t, k, c, dz, i, col, bf, ga, wa, ma);
-      if (two) p3_row8<XU, DEC, GC>(t, k, c, dz, i2, col, bf, gb, wb, mb);
     }
-  } else {
-    for (int64_t lr = wm.wr; lr < tl.nr; lr += wm.rpi) {
-    const int64_t i = tl.row(lr);
-      const float alpha = (float)(c.lsk * ldg(t.ainv + i));
-      const uint64_t rowidx = (uint64_t)t.idx0 + (uint64_t)i * (uint64_t)m;
-#pragma unroll
-      for (int e = 0; e < 8; e++) {
-        if (col + e >= m) continue;
-        float x = bf_one(ldg(t.g + i * ld + col + e));
-        const float w = bf_one(ldg(t.w + i * ld + col + e));
-        if (GC) x = c.gc * x;
-        if (mom) {
-          x = fmaf(k.a1, x, __fmul_rn(k.b1, ldg(t.M + i * m + col + e)));
-          stg(t.M + i * m + col + e, x);
-        }
-        const uint64_t idx = rowidx + (uint64_t)(col + e);
-        const float dith = dither_of(dz.pair(idx >> 1), idx);
-        const float F = fminf(alpha * (float)col_factor(t, col + e, c.q), c.cap3);
-        const float wd = decayed(w, DEC && t.decay, k.wd);
-        constexpr bool xu = XU;
-        float y = fmaf(dith, dither_mul(w, xu), fmaf(-x, F, wd));
-        if (near_boundary(y, x * F, w))
-          y = exact_factored_y(x, w, wd, ldg(t.R + i), ldg(t.C + col + e) / c.q, c.s, kc, k.eps, k.lr, dith, xu);
-        stg(t.w + i * ld + col + e, to_bf16(y));
-      }
-    }
+    p3_row8<XU, DEC, GC, RAG>(t, k, c, dz, i, cols, bf, ga, wa, ma);
+    if (two) p3_row8<XU, DEC, GC, RAG>(t, k, c, dz, i2, cols, bf, gb, wb, mb);
   }
 }
 
@@ -2118,38 +2178,44 @@ __device__ __forceinline__ void p3_exact(const DevTensor &t, const Tile &tl, con
   const WaveMap wm(t, tl);
   const int64_t m = t.m, ld = t.ld, col = wm.col;
   const bool mom = t.momentum != 0;
+  if (col >= m) return;
+  const Cols8 cols(m, col);
   const float gc = GC ? ldg(k.gscale) : 1.f;
+  const bool wide = t.idx0 + t.n * t.m > (int64_t(1) << 33);
+  constexpr bool xu = XU;
   for (int64_t lr = wm.wr; lr < tl.nr; lr += wm.rpi) {
     const int64_t i = tl.row(lr);
+    float g[8], w[8], v[8], mo[8];
+    load_elems8(t.g, i * ld, cols, t.fp32, g);
+    load_elems8(t.w, i * ld, cols, t.fp32, w);
+    load8(t.V + i * m, cols, v);
+    if (mom) load8(t.M + i * m, cols, mo);
+    float dith[8];
+    if (!t.fp32) dither8(dz, (uint64_t)t.idx0 + (uint64_t)i * (uint64_t)m + (uint64_t)col, wide, dith);
 #pragma unroll
     for (int e = 0; e < 8; e++) {
-      if (col + e >= m) continue;
-      const int64_t sidx = i * m + col + e;
-      float g = elem(t.g, i * ld + col + e, t.fp32);
-      if (GC) g = gc * g;
-      const float w = elem(t.w, i * ld + col + e, t.fp32);
-      const float vn = fmaf(k.a2, __fmul_rn(g, g), __fmul_rn(k.b2, ldg(t.V + sidx)));
-      stg(t.V + sidx, vn);
-      const float dd = sqrtf(max_nan(vn, k.eps));
+      if (GC) g[e] = gc * g[e];
+      v[e] = fmaf(k.a2, __fmul_rn(g[e], g[e]), __fmul_rn(k.b2, v[e]));
+      const float dd = sqrtf(max_nan(v[e], k.eps));
       float num;
       if (mom) {
-        const float mn = fmaf(k.a1, g, __fmul_rn(k.b1, ldg(t.M + sidx)));
-        stg(t.M + sidx, mn);
-        num = __fmul_rn(k.s_m, mn);
+        mo[e] = fmaf(k.a1, g[e], __fmul_rn(k.b1, mo[e]));
+        num = __fmul_rn(k.s_m, mo[e]);
       } else {
-        num = __fmul_rn(k.s_0, g);
+        num = __fmul_rn(k.s_0, g[e]);
       }
       const float U = __fmul_rn(num / dd, kc);
-      const float x = fmaf(-k.lr, U, decayed(w, DEC && t.decay, k.wd));
-      if (t.fp32) {   // float32 master: no dither, no cast
-        stg(reinterpret_cast<float *>(t.w) + i * ld + col + e, x);
-        continue;
-      }
-      const uint64_t idx = (uint64_t)(t.idx0 + sidx);
-      constexpr bool xu = XU;
-      const float y = fmaf(dither_of(dz.pair(idx >> 1), idx), dither_mul(w, xu), x);
-      stg(t.w + i * ld + col + e, to_bf16(y));
+      const float x = fmaf(-k.lr, U, decayed(w[e], DEC && t.decay, k.wd));
+      // (float32 masters: no dither, no cast)
+      w[e] = t.fp32 ? x : fmaf(dith[e], dither_mul(w[e], xu), x);
     }
+    store8(t.V + i * m, cols, v);
+    if (mom) store8(t.M + i * m, cols, mo);
+    if (t.fp32)
+      store8(reinterpret_cast<float *>(t.w) + i * ld, cols, w);
+    else
+      store8(t.w + i * ld, cols, make_uint4(pack_bf16x2(w[0], w[1]), pack_bf16x2(w[2], w[3]),
+                                            pack_bf16x2(w[4], w[5]), pack_bf16x2(w[6], w[7])));
   }
 }
 
@@ -2157,9 +2223,11 @@ __device__ __forceinline__ void p3_exact(const DevTensor &t, const Tile &tl, con
 // p3: clip factor, state update, weight update and dithered bf16 write-back (Alg. 1)
 // --------------------------------------------------------------------------------------------
 // XU: the exact-ulp dither; DEC: the decoupled weight decay is on (lr lambda != 0); GC: the
-// gradient-norm mode (elements enter as fl(c g))
+// gradient-norm mode (elements enter as fl(c g)); RAG: the table has a factored tensor whose rows
+// are not all 16-byte aligned multiples of 8 columns (its path takes registers from the other:
+// with both in every instantiation the 6.78B-like tables' pass ran 1.5% slower)
 // (at most 128 VGPRs: four waves per SIMD keep enough loads in flight)
-template <bool XU, bool DEC, bool GC>
+template <bool XU, bool DEC, bool GC, bool RAG>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) void p3_kernel(const DevTensor *__restrict__ TT,
                                                       const Item *__restrict__ items, StepConsts k,
                                                       RecheckLists *L) {
@@ -2173,9 +2241,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
   const Tile tl = tile_of(t, it.tile);
   const float kc = ldg(&t.sc->k);
   const Dither dz(k.seed, k.step, t.tensor_id);
-  if (t.kind == kFactored)
-    p3_factored<XU, DEC, GC>(t, tl, k, kc, ldg(&t.sc->q), dz);
-  else
+  if (t.kind == kFactored) {
+    if (!RAG || t.vec)
+      p3_factored<XU, DEC, GC, false>(t, tl, k, kc, ldg(&t.sc->q), dz);
+    else if constexpr (RAG)
+      p3_factored<XU, DEC, GC, true>(t, tl, k, kc, ldg(&t.sc->q), dz);
+  } else
     p3_exact<XU, DEC, GC>(t, tl, k, kc, dz);
 }
 
@@ -2275,10 +2346,14 @@ int launch_p3(const DevTensor *T, const Item *items, int64_t count, const StepCo
               void *stream) {
   if (count <= 0) return hipSuccess;
   const bool xu = (k.flags & SKEW_FLAG_EXACT_ULP) != 0, dec = k.wd != 0.f, gc = k.gclip != 0;
-  auto *kern = xu ? (dec ? (gc ? p3_kernel<true, true, true> : p3_kernel<true, true, false>)
-                         : (gc ? p3_kernel<true, false, true> : p3_kernel<true, false, false>))
-                  : (dec ? (gc ? p3_kernel<false, true, true> : p3_kernel<false, true, false>)
-                         : (gc ? p3_kernel<false, false, true> : p3_kernel<false, false, false>));
+  auto pick = [&](auto x, auto d, auto g) {
+    return k.ragged ? p3_kernel<decltype(x)::value, decltype(d)::value, decltype(g)::value, true>
+                    : p3_kernel<decltype(x)::value, decltype(d)::value, decltype(g)::value, false>;
+  };
+  const std::true_type yes;
+  const std::false_type no;
+  auto *kern = xu ? (dec ? (gc ? pick(yes, yes, yes) : pick(yes, yes, no)) : (gc ? pick(yes, no, yes) : pick(yes, no, no)))
+                  : (dec ? (gc ? pick(no, yes, yes) : pick(no, yes, no)) : (gc ? pick(no, no, yes) : pick(no, no, no)));
   hipLaunchKernelGGL(kern, dim3((uint32_t)count), dim3(kThreads), 0, (hipStream_t)stream, T, items, k, L);
   return (int)hipGetLastError();
 }

@@ -50,9 +50,10 @@ static int64_t band_rows(const RowBandShape &r, int64_t m, bool momentum, int64_
 // end (kBandUs) and a row of column partials that the fold reads back (kFoldBytesPerUs for both).
 // Measured on one MI355X: 1.07e-4 us per element and compute unit (3.3 times that with
 // momentum), 3 us per band, 4 TB/s. 1.1e9 elements in bands of 2^21 / 2^20 / 2^19: 2.2, 4.4 and
-// 8.75 rounds, 724 / 608 / 561 us for the pass and 24 / 27 / 42 us for the fold. The partials of a
-// table with gradients of 2 GiB or more stay below 1/40 of them.
-constexpr double kCus = 256.0, kElemUs = 1.07e-4, kBandUs = 3.0, kFoldBytesPerUs = 2.0e6;
+// 8.75 rounds, 724 / 608 / 561 us for the pass and 24 / 27 / 42 us for the fold. The partials stay
+// below 256 MiB or 1/40 of the gradients.
+constexpr double kCus = 256.0, kElemUs = 1.07e-4, kBandUs = 3.0, kFoldBytesPerUs = 2.0e6,
+                 kFoldMaxBytes = 268435456.0;
 static int64_t choose_band_elems(const skew_tensor_desc *d, int n) {
   struct Shape {
     RowBandShape r;
@@ -94,7 +95,7 @@ static int64_t choose_band_elems(const skew_tensor_desc *d, int n) {
       bands += nb;
       bytes += nb * 16.0 * (double)s.m;
     }
-    if (bands <= 0.0 || (step > 0 && grad_bytes >= 2147483648.0 && bytes > grad_bytes / 40.0)) break;
+    if (bands <= 0.0 || (step > 0 && bytes > std::max(kFoldMaxBytes, grad_bytes / 40.0))) break;
     const double us = std::ceil(bands / kCus) * (cost / bands + kBandUs) + bytes / kFoldBytesPerUs;
     if (us < best_us) {
       best_us = us;
@@ -102,6 +103,22 @@ static int64_t choose_band_elems(const skew_tensor_desc *d, int n) {
     }
   }
   return best;
+}
+
+// Elements per update tile: kTileElems, or fewer where the table would not fill the chip with
+// them (four work-groups of the update pass fit a compute unit: kTileCount is two rounds), down to
+// kMinTileElems (a work-group of the pass takes 2048 elements at a time, and starts each tile
+// with its column factors). Update pass at tiles of 2^16 / 2^13 / 2^12 / 2^11 elements: 4.5e6
+// elements 39 / 18 / 21 / 29 us; 5.0e7 odd-width ones 142 us at 2^16, 110 at 2^14, 129 at 2^13.
+constexpr int64_t kMinTileElems = 1 << 13, kTileCount = 2048;
+static int64_t choose_tile_elems(const skew_tensor_desc *d, int n) {
+  double total = 0.0;
+  for (int i = 0; i < n; i++)
+    if (d[i].rows > 0 && d[i].cols > 0)
+      total += (double)d[i].rows * (double)d[i].cols * (d[i].ndim == 3 ? (double)std::max<int64_t>(d[i].batch, 0) : 1.0);
+  int64_t t = kTileElems;
+  while (t > kMinTileElems && total < (double)t * (double)kTileCount) t >>= 1;
+  return t;
 }
 
 int plan_build(const skew_tensor_desc *d, int n, Plan *out, bool compact) {
@@ -129,6 +146,7 @@ int plan_build(const skew_tensor_desc *d, int n, Plan *out, bool compact) {
   }
   p.t.resize((size_t)nsub);
   const int64_t band_elems = compact ? kZBandElems : choose_band_elems(d, n);
+  const int64_t tile_elems = compact ? kTileElems : choose_tile_elems(d, n);
   size_t st = 0;        // state bytes
   size_t ws_part = 0;   // partial-sum bytes (offsets relative to the partial region)
   int64_t items_total = 0;
@@ -169,6 +187,13 @@ int plan_build(const skew_tensor_desc *d, int n, Plan *out, bool compact) {
     tp.fp32 = (x.state_flags & SKEW_STATE_FP32) != 0 ? 1 : 0;
     if (tp.fp32 && tp.kind != kExact) return SKEW_EINVAL;   // float32 masters: exact-moment tensors
     if (tp.empty) continue;
+    // exact-moment tensors are elementwise: where the rows follow each other they are taken as rows
+    // of 2048 elements, or as one row (a 2048 x 128 router would leave three lanes of four idle)
+    if (tp.kind == kExact && tp.ld == tp.m && !compact) {
+      constexpr int64_t kRow = kChunk * kMaxCw;
+      tp.n = N % kRow == 0 ? N / kRow : 1;
+      tp.m = tp.ld = N / tp.n;
+    }
 
     // state slices: one contiguous array per descriptor (slice e at e times the slice)
     if (e == 0) {
@@ -202,7 +227,7 @@ int plan_build(const skew_tensor_desc *d, int n, Plan *out, bool compact) {
     const int64_t tc = (int64_t)kChunk * tp.cw;
     // (exact-moment tensors take a quarter of that: their element-by-element path is the
     // slowest per element, and their few tiles would otherwise finish last)
-    tp.tr = std::max<int64_t>(1, kTileElems / tc / (tp.kind == kExact ? 4 : 1));
+    tp.tr = std::max<int64_t>(1, tile_elems / tc / (tp.kind == kExact ? 4 : 1));
     const int64_t ntc = ceil_div(tp.m, tc), ntr = ceil_div(tp.n, tp.tr);
     if (ntc * ntr > INT32_MAX / 2 / kSub) return SKEW_EINVAL;   // tile * kSub + part fits an int32
     tp.ntc = (int32_t)ntc;

@@ -66,3 +66,34 @@ def test_row_widths_and_positions(tier, pad, shift, hp):
         assert bool((wb == 3.0).all()), s.name
         wb.copy_(keep)
         assert (bits(w) == bits(w_now)).all()
+
+
+@pytest.mark.parametrize("flags", [0, 2], ids=["plain", "exact_ulp"])
+@pytest.mark.parametrize("fp32", [False, True], ids=["bf16", "fp32"])
+def test_exact_moment_tensors_at_row_ends(fp32, flags):
+    """Routers and vectors (the exact second moment, taken 8 elements at a time): contiguous ones of
+    one element to several tiles, with and without a whole number of 2048-element rows, and
+    router views whose rows start at any position, with momentum (vectors of the backbone) and
+    without."""
+    sf = oracle.STATE_FP32 if fp32 else 0
+    shapes = [(W.ROUTER, (n, m)) for n, m in ((1, 1), (3, 5), (256, 8), (37, 7), (64, 96), (2049, 3), (130, 1031))]
+    shapes += [(tier, (n,)) for tier in (W.BACKBONE, W.EXPERT) for n in (1, 7, 8, 9, 2047, 2048, 2049, 10240, 10243)]
+    views = [W.Spec(f"rv{m}", W.ROUTER, (33, m), 100 + m, state_flags=sf) for m in (7, 8, 13, 130)]
+    specs = [W.Spec(f"x{k}", t, s, k, state_flags=sf) for k, (t, s) in enumerate(shapes)] + views
+    wl = W.Workload("exact", specs, 3)
+    dt = torch.float32 if fp32 else torch.bfloat16
+    ws, gs = [], []
+    for s in specs:
+        if s in views:
+            base = [torch.zeros(33 * (s.shape[1] + 3) + 9, dtype=dt, device="cuda") for _ in range(2)]
+            w, g = (b.as_strided(s.shape, (s.shape[1] + 3, 1), 1) for b in base)
+        else:
+            w, g = (torch.zeros(s.shape, dtype=dt, device="cuda") for _ in range(2))
+        w.copy_(W.init_weight(s, wl, torch.device("cuda")))
+        ws.append(w)
+        gs.append(g)
+    log(f"[parity] {len(specs)} exact-moment tensors, fp32={fp32}, flags={flags}; 3 steps")
+    pr = ParityRun(wl, weights=ws, grads=gs, hp=dict(oracle.DEFAULTS, weight_decay=0.05), flags=flags)
+    for t in (1, 2, 3):
+        pr.step(t)
+    assert pr.stats.ok(), pr.stats
