@@ -310,6 +310,47 @@ struct WaveMap {
   }
 };
 
+// Rows at most this far apart are packed: 64 rows' offsets stay below 2^31 bytes
+constexpr int64_t kPackLd = (int64_t(1) << 31) / 64 / 4;
+
+// The update pass's map: a wave keeps its chunk of 512 columns for the whole tile, and where the
+// chunk holds only `g` of the 64 groups of 8 columns (a narrow matrix, or the end of a row) its
+// lanes take 64 / g rows at a time, so that a 7-column remainder does not cost as much as a whole
+// chunk (update pass over 3.65e8 elements in rows of 1031 columns: 718 -> 570 us; 2.6e8 in rows of
+// 256: 422 -> 290 us). The rows of a tile are blocks of that many rows, interleaved with the other
+// bands'. Chunks of more than 32 groups take one row, with the offsets of a lane's row left out.
+struct LaneMap {
+  int64_t c0;            // the wave's first column (uniform)
+  int64_t row, step;     // first row of the wave's first block of rows, and the step to its next (uniform)
+  int sub;               // the lane's row within a block
+  int col;               // its first column from c0 on (negative: see `over`)
+  int over;              // its columns past the row's end; col moves back by as many (not in rows of < 8)
+  bool idle;
+  // whether the wave's chunk is narrow enough for two rows or more (uniform)
+  static __device__ __forceinline__ bool packs(const DevTensor &t, const Tile &tl) {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    return t.m - tl.c0 - (int64_t)(wave % t.cw) * kChunk <= kChunk / 2 && t.ld <= kPackLd;
+  }
+  __device__ __forceinline__ LaneMap(const DevTensor &t, const Tile &tl, bool pack) {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int wq = wave % t.cw, wr = wave / t.cw, rpi = kWaves / t.cw;
+    c0 = tl.c0 + (int64_t)wq * kChunk;
+    const int64_t left = t.m - c0;
+    int g = 64, rpw = 1;
+    if (pack && left > 0 && left <= kChunk / 2) {
+      g = ((int)left + 7) >> 3;
+      rpw = 64 / g;
+    }
+    sub = pack ? lane / g : 0;
+    const int gi = lane - sub * g;
+    row = (tl.band + (int64_t)wr * tl.stride) * rpw;
+    step = (int64_t)rpi * tl.stride * rpw;
+    idle = gi * 8 >= left || sub >= rpw;
+    over = gi * 8 + 8 > left ? gi * 8 + 8 - (int)left : 0;
+    col = gi * 8 - (t.m < 8 ? 0 : over);
+  }
+};
+
 __device__ __forceinline__ uint4 to_uint4(const u32x4_t &v) { return make_uint4(v.x, v.y, v.z, v.w); }
 // v shifted down by sh elements (0..7), zeros entering at the top: of 8 packed bf16 values,
 // and of 8 floats in two halves
@@ -367,6 +408,8 @@ struct Cols8 {
   bool narrow;   // m < 8
   __device__ __forceinline__ Cols8(int64_t m, int64_t c)
       : col(c), over(c + 8 > m ? (int)(c + 8 - m) : 0), narrow(m < 8) {}
+  // relative to the first of the 8 elements that the lane loads
+  __device__ __forceinline__ Cols8(int over_, bool narrow_) : col(narrow_ ? 0 : over_), over(over_), narrow(narrow_) {}
   __device__ __forceinline__ int count() const { return 8 - over; }
 };
 __device__ __forceinline__ u32x4_t load8(const uint16_t *row, const Cols8 &c) {
@@ -398,24 +441,40 @@ __device__ __forceinline__ void load8(const float *row, const Cols8 &c, float *o
     o[4 + e] = __uint_as_float(b[e]);
   }
 }
+// (the row's last lane stores its count() first values as 4 + 2 + 1 of them)
 __device__ __forceinline__ void store8(float *row, const Cols8 &c, const float *v) {
   if (c.over == 0) {
     stg_u(row + c.col, f32x4_t{v[0], v[1], v[2], v[3]});
     stg_u(row + c.col + 4, f32x4_t{v[4], v[5], v[6], v[7]});
   } else {
-#pragma unroll
-    for (int e = 0; e < 8; e++)
-      if (e < c.count()) stg(row + c.col + e, v[e]);
+    const int n = c.count();
+    float *p = row + c.col;
+    const bool four = (n & 4) != 0;
+    if (four) stg_u(p, f32x4_t{v[0], v[1], v[2], v[3]});
+    p += n & 4;
+    const float a = four ? v[4] : v[0], b = four ? v[5] : v[1];
+    const float d = four ? v[6] : v[2];
+    if (n & 2) {
+      stg(p, a);
+      stg(p + 1, b);
+    }
+    if (n & 1) stg(p + (n & 2), (n & 2) ? d : a);
   }
 }
+typedef unsigned u32x2_u2_t __attribute__((ext_vector_type(2), aligned(2)));
+typedef unsigned u32_u2_t __attribute__((aligned(2)));
 __device__ __forceinline__ void store8(uint16_t *row, const Cols8 &c, const uint4 &v) {
   if (c.over == 0) {
     stg_u(row + c.col, u32x4_t{v.x, v.y, v.z, v.w});
   } else {
-    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-    for (int e = 0; e < 8; e++)
-      if (e < c.count()) stg(row + c.col + e, (uint16_t)(w[e >> 1] >> (16 * (e & 1))));
+    const int n = c.count();
+    uint16_t *p = row + c.col;
+    const bool four = (n & 4) != 0;
+    if (four) *(__attribute__((address_space(1))) u32x2_u2_t *)p = u32x2_u2_t{v.x, v.y};
+    p += n & 4;
+    const uint32_t a = four ? v.z : v.x, b = four ? v.w : v.y;
+    if (n & 2) *(__attribute__((address_space(1))) u32_u2_t *)p = a;
+    if (n & 1) stg(p + (n & 2), (uint16_t)((n & 2) ? b : a));
   }
 }
 // 8 elements of a weight or gradient row, bf16 or float32 (float32 masters)
@@ -2050,16 +2109,70 @@ struct P3Scalars {
   double lsk;
 };
 
+// How a factored tensor's rows lie: aligned multiples of 8 columns (kPacked: taken several at a
+// time); at any position, of 8 columns or more; of fewer
+enum { kAligned = 0, kRagged = 1, kNarrow = 2, kPacked = 3 };
+// kRagged: the lane at a row's end works on the row's last 8 elements (p on), of which the lane
+// before it owns the first `over`: it computes them too (from values that may be new already) and
+// stores its own only. Rows of fewer than 8 start at their first column.
+// A template argument tells the two apart: with a branch at each load (whose result the branches
+// share) every load would be waited for before the next went out.
+template <int RAG>
+__device__ __forceinline__ u32x4_t load8_from(const uint16_t *p, const Cols8 &c) {
+  return RAG == kNarrow ? load8(p, c) : ldg_u(p);
+}
+template <int RAG>
+__device__ __forceinline__ void load8_from(const float *p, const Cols8 &c, float *o) {
+  if constexpr (RAG == kNarrow) {
+    load8(p, c, o);
+  } else {
+    const u32x4_t a = ldg_u(p), b = ldg_u(p + 4);
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+      o[e] = __uint_as_float(a[e]);
+      o[4 + e] = __uint_as_float(b[e]);
+    }
+  }
+}
+__device__ __forceinline__ void store8_from(uint16_t *p, const Cols8 &c, const uint4 &v) {
+  u32x4_t o = {v.x, v.y, v.z, v.w};
+  if (c.over != 0 && !c.narrow) shift_down(o, c.over);
+  store8(p, c, to_uint4(o));
+}
+__device__ __forceinline__ void store8_from(float *p, const Cols8 &c, const float *v) {
+  if (c.over != 0 && !c.narrow) {
+    u32x4_t a, b;
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+      a[e] = __float_as_uint(v[e]);
+      b[e] = __float_as_uint(v[4 + e]);
+    }
+    shift_down(a, b, c.over);
+    float o[8];
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+      o[e] = __uint_as_float(a[e]);
+      o[4 + e] = __uint_as_float(b[e]);
+    }
+    store8(p, c, o);
+  } else {
+    store8(p, c, v);
+  }
+}
+
 // one row segment of 8 elements: momentum, update, dither, bf16 store. The fast path forms 1/D
 // from per-row and per-column factors; the few elements whose result might round to the other
 // bf16 neighbour take the oracle's exact sequence. RAG: the row may start at any position and
 // end within the 8 columns.
-template <bool XU, bool DEC, bool GC, bool RAG>
+template <bool XU, bool DEC, bool GC, int RAG>
 __device__ __forceinline__ void p3_row8(const DevTensor &t, const StepConsts &k, const P3Scalars &c,
-                                        const Dither &dz, int64_t i, const Cols8 &cols, const float *bf, uint4 gw,
-                                        uint4 ww, const float *mv) {
+                                        const Dither &dz, const LaneMap &lm, int64_t i, int64_t wi, int64_t mi,
+                                        const float *bf, uint4 gw, uint4 ww, const float *mv) {
   const bool mom = t.momentum != 0;
-  const int64_t col = cols.col;
+  // i: the block's first row (uniform; the lane's row is i + sub), wi and mi: the chunk's first
+  // element of that row in W and in M
+  const Cols8 cols(lm.over, RAG == kNarrow);
+  const uint32_t om = (uint32_t)(lm.sub * (int)t.m + lm.col);   // (sub > 0 only where this fits)
   float x[8], w[8];
   unpack8(gw, x);
   unpack8(ww, w);
@@ -2070,17 +2183,17 @@ __device__ __forceinline__ void p3_row8(const DevTensor &t, const StepConsts &k,
   if (mom) {
 #pragma unroll
     for (int e = 0; e < 8; e++) x[e] = fmaf(k.a1, x[e], __fmul_rn(k.b1, mv[e]));
-    if constexpr (RAG)
-      store8(t.M + i * t.m, cols, x);
+    if constexpr (RAG == kRagged || RAG == kNarrow)
+      store8_from(t.M + mi + (int)om, cols, x);
     else
-      store_m8(t.M + i * t.m + col, x);
+      store_m8(t.M + mi + om, x);
   }
-  const float alpha = (float)(c.lsk * ldg(t.ainv + i));
+  const float alpha = (float)(c.lsk * ldg(t.ainv + i + lm.sub));
   // pair indices reach 2^32 only in tensors of more than 2^33 elements (a uniform test)
   const bool wide = t.idx0 + t.n * t.m > (int64_t(1) << 33);
-  const uint64_t idx = (uint64_t)t.idx0 + (uint64_t)i * (uint64_t)t.m + (uint64_t)col;
+  const uint64_t idx = (uint64_t)(t.idx0 + mi + ((RAG == kRagged || RAG == kNarrow) ? (int64_t)(int)om : (int64_t)om));
   float y[8], dith[8];
-  if constexpr (RAG) {
+  if constexpr (RAG == kRagged || RAG == kNarrow) {
     dither8(dz, idx, wide, dith);
   } else {
     // pairs p0 .. p0 + 3: m and col are multiples of 8, so p0 is a multiple of 4 and the
@@ -2104,31 +2217,31 @@ __device__ __forceinline__ void p3_row8(const DevTensor &t, const StepConsts &k,
     slack = fmaxf(slack, boundary_slack(y[e], x[e] * F, w[e]));
   }
   if (slack >= 0.f) {
-    const float Ri = ldg(t.R + i);
+    const float Ri = ldg(t.R + i + lm.sub);
 #pragma unroll
     for (int e = 0; e < 8; e++) {
       const float F = fminf(alpha * bf[e], c.cap3);
-      if ((!RAG || e < cols.count()) && near_boundary(y[e], x[e] * F, w[e]))
-        y[e] = exact_factored_y(x[e], w[e], decayed(w[e], dec, k.wd), Ri, ldg(t.C + col + e) / c.q, c.s, c.kc,
+      if ((RAG != kNarrow || e < cols.count()) && near_boundary(y[e], x[e] * F, w[e]))
+        y[e] = exact_factored_y(x[e], w[e], decayed(w[e], dec, k.wd), Ri, ldg(t.C + lm.c0 + lm.col + e) / c.q, c.s, c.kc,
                                 c.eps, c.lr, dith[e], xu);
     }
   }
   const uint4 out = make_uint4(pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3]), pack_bf16x2(y[4], y[5]),
                                pack_bf16x2(y[6], y[7]));
-  if constexpr (RAG)
-    store8(t.w + i * t.ld, cols, out);
+  if constexpr (RAG == kRagged || RAG == kNarrow)
+    store8_from(t.w + wi + (lm.sub * (int)t.ld + lm.col), cols, out);
   else
-    stg_nt(reinterpret_cast<uint4 *>(t.w + i * t.ld + col), out);
+    stg_nt(reinterpret_cast<uint4 *>(t.w + wi + (uint32_t)(lm.sub * (int)t.ld + lm.col)), out);
 }
 
-template <bool XU, bool DEC, bool GC, bool RAG>
+template <bool XU, bool DEC, bool GC, int RAG>
 __device__ __forceinline__ void p3_factored(const DevTensor &t, const Tile &tl, const StepConsts &k, float kc,
                                             float q, const Dither &dz) {
-  const WaveMap wm(t, tl);
-  const int64_t m = t.m, ld = t.ld, col = wm.col;
+  const LaneMap lm(t, tl, RAG != kAligned && LaneMap::packs(t, tl));
+  const int64_t n = t.n, m = t.m, ld = t.ld;
   const bool mom = t.momentum != 0;
-  if (col >= m) return;
-  const Cols8 cols(m, col);
+  if (lm.idle) return;
+  const Cols8 cols(lm.over, RAG == kNarrow);
   P3Scalars c;
   c.q = q;
   c.s = mom ? k.s_m : k.s_0;
@@ -2140,34 +2253,47 @@ __device__ __forceinline__ void p3_factored(const DevTensor &t, const Tile &tl, 
   c.cap3 = (float)(c.lsk / (double)sqrtf(k.eps));
   float bf[8];
 #pragma unroll
-  for (int e = 0; e < 8; e++) bf[e] = !RAG || e < cols.count() ? (float)col_factor(t, col + e, c.q) : 0.f;
-  for (int64_t lr = wm.wr; lr < tl.nr; lr += 2 * wm.rpi) {
-    const bool two = lr + wm.rpi < tl.nr;
-    const int64_t i = tl.row(lr), i2 = two ? tl.row(lr + wm.rpi) : i;
+  for (int e = 0; e < 8; e++) bf[e] = RAG != kNarrow || e < cols.count() ? (float)col_factor(t, lm.c0 + lm.col + e, c.q) : 0.f;
+  const int og = lm.sub * (int)ld + lm.col, om = lm.sub * (int)m + lm.col;   // (sub > 0 only where these fit)
+  // (uniform offsets, stepped: 64-bit products in the loop delay its loads. The ragged path has no
+  // registers left for the steps: it spills with them, and ran 2.5% slower)
+  constexpr bool kStep = RAG == kAligned || RAG == kPacked;
+  const int64_t dg = kStep ? lm.step * ld : 0, dm = kStep ? lm.step * m : 0;
+  int64_t gi = lm.row * ld + lm.c0, mi = lm.row * m + lm.c0;
+  for (int64_t i = lm.row; i + lm.sub < n; i += 2 * lm.step, gi += 2 * dg, mi += 2 * dm) {
+    if constexpr (!kStep) {
+      gi = i * ld + lm.c0;
+      mi = i * m + lm.c0;
+    }
+    // the second row, where there is one; lanes without one load a row of their wave's again
+    const bool more = i + lm.step < n, two = i + lm.step + lm.sub < n;
+    const int og2 = two || !more ? og : lm.col, om2 = two || !more ? om : lm.col;
+    const int64_t gi2 = more ? (kStep ? gi + dg : (i + lm.step) * ld + lm.c0) : gi;
+    const int64_t mi2 = more ? (kStep ? mi + dm : (i + lm.step) * m + lm.c0) : mi;
     uint4 ga, wa, gb, wb;
     float ma[8], mb[8];
-    if constexpr (RAG) {
-      ga = to_uint4(load8(t.g + i * ld, cols));
-      wa = to_uint4(load8(t.w + i * ld, cols));
-      gb = to_uint4(load8(t.g + i2 * ld, cols));
-      wb = to_uint4(load8(t.w + i2 * ld, cols));
+    if constexpr (RAG == kRagged || RAG == kNarrow) {
+      ga = to_uint4(load8_from<RAG>(t.g + gi + og, cols));
+      wa = to_uint4(load8_from<RAG>(t.w + gi + og, cols));
+      gb = to_uint4(load8_from<RAG>(t.g + gi2 + og2, cols));
+      wb = to_uint4(load8_from<RAG>(t.w + gi2 + og2, cols));
     } else {
-      ga = ldg_nt(reinterpret_cast<const uint4 *>(t.g + i * ld + col));
-      wa = ldg_nt(reinterpret_cast<const uint4 *>(t.w + i * ld + col));
-      gb = ldg_nt(reinterpret_cast<const uint4 *>(t.g + i2 * ld + col));
-      wb = ldg_nt(reinterpret_cast<const uint4 *>(t.w + i2 * ld + col));
+      ga = ldg_nt(reinterpret_cast<const uint4 *>(t.g + gi + (uint32_t)og));
+      wa = ldg_nt(reinterpret_cast<const uint4 *>(t.w + gi + (uint32_t)og));
+      gb = ldg_nt(reinterpret_cast<const uint4 *>(t.g + gi2 + (uint32_t)og2));
+      wb = ldg_nt(reinterpret_cast<const uint4 *>(t.w + gi2 + (uint32_t)og2));
     }
     if (mom) {
-      if constexpr (RAG) {
-        load8(t.M + i * m, cols, ma);
-        load8(t.M + i2 * m, cols, mb);
+      if constexpr (RAG == kRagged || RAG == kNarrow) {
+        load8_from<RAG>(t.M + mi + om, cols, ma);
+        load8_from<RAG>(t.M + mi2 + om2, cols, mb);
       } else {
-        load_m8(t.M + i * m + col, ma);
-        load_m8(t.M + i2 * m + col, mb);
+        load_m8(t.M + mi + (uint32_t)om, ma);
+        load_m8(t.M + mi2 + (uint32_t)om2, mb);
       }
     }
-    p3_row8<XU, DEC, GC, RAG>(t, k, c, dz, i, cols, bf, ga, wa, ma);
-    if (two) p3_row8<XU, DEC, GC, RAG>(t, k, c, dz, i2, cols, bf, gb, wb, mb);
+    p3_row8<XU, DEC, GC, RAG>(t, k, c, dz, lm, i, gi, mi, bf, ga, wa, ma);
+    if (two) p3_row8<XU, DEC, GC, RAG>(t, k, c, dz, lm, i + lm.step, gi2, mi2, bf, gb, wb, mb);
   }
 }
 
@@ -2242,10 +2368,17 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
   const float kc = ldg(&t.sc->k);
   const Dither dz(k.seed, k.step, t.tensor_id);
   if (t.kind == kFactored) {
-    if (!RAG || t.vec)
-      p3_factored<XU, DEC, GC, false>(t, tl, k, kc, ldg(&t.sc->q), dz);
-    else if constexpr (RAG)
-      p3_factored<XU, DEC, GC, true>(t, tl, k, kc, ldg(&t.sc->q), dz);
+    if (!RAG || t.vec) {
+      if (LaneMap::packs(t, tl))
+        p3_factored<XU, DEC, GC, kPacked>(t, tl, k, kc, ldg(&t.sc->q), dz);
+      else
+        p3_factored<XU, DEC, GC, kAligned>(t, tl, k, kc, ldg(&t.sc->q), dz);
+    } else if constexpr (RAG) {
+      if (t.m < 8)
+        p3_factored<XU, DEC, GC, kNarrow>(t, tl, k, kc, ldg(&t.sc->q), dz);
+      else
+        p3_factored<XU, DEC, GC, kRagged>(t, tl, k, kc, ldg(&t.sc->q), dz);
+    }
   } else
     p3_exact<XU, DEC, GC>(t, tl, k, kc, dz);
 }

@@ -68,6 +68,21 @@ def test_row_widths_and_positions(tier, pad, shift, hp):
         assert (bits(w) == bits(w_now)).all()
 
 
+@pytest.mark.parametrize("tier", [W.BACKBONE, W.EXPERT], ids=["momentum", "expert"])
+def test_narrow_chunks_taken_several_rows_at_a_time(tier):
+    """The update pass takes 64 / g rows at a time where a chunk of 512 columns holds only g groups of
+    8 (up to 32): aligned tables with one to 33 groups in their last chunk, and numbers of rows
+    around those of a block of rows."""
+    widths = (8, 16, 24, 40, 128, 168, 248, 256, 264, 520, 776, 1032, 2056)
+    specs = [W.Spec(f"w{m}x{n}", tier, (n, m), k) for k, (m, n) in
+             enumerate((m, n) for m in widths for n in (1, 2, 63, 65, 531) if m <= 776 or n > 63)]
+    log(f"[parity] aligned widths {widths}, tier {tier}; 3 steps")
+    pr = ParityRun(W.Workload("narrow", specs, 3), device="cuda:0")
+    for t in (1, 2, 3):
+        pr.step(t)
+    assert pr.stats.ok(), pr.stats
+
+
 @pytest.mark.parametrize("flags", [0, 2], ids=["plain", "exact_ulp"])
 @pytest.mark.parametrize("fp32", [False, True], ids=["bf16", "fp32"])
 def test_exact_moment_tensors_at_row_ends(fp32, flags):
