@@ -395,10 +395,13 @@ int skew_step(skew_ctx *ctx, const skew_hparams *hp, void *stream) {
     if (ctx->clip_slices.n > 0)
       run(5, [&] { return launch_clip_slices(T, ctx->clip_slices.d, ctx->clip_slices.n, k, s); });
     run(5, [&] { return launch_clip(T, ctx->clip.d, ctx->clip.n, k, L, nt, s); });
-    run(6, [&] { return launch_recheck(T, L, nt, k, 1, s); });
-    run(7, [&] { return launch_clip_recheck(T, L, nt, k, 1, s); });
-    run(6, [&] { return launch_recheck(T, L, nt, k, 2, s); });
-    run(7, [&] { return launch_clip_recheck(T, L, nt, k, 2, s); });
+    // (only factored tensors are ever listed: a group of routers and norm vectors alone has none)
+    if (ctx->fold.n > 0) {
+      run(6, [&] { return launch_recheck(T, L, nt, k, 1, s); });
+      run(7, [&] { return launch_clip_recheck(T, L, nt, k, 1, s); });
+      run(6, [&] { return launch_recheck(T, L, nt, k, 2, s); });
+      run(7, [&] { return launch_clip_recheck(T, L, nt, k, 2, s); });
+    }
   }
   if (ctx->p3.n > 0) run(8, [&] { return launch_p3(T, ctx->p3.d, ctx->p3.n, k, L, s); });
   return e == 0 ? SKEW_OK : SKEW_EHIP;

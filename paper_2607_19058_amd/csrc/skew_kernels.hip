@@ -179,20 +179,6 @@ __device__ __forceinline__ float bf16_ulp128(float w) {
 }
 __device__ __forceinline__ float dither_mul(float w, bool xu) { return xu ? bf16_ulp128(w) : fabsf(w); }
 
-// fixed-order tree over the work-group (every thread gets the total)
-__device__ __forceinline__ double block_sum(double x, double *sh) {
-  sh[threadIdx.x] = x;
-  __syncthreads();
-#pragma unroll
-  for (int s = kThreads / 2; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
-    __syncthreads();
-  }
-  const double r = sh[0];
-  __syncthreads();
-  return r;
-}
-
 // Butterfly reductions over one wave64: every lane ends with the same value (each step
 // adds two equal-order partials, and IEEE addition is commutative), so the result is
 // deterministic.
@@ -231,50 +217,8 @@ __device__ __forceinline__ double wg_sum_w(double x, double *sh) {
   __syncthreads();
   return r;
 }
-template <int NW>
-__device__ __forceinline__ double wg_max_w(double x, double *sh) {
-  x = wave_max_d(x);
-  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = x;
-  __syncthreads();
-  double r = sh[0];
-#pragma unroll
-  for (int w = 1; w < NW; w++) r = fmax(r, sh[w]);
-  __syncthreads();
-  return r;
-}
-template <int NW>
-__device__ __forceinline__ float wg_min_wf(float x, double *sh) {
-  x = wave_min_f(x);
-  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = (double)x;
-  __syncthreads();
-  float r = (float)sh[0];
-#pragma unroll
-  for (int w = 1; w < NW; w++) r = fminf(r, (float)sh[w]);
-  __syncthreads();
-  return r;
-}
-template <int NW>
-__device__ __forceinline__ float wg_max_wf(float x, double *sh) {
-  x = wave_max_f(x);
-  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = (double)x;
-  __syncthreads();
-  float r = (float)sh[0];
-#pragma unroll
-  for (int w = 1; w < NW; w++) r = fmaxf(r, (float)sh[w]);
-  __syncthreads();
-  return r;
-}
-template <int NW>
-__device__ __forceinline__ int wg_or_w(int x, double *sh) {
-  x = wave_or(x);
-  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = (double)x;
-  __syncthreads();
-  int r = 0;
-#pragma unroll
-  for (int w = 0; w < NW; w++) r |= (sh[w] != 0.0) ? 1 : 0;
-  __syncthreads();
-  return r;
-}
+// fixed-order sum over a work-group of kThreads (every thread gets the total)
+__device__ __forceinline__ double block_sum(double x, double *sh) { return wg_sum_w<kWaves>(x, sh); }
 
 // A tile is one row band (rows band, band + ntr, band + 2 ntr, ...: interleaved, so that
 // the work-groups running at the same time on one tensor read neighbouring rows) times
@@ -1080,26 +1024,70 @@ __global__ __launch_bounds__(kZThreads) void p1z_kernel(const DevTensor *__restr
 // Reductions of the clip stage, over the whole work-group (a tensor of its own) or over one
 // wave (the slices of a stacked tensor, one slice per wave at a time). Every participating
 // lane gets the result, in a fixed order.
+// What the clip stage reduces over a tensor or a slice: sums, a maximum, extremes and a flag. All of
+// them in one exchange: one after the other, each with its barriers and its loads waited for on
+// their own, they took the stage's 10 us (21 tensors) to 17 us (431).
+struct RedAll {
+  double s[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+  double um = 0.0;
+  float rmn = __builtin_inff(), cmn = __builtin_inff(), rmx = 0.f, cmx = 0.f;
+  int bad = 0;
+  __device__ __forceinline__ void wave() {
+#pragma unroll
+    for (int j = 0; j < 6; j++) s[j] = wave_sum_d(s[j]);
+    um = wave_max_d(um);
+    rmn = wave_min_f(rmn);
+    cmn = wave_min_f(cmn);
+    rmx = wave_max_f(rmx);
+    cmx = wave_max_f(cmx);
+    bad = wave_or(bad);
+  }
+};
 struct RedGroup {
-  double *sh;
+  double *sh;   // [kThreads]
   static constexpr int kN = kThreads;
   __device__ __forceinline__ int lane() const { return (int)threadIdx.x; }
   __device__ __forceinline__ bool lead() const { return threadIdx.x == 0; }
   __device__ __forceinline__ double sum(double x) const { return block_sum(x, sh); }
-  __device__ __forceinline__ double max(double x) const { return wg_max_w<kWaves>(x, sh); }
-  __device__ __forceinline__ float minf(float x) const { return wg_min_wf<kWaves>(x, sh); }
-  __device__ __forceinline__ float maxf(float x) const { return wg_max_wf<kWaves>(x, sh); }
-  __device__ __forceinline__ int any(int x) const { return wg_or_w<kWaves>(x, sh); }
+  __device__ __forceinline__ void all(RedAll &a) const {   // the waves in order
+    constexpr int kVals = 12;
+    static_assert(kVals * kWaves <= kThreads, "sh holds every wave's values");
+    a.wave();
+    if ((threadIdx.x & 63) == 0) {
+      double *o = sh + (threadIdx.x >> 6) * kVals;
+#pragma unroll
+      for (int j = 0; j < 6; j++) o[j] = a.s[j];
+      o[6] = a.um;
+      o[7] = (double)a.rmn;
+      o[8] = (double)a.cmn;
+      o[9] = (double)a.rmx;
+      o[10] = (double)a.cmx;
+      o[11] = (double)a.bad;
+    }
+    __syncthreads();
+    RedAll r;
+#pragma unroll
+    for (int w = 0; w < kWaves; w++) {
+      const double *o = sh + w * kVals;
+#pragma unroll
+      for (int j = 0; j < 6; j++) r.s[j] += o[j];
+      r.um = fmax(r.um, o[6]);
+      r.rmn = fminf(r.rmn, (float)o[7]);
+      r.cmn = fminf(r.cmn, (float)o[8]);
+      r.rmx = fmaxf(r.rmx, (float)o[9]);
+      r.cmx = fmaxf(r.cmx, (float)o[10]);
+      r.bad |= o[11] != 0.0 ? 1 : 0;
+    }
+    __syncthreads();
+    a = r;
+  }
 };
 struct RedWave {
   static constexpr int kN = 64;
   __device__ __forceinline__ int lane() const { return (int)(threadIdx.x & 63); }
   __device__ __forceinline__ bool lead() const { return (threadIdx.x & 63) == 0; }
   __device__ __forceinline__ double sum(double x) const { return wave_sum_d(x); }
-  __device__ __forceinline__ double max(double x) const { return wave_max_d(x); }
-  __device__ __forceinline__ float minf(float x) const { return wave_min_f(x); }
-  __device__ __forceinline__ float maxf(float x) const { return wave_max_f(x); }
-  __device__ __forceinline__ int any(int x) const { return wave_or(x); }
+  __device__ __forceinline__ void all(RedAll &a) const { a.wave(); }
 };
 template <class Red>
 __device__ __forceinline__ double red_sum(const Red &r, const double *p, int64_t n, int64_t stride = 1) {
@@ -1118,12 +1106,23 @@ __device__ __forceinline__ double wg_sum(const double *p, int64_t n, double *sh,
 // q = max(mean R, eps) for a factored tensor (the clamp of the reconstruction), from the
 // sums of R over the fold chunks of rows or over the row bands
 template <class Red>
-__device__ __forceinline__ float mean_r_of(const DevTensor &t, const StepConsts &k, const Red &r) {
+__device__ __forceinline__ double sum_r_part(const DevTensor &t, const StepConsts &k, const Red &r) {
   // row-band tensors keep the sums of R in their band statistics, except in the gradient-
   // norm mode, where the fold forms R and its sums per chunk of rows as for wide tensors
-  const double sr = (t.zpath && !k.gclip) ? red_sum(r, &t.bst->rsum, t.nzb, sizeof(BandStats) / sizeof(double))
-                                          : red_sum(r, t.rsum, t.zpath ? (t.n + kFold - 1) / kFold : t.nfr);
+  const bool bands = t.zpath && !k.gclip;
+  const double *p = bands ? &t.bst->rsum : t.rsum;
+  const int64_t n = bands ? t.nzb : (t.zpath ? (t.n + kFold - 1) / kFold : t.nfr);
+  const int64_t stride = bands ? sizeof(BandStats) / sizeof(double) : 1;
+  double s = 0.0;   // the thread's share
+  for (int64_t c = r.lane(); c < n; c += Red::kN) s += ldg(p + c * stride);
+  return s;
+}
+__device__ __forceinline__ float mean_r_from(const DevTensor &t, const StepConsts &k, double sr) {
   return max_nan((float)(sr / (double)t.n), k.eps);
+}
+template <class Red>
+__device__ __forceinline__ float mean_r_of(const DevTensor &t, const StepConsts &k, const Red &r) {
+  return mean_r_from(t, k, r.sum(sum_r_part(t, k, r)));
 }
 __device__ __forceinline__ float mean_r_clamped(const DevTensor &t, const StepConsts &k, double *sh) {
   return mean_r_of(t, k, RedGroup{sh});
@@ -1822,69 +1821,64 @@ __device__ __forceinline__ int repeats_rule(const DevTensor &t, float rmn, float
   const bool uc = t.m > 1 && cmx <= cmn * (1.f + 0x1p-20f);
   return (ur || uc || 64.0 * dup_r > (double)t.n || 64.0 * dup_c > (double)t.m) ? 1 : 0;
 }
-// wide factored tensors: from the fold's per-chunk statistics of R and C (the row-band
-// tensors have these in their band and column-chunk statistics)
-template <class Red>
-__device__ __forceinline__ int repeated_factors(const DevTensor &t, const Red &r) {
-  double dup_r = 0.0, dup_c = 0.0;
-  float rmn = __builtin_inff(), rmx = 0.f, cmn = __builtin_inff(), cmx = 0.f;
-  for (int64_t q = r.lane(); q < (int64_t)t.nfr + t.nfc; q += Red::kN) {
-    const ColStats *c = t.cst + q;
-    const float mn = ldg(&c->cmin), mx = ldg(&c->cmax);
-    const double d = (double)ldg(&c->cdup);
-    if (q < t.nfr) {
-      rmn = fminf(rmn, mn);
-      rmx = fmaxf(rmx, mx);
-      dup_r += d;
-    } else {
-      cmn = fminf(cmn, mn);
-      cmx = fmaxf(cmx, mx);
-      dup_c += d;
-    }
-  }
-  dup_r = r.sum(dup_r);
-  dup_c = r.sum(dup_c);
-  rmn = r.minf(rmn);
-  rmx = r.maxf(rmx);
-  cmn = r.minf(cmn);
-  cmx = r.maxf(cmx);
-  return repeats_rule(t, rmn, rmx, cmn, cmx, dup_r, dup_c);
-}
 
 template <class Red>
 __device__ __forceinline__ SliceSum slice_sum(const DevTensor &t, const StepConsts &k, const Red &r) {
   SliceSum o = {0.0, 0.0, 0, 0, 0};
-  const float q = t.kind == kFactored ? mean_r_of(t, k, r) : 0.f;
-  if (t.kind == kFactored && !t.zpath) o.repeats = repeated_factors(t, r);
+  const bool factored = t.kind == kFactored;
+  // s: the sum of R, then of the row-band tensors Y, S and S2 (below), of others the sum of
+  // U_hat^2, nothing and the sum of U_hat^4; and the repeats of R and of C
+  RedAll a;
+  if (factored) a.s[0] = sum_r_part(t, k, r);
   if (t.zpath) {
-    const int64_t bstride = sizeof(BandStats) / sizeof(double), cstride = sizeof(ColStats) / sizeof(double);
-    const double Y = red_sum(r, &t.bst->ysum, t.nzb, bstride);
-    const double SU = red_sum(r, &t.cst->s, t.nfc, cstride);
-    // sum over the terms t_ij = (s x)^2 / (R_i c'_j) of t_ij^2 <= umax * sum_j z_j / c'_j^2
-    const double SU2 = red_sum(r, &t.cst->s2, t.nfc, cstride);
-    double um = 0.0, dup_r = 0.0, dup_c = 0.0;
-    float rmn = __builtin_inff(), rmx = 0.f, cmn = __builtin_inff(), cmx = 0.f;
-    int bad = 0;
     for (int64_t b = r.lane(); b < t.nzb; b += Red::kN) {
-      um = fmax(um, ldg(&t.bst[b].umax));
-      rmn = fminf(rmn, ldg(&t.bst[b].rmin));
-      rmx = fmaxf(rmx, ldg(&t.bst[b].rmax));
-      bad |= ldg(&t.bst[b].bad);
-      dup_r += (double)ldg(&t.bst[b].rdup);
+      const BandStats *x = t.bst + b;
+      a.s[1] += ldg(&x->ysum);
+      a.um = fmax(a.um, ldg(&x->umax));
+      a.rmn = fminf(a.rmn, ldg(&x->rmin));
+      a.rmx = fmaxf(a.rmx, ldg(&x->rmax));
+      a.bad |= ldg(&x->bad);
+      a.s[4] += (double)ldg(&x->rdup);
     }
     for (int64_t c = r.lane(); c < t.nfc; c += Red::kN) {
-      cmn = fminf(cmn, ldg(&t.cst[c].cmin));
-      cmx = fmaxf(cmx, ldg(&t.cst[c].cmax));
-      bad |= ldg(&t.cst[c].bad);
-      dup_c += (double)ldg(&t.cst[c].cdup);
+      const ColStats *x = t.cst + c;
+      a.s[2] += ldg(&x->s);
+      a.s[3] += ldg(&x->s2);
+      a.cmn = fminf(a.cmn, ldg(&x->cmin));
+      a.cmx = fmaxf(a.cmx, ldg(&x->cmax));
+      a.bad |= ldg(&x->bad);
+      a.s[5] += (double)ldg(&x->cdup);
     }
-    um = r.max(um);
-    rmn = r.minf(rmn);
-    rmx = r.maxf(rmx);
-    cmn = r.minf(cmn);
-    cmx = r.maxf(cmx);
-    bad = r.any(bad);
-    o.repeats = repeats_rule(t, rmn, rmx, cmn, cmx, r.sum(dup_r), r.sum(dup_c));
+  } else {
+    if (factored)   // the fold's per-chunk statistics of R and C
+      for (int64_t q = r.lane(); q < (int64_t)t.nfr + t.nfc; q += Red::kN) {
+        const ColStats *c = t.cst + q;
+        const float mn = ldg(&c->cmin), mx = ldg(&c->cmax);
+        const double d = (double)ldg(&c->cdup);
+        if (q < t.nfr) {
+          a.rmn = fminf(a.rmn, mn);
+          a.rmx = fmaxf(a.rmx, mx);
+          a.s[4] += d;
+        } else {
+          a.cmn = fminf(a.cmn, mn);
+          a.cmx = fmaxf(a.cmx, mx);
+          a.s[5] += d;
+        }
+      }
+    const int64_t ntiles = (int64_t)t.ntr * t.ntc * kSub;   // per-part sums
+    for (int64_t c = r.lane(); c < ntiles; c += Red::kN) {
+      a.s[1] += ldg(t.ssum + c);
+      a.s[3] += ldg(t.qsum + c);
+    }
+  }
+  r.all(a);
+  const float q = factored ? mean_r_from(t, k, a.s[0]) : 0.f;
+  if (factored) o.repeats = repeats_rule(t, a.rmn, a.rmx, a.cmn, a.cmx, a.s[4], a.s[5]);
+  if (t.zpath) {
+    // SU2: the sum over the terms t_ij = (s x)^2 / (R_i c'_j) of t_ij^2 <= umax * sum_j z_j / c'_j^2
+    const double Y = a.s[1], SU = a.s[2], SU2 = a.s[3], um = a.um;
+    const float rmn = a.rmn, rmx = a.rmx, cmn = a.cmn, cmx = a.cmx;
+    const int bad = a.bad;
     // the sums the row-band pass formed this step (it skips one when the last step
     // predicts the regime); a sum it did not form counts as +inf
     const int formed = ldg(&t.bst[0].regime);
@@ -1913,9 +1907,8 @@ __device__ __forceinline__ SliceSum slice_sum(const DevTensor &t, const StepCons
     const int next = (lo >= 1.05f * k.eps) ? kRegimeAbove : (2.f * hi < k.eps ? kRegimeFloor : kRegimeBoth);
     if (r.lead()) stg(&t.sc->regime, o.bad ? (int32_t)kRegimeBoth : (int32_t)next);
   } else {
-    const int64_t ntiles = (int64_t)t.ntr * t.ntc * kSub;   // per-part sums
-    o.S = red_sum(r, t.ssum, ntiles);
-    const double Q4 = red_sum(r, t.qsum, ntiles);
+    o.S = a.s[1];
+    const double Q4 = a.s[3];
     // the exact second moment's sum is the oracle's own; a factored one carries the
     // spread of its unrounded terms (20 standard deviations)
     o.E = t.kind == kFactored ? 20.0 * 0x1p-23 * sqrt(Q4) + 1e-14 * o.S : 0.0;
