@@ -14,8 +14,10 @@ static int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 
 // Row-band pass: zcw 512-column chunks per row, nseg of them per wave, so wpr = ceil(zcw /
 // nseg) <= 8 waves share a row and rpi = 8 / wpr rows are side by side. One chunk per wave
-// only for rows of one chunk; two up to 16 chunks; three without momentum up to 24; else
-// four. A block is rpi * zrb rows, zrb (rows per group) as many as the registers hold: two
+// only for rows of one chunk; two up to 16 chunks; three without momentum up to 24, and where two
+// leave more of the waves idle (3, 5, 6, 9 to 12 chunks: a slot of either costs the same; pass over
+// 3.65e8 elements in rows of 2730 / 2765 / 1031 columns: 215 / 242 / 312 us with two, 181 / 208 /
+// 260 with three); else four. A block is rpi * zrb rows, zrb (rows per group) as many as the registers hold: two
 // blocks (bf16 gradient, and fp32 momentum where kept) beside the band's double sums.
 // zrb = 0: no row band.
 struct RowBandShape {
@@ -25,6 +27,11 @@ static RowBandShape rowband_shape(int64_t m, int64_t ld, bool momentum) {
   RowBandShape r;
   r.zcw = ceil_div(m, kChunk);
   r.nseg = r.zcw <= 1 ? 1 : (r.zcw <= 2 * kZWaves ? 2 : (!momentum && r.zcw <= 3 * kZWaves ? 3 : 4));
+  auto busy = [&](int64_t nseg) {   // chunks summed per pass of the work-group, of 8 * nseg that it could
+    const int64_t w = ceil_div(r.zcw, nseg);
+    return w > kZWaves ? 0.0 : (double)(kZWaves / w * r.zcw) / (double)(kZWaves * nseg);
+  };
+  if (!momentum && r.nseg == 2 && busy(3) > busy(2)) r.nseg = 3;
   const int64_t wpr = ceil_div(r.zcw, r.nseg);
   r.rpi = wpr <= kZWaves ? kZWaves / wpr : 0;
   r.zrb = r.nseg == 1 ? 4 : (r.nseg == 2 ? (momentum ? 2 : 4) : (r.nseg == 3 ? 2 : 1));
