@@ -33,6 +33,21 @@ constexpr int kZLdsBytes = 96 * 1024;    // bytes of one staged block of rows, a
 constexpr int kZMaxBlockRows = 64;       // rows staged per block, at most
 constexpr int kZMaxBandRows = 2048;      // rows per band, at most (their R are staged in LDS)
 
+// Rows per group and block of the row-band pass in each of its modes (0: the whole pass; 1: the sums
+// of g^2 alone, which read no momentum; 2: z of the scaled gradient): as many as the registers hold
+// without spills. A block of any mode is addressed by 31-bit byte offsets from its first row, so the
+// planner bounds its span by the mode with the most rows.
+constexpr int zrows_per_group(int nseg, bool momentum, int mode) {
+  return nseg == 1 ? (momentum && mode == 2 ? 2 : 4)
+                   : (nseg == 2 ? (mode == 2 || (momentum && mode == 0) ? 2 : 4) : (nseg == 3 ? 2 : 1));
+}
+constexpr int zrows_per_group_max(int nseg, bool momentum) {
+  int r = 0;
+  for (int mode = 0; mode < 3; mode++)
+    if (zrows_per_group(nseg, momentum, mode) > r) r = zrows_per_group(nseg, momentum, mode);
+  return r;
+}
+
 // Per-tensor scalars of one step, written by the clip stage and read by the update.
 struct TensorScalars {
   float k;            // clip factor 1 / max(1, RMS(U_hat) / d), rounded as the oracle rounds it

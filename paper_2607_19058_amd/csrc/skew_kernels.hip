@@ -990,7 +990,6 @@ __device__ __forceinline__ void p1z_body(const DevTensor &t, int band, const Ste
 // One launch covers the bands of every shape: a work-group fills a compute unit in all of
 // them (two waves of up to 256 VGPRs per SIMD), so the variants share a launch at no cost in
 // occupancy, and the bands of a few small tensors run beside the others instead of after them.
-// Rows per group and block (RB) are as many as the registers hold without spills.
 template <int MODE>
 __global__ __launch_bounds__(kZThreads) void p1z_kernel(const DevTensor *__restrict__ TT,
                                                         const Item *__restrict__ items, StepConsts k) {
@@ -1003,21 +1002,20 @@ __global__ __launch_bounds__(kZThreads) void p1z_kernel(const DevTensor *__restr
   if (MODE != 1 && t.momentum) {
     constexpr bool M = MODE != 1;
     if (t.nseg == 1)
-      p1z_body<1, MODE == 2 ? 2 : 4, M, MODE>(t, it.tile, k, colbuf, rowsh, sh, rstash);
+      p1z_body<1, zrows_per_group(1, true, MODE), M, MODE>(t, it.tile, k, colbuf, rowsh, sh, rstash);
     else if (t.nseg == 2)
-      p1z_body<2, 2, M, MODE>(t, it.tile, k, colbuf, rowsh, sh, rstash);
+      p1z_body<2, zrows_per_group(2, true, MODE), M, MODE>(t, it.tile, k, colbuf, rowsh, sh, rstash);
     else
-      p1z_body<4, 1, M, MODE>(t, it.tile, k, colbuf, rowsh, sh, rstash);
-  } else {
-    constexpr int RB2 = MODE == 2 ? 2 : 4;
+      p1z_body<4, zrows_per_group(4, true, MODE), M, MODE>(t, it.tile, k, colbuf, rowsh, sh, rstash);
+  } else {   // (mode 1 reads no momentum: its rows per group do not depend on it)
     if (t.nseg == 1)
-      p1z_body<1, 4, false, MODE>(t, it.tile, k, colbuf, rowsh, sh, rstash);
+      p1z_body<1, zrows_per_group(1, false, MODE), false, MODE>(t, it.tile, k, colbuf, rowsh, sh, rstash);
     else if (t.nseg == 2)
-      p1z_body<2, RB2, false, MODE>(t, it.tile, k, colbuf, rowsh, sh, rstash);
+      p1z_body<2, zrows_per_group(2, false, MODE), false, MODE>(t, it.tile, k, colbuf, rowsh, sh, rstash);
     else if (t.nseg == 3)
-      p1z_body<3, 2, false, MODE>(t, it.tile, k, colbuf, rowsh, sh, rstash);
+      p1z_body<3, zrows_per_group(3, false, MODE), false, MODE>(t, it.tile, k, colbuf, rowsh, sh, rstash);
     else
-      p1z_body<4, 1, false, MODE>(t, it.tile, k, colbuf, rowsh, sh, rstash);
+      p1z_body<4, zrows_per_group(4, false, MODE), false, MODE>(t, it.tile, k, colbuf, rowsh, sh, rstash);
   }
 }
 

@@ -34,10 +34,12 @@ static RowBandShape rowband_shape(int64_t m, int64_t ld, bool momentum) {
   if (!momentum && r.nseg == 2 && busy(3) > busy(2)) r.nseg = 3;
   const int64_t wpr = ceil_div(r.zcw, r.nseg);
   r.rpi = wpr <= kZWaves ? kZWaves / wpr : 0;
-  r.zrb = r.nseg == 1 ? 4 : (r.nseg == 2 ? (momentum ? 2 : 4) : (r.nseg == 3 ? 2 : 1));
+  r.zrb = zrows_per_group((int)r.nseg, momentum, 0);
   // rows too short for the row's end to be one 16-byte load, too long for the work-group, or so
-  // far apart that a block's byte offsets pass 31 bits take the tiled passes
-  if (m < kZMinCols || r.rpi < 1 || ld > 0x7FFFFFFF / 2 / (r.rpi * r.zrb)) r.zrb = 0;
+  // far apart that the byte offsets of a block (of the mode with the longest blocks) pass 31 bits
+  // take the tiled passes
+  if (m < kZMinCols || r.rpi < 1 || ld > 0x7FFFFFFF / 2 / (r.rpi * zrows_per_group_max((int)r.nseg, momentum)))
+    r.zrb = 0;
   return r;
 }
 

@@ -108,11 +108,7 @@ int launch_p1z(const DevTensor *T, const Item *items, int64_t count, const StepC
   for (int64_t q = 0; q < count; q++) {
     const DevTensor &t = T[items[q].tensor];
     const int lg = t.nseg == 1 ? 0 : (t.nseg == 2 ? 1 : (t.nseg == 4 ? 2 : 3));
-    // the aligned variants without momentum and up to two chunks per wave address a block by
-    // 32-bit offsets: a wider block span takes the element-load variant
-    const bool wide_span = (int64_t)t.zrpi * t.zrb * t.ld * 2 > 0x7FFFFFFF;
-    const bool vec = t.vec && !(wide_span && !t.momentum && t.nseg <= 2);
-    CHECK(variant == lg * 4 + (vec ? 0 : 2) + (t.momentum ? 1 : 0), "row-band variant %d", variant);
+    CHECK(variant == lg * 4 + (t.vec ? 0 : 2) + (t.momentum ? 1 : 0), "row-band variant %d", variant);
   }
   return 0;
 }
@@ -228,7 +224,27 @@ static void check_plan(const std::string &name, const std::vector<skew_tensor_de
     ws.push_back({tp.off_qsum, tp.off_qsum + (size_t)tiles * kSub * 8, tn + ".qsum"});
     ws.push_back({tp.off_sc, tp.off_sc + sizeof(TensorScalars), tn + ".sc"});
     if (tp.zpath) {
-      // row bands: rows [b zrows, min((b + 1) zrows, n)), whole blocks of rpi * zrb rows
+      // row bands: band b takes the blocks b, b + nzb, ... of rpi * RB rows, where RB depends on the
+      // mode. In every mode each row lies in one block of one band, a block's byte offsets stay
+      // below 2^31 (the kernel's lanes without work take that offset, and the range of a buffer
+      // ends there: a row beyond it would read as zeros), and a band's rows fit their LDS area
+      // (mode 1 stages none)
+      for (int mode = 0; mode < 3; mode++) {
+        const int64_t br = (int64_t)tp.zrpi * zrows_per_group(tp.nseg, tp.momentum != 0, mode);
+        CHECK(br * tp.ld * 2 <= 0x7FFFFFFF && (mode == 1 || br * tp.m * 4 <= 0x7FFFFFFF),
+              "%s: mode %d: a block spans %lld bytes", tn.c_str(), mode, (long long)(br * tp.ld * 2));
+        CHECK(br <= kZMaxBlockRows, "%s: mode %d: %lld rows per block", tn.c_str(), mode, (long long)br);
+        int64_t rows = 0, most = 0;
+        for (int64_t b = 0; b < tp.nzb; b++) {
+          const int64_t nblk = cdiv(cdiv(tp.n, br) - b, tp.nzb);
+          most = std::max(most, nblk * br);
+          for (int64_t q = 0; q < nblk; q++) rows += std::min(br, tp.n - (q * tp.nzb + b) * br);
+        }
+        CHECK(rows == tp.n, "%s: mode %d: the bands hold %lld rows of %lld", tn.c_str(), mode, (long long)rows,
+              (long long)tp.n);
+        CHECK(mode == 1 || most <= kZMaxBandRows + kZMaxBlockRows, "%s: mode %d: %lld rows in a band", tn.c_str(),
+              mode, (long long)most);
+      }
       const int64_t blk = (int64_t)tp.zrpi * tp.zrb;
       CHECK(tp.zrows % blk == 0 && tp.zrows <= kZMaxBandRows && blk <= kZMaxBlockRows, "%s: band geometry",
             tn.c_str());
@@ -436,6 +452,16 @@ int main() {
   check_plan("big", big);
   check_plan("stacked", stacked);
   check_plan("variants", variants);
+  // row strides around the largest span of a block of rows, for every number of chunks per wave,
+  // with and without momentum
+  for (int tier : {0, 1})
+    for (int64_t m : {8, 512, 1024, 1536, 2048, 4096, 8192, 11008, 16384})
+      for (int64_t rows_block : {1, 2, 4, 8, 16, 32})
+        for (int64_t off : {-1, 0, 1})
+          for (int64_t over : {1, 2}) {
+            const int64_t ld = std::max(m, (int64_t(1) << 30) / rows_block * over + off);
+            check_plan("stride m " + std::to_string(m) + " ld " + std::to_string(ld), {mk(tier, 2, 64, m, ld, id)});
+          }
   for (bool gn : {false, true}) {
     check_init_and_step(gn ? "unit+gnorm" : "unit", unit, gn);
     check_init_and_step(gn ? "stacked+gnorm" : "stacked", stacked, gn);

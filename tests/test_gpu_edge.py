@@ -172,6 +172,33 @@ def test_row_strides_past_a_32_bit_block_span():
     torch.cuda.empty_cache()
 
 
+@pytest.mark.parametrize("ld", [(1 << 25) - 8, 50_000_000], ids=["largest_block_span", "beyond_it"])
+def test_momentum_row_strides_in_the_gradient_norm_mode(ld):
+    """Backbone rows of 1024 columns (32 of them in a block of the gradient-norm mode's sums pass, 16
+    in one of the step's own) at the largest stride whose blocks are addressed by 31-bit offsets,
+    and at one between that of the shorter blocks and that of the longer ones (the tiled passes
+    take it): every row counts in the norm, R, C and the weights, against the oracle."""
+    dev = torch.device("cuda")
+    specs = [W.Spec("bb.far", W.BACKBONE, (24, 1024), 0), W.Spec("ex", W.EXPERT, (64, 512), 1)]
+    wl = W.Workload("momentum_strides", specs, 2)
+    Ws, Gs = [], []
+    for s, stride in zip(specs, (ld, 512)):
+        n, m = s.shape
+        w, g = (torch.zeros((n - 1) * stride + m, dtype=torch.bfloat16, device=dev).as_strided((n, m), (stride, 1))
+                for _ in range(2))
+        w.copy_(W.init_weight(s, wl, dev))
+        Ws.append(w)
+        Gs.append(g)
+    log(f"[parity] backbone rows at stride {ld}, gradient norm 1e-2, 2 steps")
+    pr = ParityRun(wl, weights=Ws, grads=Gs, hp=dict(oracle.DEFAULTS, weight_decay=0.05, max_grad_norm=1e-2))
+    for t in (1, 2):
+        pr.step(t)
+    assert pr.stats.ok(), pr.stats
+    assert pr.stats.compared == 2 * sum(s.numel for s in specs)
+    del Ws, Gs, pr
+    torch.cuda.empty_cache()
+
+
 def test_overlapping_row_views_are_refused_before_any_launch():
     """A view whose rows overlap (an expanded row, or an unfold window: row stride below the
     row length) would make the in-place update write past the view; the binding refuses it
