@@ -100,7 +100,8 @@ struct BandStats {
   float rmax;     // max R_i
   int32_t bad;    // a row with R_i == 0 but a nonzero gradient (its elements escape the bounds)
   int32_t regime; // the sums this band formed (kRegime*)
-  int32_t rdup;   // rows whose R_i > 0 equals the previous row's (repeated factors)
+  int32_t rdup;   // of the rows [b, b + 1) * kZMaxBandRows, for b below their number, those whose
+                  // R_i > 0 equals the previous row's (repeated factors; written by the fold, 0 in others)
   int32_t pad;
 };
 

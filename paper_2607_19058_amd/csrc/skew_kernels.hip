@@ -546,7 +546,7 @@ constexpr int kZRowSlots = kZMaxBlockRows * kZWaves;   // row partials of one bl
 // e * kColPad + l of its chunk (the writes of a wave and the reads of 64 consecutive columns
 // both spread over all banks)
 constexpr int kColPad = 72, kColChunks = 16;
-constexpr int kZStats = 7;   // values of a band reduced over its work-group
+constexpr int kZStats = 6;   // values of a band reduced over its work-group
 
 // Cross-lane moves of doubles without LDS: DPP within 16-lane rows (quad permutes, half
 // and full row mirrors) and the gfx950 lane-half swaps. Each reduction step adds two
@@ -929,15 +929,13 @@ __device__ __forceinline__ void p1z_body(const DevTensor &t, int band, const Ste
   __syncthreads();   // every wave's rstash rows are there
   // the band's R and 1/sqrt(R) (coalesced), and its statistics: fixed-order reductions
   // (mode 1: the band's sum of g^2 instead; mode 2: R was written by the fold)
-  // (rdup: equal neighbours within a block)
-  double rs = rs_l, rdup = 0.0;
+  double rs = rs_l;
   float rmn = __builtin_inff(), rmx = 0.f;
   if constexpr (MODE != 1)
     for (int j = threadIdx.x; j < (int)nblk * br; j += kZThreads) {
       const int64_t i = first_row(j / br) + j % br;
       if (i >= t.n) continue;
       const float R = rstash[j];
-      if (j % br > 0 && R > 0.f && R == rstash[j - 1]) rdup += 1.0;
       const double Rd = (double)R;
       const bool normal = R > 0.f && R < __builtin_inff();
       if (MODE == 0) {
@@ -949,7 +947,7 @@ __device__ __forceinline__ void p1z_body(const DevTensor &t, int band, const Ste
       rmx = fmaxf(rmx, R);
     }
   // each wave reduces its values, thread 0 adds the waves in order (one barrier for all)
-  const double ys = wave_sum_d(ysum + ysum2), um = wave_max_d(umax), rw = wave_sum_d(rs), rd = wave_sum_d(rdup);
+  const double ys = wave_sum_d(ysum + ysum2), um = wave_max_d(umax), rw = wave_sum_d(rs);
   const float rmin = wave_min_f(rmn), rmax = wave_max_f(rmx);
   const int bd = wave_or(bad_l);
   if (lane == 0) {
@@ -957,10 +955,9 @@ __device__ __forceinline__ void p1z_body(const DevTensor &t, int band, const Ste
     o[0] = ys;
     o[1] = um;
     o[2] = rw;
-    o[3] = rd;
-    o[4] = (double)rmin;
-    o[5] = (double)rmax;
-    o[6] = (double)bd;
+    o[3] = (double)rmin;
+    o[4] = (double)rmax;
+    o[5] = (double)bd;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -971,18 +968,16 @@ __device__ __forceinline__ void p1z_body(const DevTensor &t, int band, const Ste
       a[0] += o[0];
       a[1] = fmax(a[1], o[1]);
       a[2] += o[2];
-      a[3] += o[3];
-      a[4] = fmin(a[4], o[4]);
+      a[3] = fmin(a[3], o[3]);
+      a[4] = fmax(a[4], o[4]);
       a[5] = fmax(a[5], o[5]);
-      a[6] = fmax(a[6], o[6]);
     }
     stg(&t.bst[band].ysum, a[0]);
     stg(&t.bst[band].umax, a[1]);
     stg(&t.bst[band].rsum, a[2]);
-    stg(&t.bst[band].rdup, (int32_t)a[3]);
-    stg(&t.bst[band].rmin, (float)a[4]);
-    stg(&t.bst[band].rmax, (float)a[5]);
-    stg(&t.bst[band].bad, (int32_t)(a[6] != 0.0));
+    stg(&t.bst[band].rmin, (float)a[3]);
+    stg(&t.bst[band].rmax, (float)a[4]);
+    stg(&t.bst[band].bad, (int32_t)(a[5] != 0.0));
     stg(&t.bst[band].regime, (int32_t)regime);
   }
 }
@@ -1240,6 +1235,28 @@ __device__ __forceinline__ void chunk_stats(ColStats *out, double *sum_out, floa
   }
 }
 
+// Repeated row factors of a row-band tensor: in rows [chunk kZMaxBandRows, ...), those whose R_i > 0
+// equals R_{i-1}. (A band's blocks of rows lie apart, so the row-band pass cannot tell: its blocks
+// are single rows where a row takes the whole work-group.)
+__device__ __forceinline__ void count_equal_rows(const DevTensor &t, int chunk, FoldShared &f) {
+  const int64_t i0 = (int64_t)chunk * kZMaxBandRows;
+  int n = 0;   // of the wave (uniform)
+#pragma unroll
+  for (int r = 0; r < kZMaxBandRows; r += kFoldThreads) {
+    const int64_t i = i0 + r + threadIdx.x;
+    const bool in = i > 0 && i < t.n;
+    const float a = ldg(t.R + (in ? i : 0)), b = ldg(t.R + (in ? i - 1 : 0));
+    n += __popcll(__ballot(in && a > 0.f && a == b));
+  }
+  if ((threadIdx.x & 63) == 0) f.stat[threadIdx.x >> 6][0] = (double)n;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    double all = 0.0;
+    for (int w = 0; w < kFoldThreads / 64; w++) all += f.stat[w][0];
+    stg(&t.bst[chunk].rdup, (int32_t)all);
+  }
+}
+
 __global__ __launch_bounds__(kFoldThreads) __attribute__((amdgpu_waves_per_eu(8))) void fold_kernel(const DevTensor *__restrict__ TT,
                                                             const Item *__restrict__ items, StepConsts k, int phase) {
   __shared__ FoldShared f;
@@ -1251,6 +1268,10 @@ __global__ __launch_bounds__(kFoldThreads) __attribute__((amdgpu_waves_per_eu(8)
   // where their row sums of g^2 wait in ainv
   const int nrows = t.zpath ? (phase == 1 ? (int)((t.n + kFold - 1) / kFold) : 0) : t.nfr;
   if (phase == 2 && !t.zpath) return;
+  if (t.zpath && phase != 1 && it.tile >= t.nfc) {   // (R is final: from the row-band pass or from phase 1)
+    count_equal_rows(t, it.tile - t.nfc, f);
+    return;
+  }
   const int c = threadIdx.x & (kFold - 1);   // the row or column of the chunk that an `own` thread ends with
   const bool own = threadIdx.x < kFold;
   if (it.tile < nrows) {

@@ -275,9 +275,12 @@ int plan_build(const skew_tensor_desc *d, int n, Plan *out, bool compact) {
       if (nzr > INT32_MAX / 4) return SKEW_EINVAL;
       tp.off_rsum = ws_part; ws_part = align_up(ws_part + (size_t)nzr * 8);
       for (int32_t k = 0; k < tp.nzb; k++) p.z.push_back({i, k});
-      for (int32_t k = 0; k < tp.nfc; k++) p.fold.push_back({i, k});
+      // fold items: the column chunks, then runs of kZMaxBandRows rows, whose repeated factors are
+      // counted (no more of them than bands: each has a band's statistics to write to)
+      const int64_t nrd = ceil_div(tp.n, kZMaxBandRows);
+      for (int32_t k = 0; k < (int32_t)nrd + tp.nfc; k++) p.fold.push_back({i, k});
       for (int32_t k = 0; k < (int32_t)nzr + tp.nfc; k++) p.fold_rows.push_back({i, k});
-      items_total += nzb + nfc + nzr + nfc;
+      items_total += nzb + nfc + nrd + nzr + nfc;
     } else if (tp.kind == kFactored) {
       const int64_t nfr = ceil_div(tp.n, kFold), nfc = ceil_div(tp.m, kFold);
       if (nfr + nfc > INT32_MAX / 2) return SKEW_EINVAL;

@@ -262,7 +262,14 @@ static void check_plan(const std::string &name, const std::vector<skew_tensor_de
         CHECK(z.count({i, b}) == 1, "%s: band %d", tn.c_str(), b);
         n_z++;
       }
-      for (int c = 0; c < tp.nfc; c++) n_fold += fold.count({i, c});
+      // the fold's items: the column chunks, then runs of rows whose repeated factors are counted into
+      // as many bands' statistics
+      const int nrd = (int)cdiv(tp.n, kZMaxBandRows);
+      CHECK(nrd <= tp.nzb, "%s: %d runs of rows, %d bands", tn.c_str(), nrd, tp.nzb);
+      for (int c = 0; c < tp.nfc + nrd; c++) {
+        CHECK(fold.count({i, c}) == 1, "%s: fold item %d", tn.c_str(), c);
+        n_fold++;
+      }
       CHECK(tp.nfc == cdiv(tp.m, kFold), "%s: fold chunks", tn.c_str());
       ws.push_back({tp.off_colpart, tp.off_colpart + (size_t)tp.nzb * tp.m * 8, tn + ".colpart"});
       ws.push_back({tp.off_zpart, tp.off_zpart + (size_t)tp.nzb * tp.m * 8, tn + ".zpart"});

@@ -4,6 +4,7 @@ empty slices) in every tier, mixed into a table of ordinary tensors, and a table
 nothing but empty tensors. Empty tensors keep no state and take no work; the others must
 match the oracle as they do without them (also with the gradient-norm scaling, whose norm
 runs over every tensor of the table, and the decay)."""
+import numpy as np
 import pytest
 import torch
 
@@ -11,7 +12,7 @@ import oracle
 from paper_2607_19058_amd import SkewAdam
 from paper_2607_19058_amd import workloads as W
 
-from parity_util import ParityRun, log, run
+from parity_util import ParityRun, bits, log, run
 
 pytestmark = pytest.mark.gpu
 
@@ -272,6 +273,61 @@ def test_structured_gradients_clip_factor_matches_the_oracle():
             routes_seen.add(route[k] & 0xF)
     log(f"  total: {pr.stats}; clip routes seen {sorted(routes_seen)}")
     assert pr.stats.ok(), pr.stats
+
+
+def _fast_sum(g, hp, momentum, t):
+    """The sum of U_hat^2 of step t on a fresh state as the row-band pass and the fold form it (sum_j z_j / c'_j in
+    64 bits from the rounded factors), and its bound under independent roundings."""
+    f = np.float32
+    b1, b2 = float(f(hp["beta1"])), float(f(hp["beta2"]))
+    a1, a2 = f(1.0 - b1), f(1.0 - b2)
+    n, m = g.shape
+    x = g.float().numpy()
+    sq = x.astype(np.float64) ** 2
+    r, c = a2 * (sq.sum(1) / m).astype(f), a2 * (sq.sum(0) / n).astype(f)
+    cp = (c / f(r.astype(np.float64).sum() / n)).astype(np.float64)
+    s = np.sqrt(1.0 - b2 ** t)
+    ax = a1 * x * f(s / (1.0 - b1 ** t)) if momentum else x * f(s)
+    terms = ax.astype(np.float64) ** 2 / r.astype(np.float64)[:, None]
+    z = terms.sum(0)
+    return float((z / cp).sum()), 20.0 * 2.0 ** -23 * float(np.sqrt(terms.max() * (z / cp ** 2).sum()))
+
+
+@pytest.mark.parametrize("tier,shape,seed", [(W.BACKBONE, (2048, 11008), 5), (W.EXPERT, (2048, 16384), 5)],
+                         ids=["momentum_11008", "expert_16384"])
+def test_clip_factor_where_only_the_row_factors_repeat(tier, shape, seed):
+    """Rows of two magnitudes and columns that differ: the roundings of R_i c'_j repeat from row to
+    row, and the fast sum lies further from the oracle's than independent roundings would put it.
+    The clipping threshold is chosen so that a rounding boundary of k lies between the two sums, out
+    of reach of that bound from the fast one: only the test of repeated row factors sends the tensor
+    to the re-check, whose k is the oracle's. Widths whose rows take the whole work-group each."""
+    n, m = shape
+    hp, t = dict(oracle.DEFAULTS, eps=1e-30), 5
+    rng = np.random.default_rng(seed)
+    v = torch.from_numpy((rng.uniform(1, 2, m) * 2.0 ** rng.integers(-2, 2, m) * 1e-3).astype(np.float32)).bfloat16()
+    v = v * torch.where(torch.arange(m) % 2 == 0, 1.0, -1.0)
+    g = (torch.where(torch.arange(n) % 3 == 0, 2.0, 1.0)[:, None] * v[None, :]).bfloat16()
+    wl = W.Workload("two_magnitudes", [W.Spec("w", tier, shape, 0)], 1)
+    w = W.init_weight(wl.specs[0], wl, torch.device("cuda"))
+    o = oracle.Tensor(tier=tier, w=bits(w), g=bits(g), tensor_id=0).init_state()
+    oracle.step([o], t, **hp)
+    fast, bound = _fast_sum(g, hp, tier == W.BACKBONE, t)
+    exact = o.rms ** 2 * n * m
+    d = np.float32(0.5) + np.arange(1 << 20).astype(np.float32) * np.float32(2.0 ** -24)
+    k = [d.astype(np.float64) / np.sqrt(x / (n * m)) for x in (exact, fast - 2 * bound, fast + 2 * bound)]
+    kf = [x.astype(np.float32) for x in k]
+    pick = np.flatnonzero((kf[0] != kf[1]) & (kf[1] == kf[2]) & (d < 0.5625))
+    assert pick.size > 0, (exact, fast, bound)
+    G = g.cuda()
+    # (the gradient-norm mode at a norm far above the gradients' own: a scale of 1, the same sums)
+    for j, norm in zip(pick[:: max(1, pick.size // 4)], (0.0, 1e30, 0.0, 1e30)):
+        wj = w.clone()
+        opt = SkewAdam([(tier, wj, G, 0)])
+        opt.step(t, **dict(hp, clip_threshold=float(d[j]), max_grad_norm=norm))
+        kk, route = opt.clip_info()
+        log(f"  threshold {d[j]!r}, norm {norm}: k {kk[0]!r} route {route[0]}, oracle {kf[0][j]!r}, fast sum's {kf[1][j]!r}")
+        assert np.float32(kk[0]) == kf[0][j]
+        opt.close()
 
 
 def test_two_contexts_on_two_streams_match_serial_runs():
