@@ -1097,28 +1097,32 @@ __device__ __forceinline__ double wg_sum(const double *p, int64_t n, double *sh,
   return block_sum(s, sh);
 }
 // q = max(mean R, eps) for a factored tensor (the clamp of the reconstruction), from the
-// sums of R over the fold chunks of rows or over the row bands
-template <class Red>
-__device__ __forceinline__ double sum_r_part(const DevTensor &t, const StepConsts &k, const Red &r) {
+// sums of R over the fold chunks of rows or over the row bands. Every kernel that forms it adds
+// them in one order, that of a work-group of kThreads (lane j takes entries j, j + kThreads, ...;
+// the lanes of a wave, then the waves in order): another one can round q to the other float, and
+// c'_j = C_j / q would differ by 2^-24 between the sum that k comes from and the update.
+__device__ __forceinline__ double sum_r_part(const DevTensor &t, const StepConsts &k, int lane) {
   // row-band tensors keep the sums of R in their band statistics, except in the gradient-
   // norm mode, where the fold forms R and its sums per chunk of rows as for wide tensors
   const bool bands = t.zpath && !k.gclip;
   const double *p = bands ? &t.bst->rsum : t.rsum;
   const int64_t n = bands ? t.nzb : (t.zpath ? (t.n + kFold - 1) / kFold : t.nfr);
   const int64_t stride = bands ? sizeof(BandStats) / sizeof(double) : 1;
-  double s = 0.0;   // the thread's share
-  for (int64_t c = r.lane(); c < n; c += Red::kN) s += ldg(p + c * stride);
+  double s = 0.0;   // the lane's share
+  for (int64_t c = lane; c < n; c += kThreads) s += ldg(p + c * stride);
+  return s;
+}
+__device__ __forceinline__ double sum_r_wave(const DevTensor &t, const StepConsts &k) {   // by one wave
+  double s = 0.0;
+#pragma unroll
+  for (int w = 0; w < kWaves; w++) s += wave_sum_d(sum_r_part(t, k, w * 64 + (int)(threadIdx.x & 63)));
   return s;
 }
 __device__ __forceinline__ float mean_r_from(const DevTensor &t, const StepConsts &k, double sr) {
   return max_nan((float)(sr / (double)t.n), k.eps);
 }
-template <class Red>
-__device__ __forceinline__ float mean_r_of(const DevTensor &t, const StepConsts &k, const Red &r) {
-  return mean_r_from(t, k, r.sum(sum_r_part(t, k, r)));
-}
 __device__ __forceinline__ float mean_r_clamped(const DevTensor &t, const StepConsts &k, double *sh) {
-  return mean_r_of(t, k, RedGroup{sh});
+  return mean_r_from(t, k, block_sum(sum_r_part(t, k, (int)threadIdx.x), sh));
 }
 
 // --------------------------------------------------------------------------------------------
@@ -1138,7 +1142,7 @@ struct FoldShared {
   double part[2][kFoldParts][kFold];
   double stat[kFoldThreads / 64][8];
   float nb[kFold];
-  float q;
+  double rsum[kWaves];
 };
 // The sums of a[p * stride + x0 + c] over p = 0 .. n - 1 (and of b) for the columns x0 + c < xn of
 // a chunk: two columns per thread (16-byte loads), the p split in kFoldParts runs of their own,
@@ -1302,15 +1306,19 @@ __global__ __launch_bounds__(kFoldThreads) __attribute__((amdgpu_waves_per_eu(8)
     if (!t.zpath) chunk_stats(t.cst + t.nfr + (it.tile - nrows), nullptr, Cv, 0.0, f);
   } else {
     // row-band tensor: C_j (phase 0; phase 2 has it from phase 1), c'_j = C_j / max(mean R,
-    // eps) and sum_j z_j / c'_j over the chunk; wave 0 forms q while the partials load
-    if (threadIdx.x < 64) {
-      const float q0 = mean_r_of(t, k, RedWave{});
-      if (threadIdx.x == 0) f.q = q0;
+    // eps) and sum_j z_j / c'_j over the chunk; the first waves add the sums of R while the
+    // partials load (fold_sum's barrier covers theirs)
+    if (threadIdx.x < kThreads) {
+      const double sr = wave_sum_d(sum_r_part(t, k, (int)threadIdx.x));
+      if ((threadIdx.x & 63) == 0) f.rsum[threadIdx.x >> 6] = sr;
     }
     const int64_t j = (int64_t)it.tile * kFold + c;
     double cs, zs;
     fold_sum<true>(t.colpart, t.zpart, t.nzb, t.ldp, j - c, t.m, f, cs, zs);
-    const float q = f.q;
+    double sr = 0.0;
+    for (int w = 0; w < kWaves; w++) sr += f.rsum[w];
+    const float q = mean_r_from(t, k, sr);
+    if (it.tile == 0 && threadIdx.x == 0) stg(&t.sc->q, q);   // for the clip stage and the update
     double sj = 0.0, sj2 = 0.0;
     float cmn = __builtin_inff(), cmx = 0.f, Cj = 0.f;
     int bad = 0;
@@ -1845,10 +1853,10 @@ template <class Red>
 __device__ __forceinline__ SliceSum slice_sum(const DevTensor &t, const StepConsts &k, const Red &r) {
   SliceSum o = {0.0, 0.0, 0, 0, 0};
   const bool factored = t.kind == kFactored;
-  // s: the sum of R, then of the row-band tensors Y, S and S2 (below), of others the sum of
-  // U_hat^2, nothing and the sum of U_hat^4; and the repeats of R and of C
+  // s: the sum of R (wide factored tensors), then of the row-band tensors Y, S and S2 (below), of
+  // others the sum of U_hat^2, nothing and the sum of U_hat^4; and the repeats of R and of C
   RedAll a;
-  if (factored) a.s[0] = sum_r_part(t, k, r);
+  if (factored && !t.zpath && Red::kN == kThreads) a.s[0] = sum_r_part(t, k, r.lane());
   if (t.zpath) {
     for (int64_t b = r.lane(); b < t.nzb; b += Red::kN) {
       const BandStats *x = t.bst + b;
@@ -1891,7 +1899,8 @@ __device__ __forceinline__ SliceSum slice_sum(const DevTensor &t, const StepCons
     }
   }
   r.all(a);
-  const float q = factored ? mean_r_from(t, k, a.s[0]) : 0.f;
+  // (the fold has formed a row-band tensor's q)
+  const float q = !factored || t.zpath ? 0.f : mean_r_from(t, k, Red::kN == kThreads ? a.s[0] : sum_r_wave(t, k));
   if (factored) o.repeats = repeats_rule(t, a.rmn, a.rmx, a.cmn, a.cmx, a.s[4], a.s[5]);
   if (t.zpath) {
     // SU2: the sum over the terms t_ij = (s x)^2 / (R_i c'_j) of t_ij^2 <= umax * sum_j z_j / c'_j^2
@@ -1933,7 +1942,7 @@ __device__ __forceinline__ SliceSum slice_sum(const DevTensor &t, const StepCons
     o.E = t.kind == kFactored ? 20.0 * 0x1p-23 * sqrt(Q4) + 1e-14 * o.S : 0.0;
     if (o.repeats) o.E = fmax(o.E, kRigorousRel * o.S + 1e-14 * o.S);
   }
-  if (r.lead()) stg(&t.sc->q, q);
+  if (!t.zpath && r.lead()) stg(&t.sc->q, q);
   return o;
 }
 

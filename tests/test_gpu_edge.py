@@ -330,6 +330,46 @@ def test_clip_factor_where_only_the_row_factors_repeat(tier, shape, seed):
         opt.close()
 
 
+def test_mean_of_the_row_factors_is_one_float_for_the_whole_step():
+    """max(mean R, eps) at a rounding midpoint that two of the sums' orders leave on either side: band 0
+    of the row-band pass holds 1 + x and half an ulp of the float, and two later bands half an ulp
+    of the double each, which vanish when added to it one by one and count when added to each other
+    first. The fast sum's c'_j and those of the exact float sequence (and of the update) come from
+    the same q, so the clip factor is the same whichever decides it."""
+    n, m = 2048, 4096
+    far = (64 * 8, 96 * 8)   # rows of bands 64 and 96 (blocks of 8 rows; the plan has 97 bands or more)
+    base = 1.0 + ((torch.arange(m) * 37) % 32) * 2 / 128     # neighbours differ: no repeated column factors
+    gen = torch.Generator().manual_seed(3)
+    while True:
+        v = base + torch.randint(0, 2, (m,), generator=gen) / 128
+        r0 = np.float32((v.double() ** 2).mean().item())
+        if 1.0 <= float(r0) < 2.0 and r0.view(np.uint32) % 2 == 0:   # the tie goes down
+            break
+    g = torch.zeros((n, m), dtype=torch.bfloat16)
+    g[0] = v.bfloat16()
+    g[1] = 2.0 ** -12
+    for r in far:
+        g[r, ::2] = 2.0 ** -26
+    assert torch.equal(g[0].double(), v.double())
+    g[:, 1::4] *= -1
+    hp = dict(beta1=0.9, beta2=0.0, eps=1e-30)
+    G = g.cuda()
+    fast = 0
+    for j in range(32):
+        d = float(np.float32(0.01 * (1 + j / 37)))
+        ks = []
+        for flags in (0, 1):   # 1: the exact sequence decides every clip factor
+            w = torch.full((n, m), 0.02, dtype=torch.bfloat16, device="cuda")
+            opt = SkewAdam([(W.EXPERT, w, G, 0)])
+            opt.step(1, clip_threshold=d, flags=flags, **hp)
+            kk, route = opt.clip_info()
+            ks.append(np.float32(kk[0]))
+            fast += flags == 0 and route[0] & 0xF == 0
+            opt.close()
+        assert ks[0] < 1.0 and ks[0] == ks[1], (d, ks)
+    assert fast >= 8, "the fast sums decide some of them"
+
+
 def test_two_contexts_on_two_streams_match_serial_runs():
     """Two contexts stepped at the same time on two streams, each with its own state and
     workspace, end with the weights, state and clip factors, bit for bit, of the same two
