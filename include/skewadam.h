@@ -188,8 +188,10 @@ int skew_state_init(skew_ctx **ctx, skew_tensor_desc *d, int n, void *state, siz
  * newer skew_state_init_static on the same GPU takes the array over, and skew_step on the
  * older context then returns SKEW_ESTALE without launching anything. Steps of contexts
  * that share the array must not overlap (they would race on it).
- * Errors: as skew_state_init, and SKEW_ETOOBIG when skew_state_bytes() reports more than
- * SKEW_STATIC_WORKSPACE_BYTES of workspace (nothing is touched then). */
+ * A table whose skew_state_bytes() workspace exceeds SKEW_STATIC_WORKSPACE_BYTES is planned
+ * with larger bands of rows, as small ones as fit (the step may take longer).
+ * Errors: as skew_state_init, and SKEW_ETOOBIG when no plan of the table fits in
+ * SKEW_STATIC_WORKSPACE_BYTES (nothing is touched then). */
 int skew_state_init_static(skew_ctx **ctx, skew_tensor_desc *d, int n, void *state, size_t state_bytes,
                            void *stream);
 

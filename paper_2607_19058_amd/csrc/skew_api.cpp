@@ -295,12 +295,8 @@ int skew_state_init_static(skew_ctx **ctx, skew_tensor_desc *d, int n, void *sta
   if (ctx == nullptr) return SKEW_EINVAL;
   *ctx = nullptr;
   Plan p;
-  int rc = plan_build(d, n, &p);
+  int rc = plan_build_within(d, n, static_workspace_bytes(), &p);
   if (rc != SKEW_OK) return rc;
-  if (p.ws_bytes > static_workspace_bytes()) {
-    rc = plan_build(d, n, &p, true);
-    if (rc != SKEW_OK) return rc;
-  }
   if (p.ws_bytes > static_workspace_bytes()) return SKEW_ETOOBIG;
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return SKEW_EHIP;

@@ -224,8 +224,10 @@ struct Plan {
 inline size_t align_up(size_t x, size_t a = kAlign) { return (x + a - 1) / a * a; }
 
 // Validates the table and computes sizes, offsets and the work-item lists.
-// `compact`: the plan with the least workspace (large bands, no padding), for the static workspace.
-int plan_build(const skew_tensor_desc *d, int n, Plan *out, bool compact = false);
+int plan_build(const skew_tensor_desc *d, int n, Plan *out);
+// The same, with a workspace of at most `limit` bytes where that is possible (the static workspace),
+// else the plan with the least workspace: larger row bands and update tiles, no padding.
+int plan_build_within(const skew_tensor_desc *d, int n, size_t limit, Plan *out);
 
 // The library's static workspace (skew_state_init_static): the device address of the
 // file-scope array on the current device, looked up once per device (skew_kernels.hip).

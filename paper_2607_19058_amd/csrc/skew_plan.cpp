@@ -130,8 +130,15 @@ static int64_t choose_tile_elems(const skew_tensor_desc *d, int n) {
   return t;
 }
 
-int plan_build(const skew_tensor_desc *d, int n, Plan *out, bool compact) {
-  if (n < 0 || (n > 0 && d == nullptr) || out == nullptr) return SKEW_EINVAL;
+// What trades workspace for time: elements per row band and per update tile, and (`compact` unset)
+// padded column partials and flat exact-moment tensors
+struct PlanSize {
+  int64_t band_elems, tile_elems;
+  bool compact;
+};
+static int plan_sized(const skew_tensor_desc *d, int n, const PlanSize &size, Plan *out) {
+  const int64_t band_elems = size.band_elems, tile_elems = size.tile_elems;
+  const bool compact = size.compact;
   Plan p;
   // descriptors -> sub-tensors: a stacked (ndim 3) descriptor of E matrices becomes E
   // sub-tensors (one per slice, factored on its own, Sec. 3 footnote) that share one clip
@@ -154,8 +161,6 @@ int plan_build(const skew_tensor_desc *d, int n, Plan *out, bool compact) {
     if (nsub > INT32_MAX / 4) return SKEW_EINVAL;
   }
   p.t.resize((size_t)nsub);
-  const int64_t band_elems = compact ? kZBandElems : choose_band_elems(d, n);
-  const int64_t tile_elems = compact ? kTileElems : choose_tile_elems(d, n);
   size_t st = 0;        // state bytes
   size_t ws_part = 0;   // partial-sum bytes (offsets relative to the partial region)
   int64_t items_total = 0;
@@ -324,10 +329,9 @@ int plan_build(const skew_tensor_desc *d, int n, Plan *out, bool compact) {
   // workspace: [device tensor table][items p1|z (by variant)|fold|p2|p3|clip][re-check lists][partials]
   size_t ws = 0;
   p.off_table = ws; ws = align_up(ws + sizeof(DevTensor) * (size_t)std::max(nt, 1));
-  // the item lists as the device keeps them: the fold's items appear twice (the whole list,
-  // and split into row-band and other tensors)
+  // the item lists as the device keeps them
   p.off_items = ws;
-  ws = align_up(ws + sizeof(Item) * (p.p1.size() + p.z.size() + 2 * p.fold.size() + p.p2.size() + p.p3.size() +
+  ws = align_up(ws + sizeof(Item) * (p.p1.size() + p.z.size() + p.fold.size() + p.p2.size() + p.p3.size() +
                                      p.clip.size() + p.clip_slices.size() + p.fold_rows.size() + 1));
   p.off_lists = ws;
   ws = align_up(ws + sizeof(RecheckLists) + sizeof(int32_t) * 2 * (size_t)std::max(nt, 1));
@@ -349,6 +353,25 @@ int plan_build(const skew_tensor_desc *d, int n, Plan *out, bool compact) {
   p.ws_bytes = ws + ws_part;
   *out = std::move(p);
   return SKEW_OK;
+}
+
+int plan_build(const skew_tensor_desc *d, int n, Plan *out) {
+  if (n < 0 || (n > 0 && d == nullptr) || out == nullptr) return SKEW_EINVAL;
+  return plan_sized(d, n, {choose_band_elems(d, n), choose_tile_elems(d, n), false}, out);
+}
+
+// A row band costs two rows of column partials, so most of a large table's workspace shrinks as the
+// bands grow: the smallest bands that fit are taken (they fill the chip best), up to those of
+// kZMaxBandRows rows
+int plan_build_within(const skew_tensor_desc *d, int n, size_t limit, Plan *out) {
+  int rc = plan_build(d, n, out);
+  int64_t band = choose_band_elems(d, n);
+  constexpr int64_t kLast = (int64_t)kZMaxBandRows * kZWaves * kZMaxSeg * kChunk;
+  for (bool last = false; rc == SKEW_OK && out->ws_bytes > limit && !last; band += band / 2) {
+    last = band >= kLast;
+    rc = plan_sized(d, n, {last ? kLast * 4 : band, kTileElems, true}, out);   // (4 > kMomCost)
+  }
+  return rc;
 }
 
 }  // namespace skew

@@ -164,11 +164,7 @@ static void check_regions(std::vector<Region> r, size_t limit, const char *buf) 
           r[i - 1].a, r[i - 1].b, r[i].what.c_str(), r[i].a, r[i].b);
 }
 
-static void check_plan(const std::string &name, const std::vector<skew_tensor_desc> &d) {
-  Plan p;
-  const int rc = plan_build(d.data(), (int)d.size(), &p);
-  CHECK(rc == SKEW_OK, "%s: plan_build %d", name.c_str(), rc);
-  if (rc != SKEW_OK) return;
+static void check_one_plan(const std::string &name, const Plan &p) {
   const int nt = (int)p.t.size();
   std::vector<Region> st, ws;
   std::set<std::pair<int, int>> p3, z, p1, fold, p2, clip;
@@ -308,6 +304,17 @@ static void check_plan(const std::string &name, const std::vector<skew_tensor_de
   ws.push_back({p.off_gscale, p.off_gscale + 4, "gscale"});
   ws.push_back({p.off_gsq, p.off_gsq + 8 * nt1, "gsq"});
   check_regions(ws, p.ws_bytes, (name + " workspace").c_str());
+}
+
+// the plan of a table, and the one with the least workspace
+static void check_plan(const std::string &name, const std::vector<skew_tensor_desc> &d) {
+  Plan p, least;
+  int rc = plan_build(d.data(), (int)d.size(), &p);
+  CHECK(rc == SKEW_OK, "%s: plan_build %d", name.c_str(), rc);
+  if (rc == SKEW_OK) check_one_plan(name, p);
+  rc = plan_build_within(d.data(), (int)d.size(), 0, &least);
+  CHECK(rc == SKEW_OK && least.state_bytes == p.state_bytes, "%s: plan_build_within %d", name.c_str(), rc);
+  if (rc == SKEW_OK) check_one_plan(name + " (least)", least);
 }
 
 // set-up and one step on host stand-ins of every buffer (tables small enough to allocate)
@@ -459,6 +466,23 @@ int main() {
   check_plan("big", big);
   check_plan("stacked", stacked);
   check_plan("variants", variants);
+  // tables that a plan of large bands keeps within the static workspace (2^21 elements per band: 49.3,
+  // 46.5 and 62 MiB), whatever their own plan takes: its bands are the smallest that fit
+  {
+    std::vector<skew_tensor_desc> a, b, c;
+    for (int k = 0; k < 600; k++) a.push_back(mk(0, 2, 2048, 2048, 2048, id++));
+    for (int k = 0; k < 700; k++) b.push_back(mk(0, 2, 4096, 1024, 1024, id++));
+    for (int k = 0; k < 100; k++) c.push_back(mk(k % 2, 2, 6144, 4096, 4096, id++));
+    for (auto *d : {&a, &b, &c}) {
+      Plan p;
+      const int rc = plan_build_within(d->data(), (int)d->size(), static_workspace_bytes(), &p);
+      CHECK(rc == SKEW_OK && p.ws_bytes <= static_workspace_bytes(), "%zu matrices: %zu bytes of workspace", d->size(),
+            p.ws_bytes);
+      CHECK(2 * p.ws_bytes > static_workspace_bytes(), "%zu matrices: larger bands than needed: %zu bytes", d->size(),
+            p.ws_bytes);
+      check_one_plan("static", p);
+    }
+  }
   // row strides around the largest span of a block of rows, for every number of chunks per wave,
   // with and without momentum
   for (int tier : {0, 1})
