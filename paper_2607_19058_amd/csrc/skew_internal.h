@@ -18,13 +18,14 @@ constexpr int kFold = 256;              // rows (or columns) folded by one work-
 constexpr int64_t kTileElems = 1 << 16; // elements per update tile, at most: 128 KiB of bf16 gradient
 constexpr size_t kAlign = 256;
 
-// Row-band pass (pass 1 of factored matrices of kZMinCols to 16384 columns): a work-group of
+// Row-band pass (pass 1 of factored matrices up to 16384 columns): a work-group of
 // kZThreads threads owns whole rows, so it knows each R_i as soon as the row is summed.
 constexpr int kSub = 2;                  // update-sum passes: work-groups (row interleaves) per tile
 constexpr int kZThreads = 512;           // 8 wave64, up to 256 VGPRs each: a work-group fills a compute unit
 constexpr int kZWaves = kZThreads / 64;
 constexpr int kZMaxSeg = 4;              // 512-column chunks per wave and row
-constexpr int kZMinCols = 8;             // the lane at a row's end loads the row's last 8 columns
+constexpr int kZMinCols = 8;             // the lane at a row's end loads the row's last 8 columns (narrower
+                                         // rows: one column per lane)
 constexpr int64_t kZBandElems = 1 << 22; // elements per row band, at most: 8 MiB of bf16 gradient
 constexpr int64_t kZMinBandElems = 1 << 14;   // ... and at least (unless one block of rows is longer)
 constexpr int kZVariants = 16;           // item lists: lg(nseg) * 4 + (unaligned rows ? 2 : 0) + momentum,

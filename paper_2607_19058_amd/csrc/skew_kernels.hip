@@ -503,7 +503,7 @@ __global__ __launch_bounds__(kThreads) void p1_kernel(const DevTensor *__restric
 }
 
 // --------------------------------------------------------------------------------------------
-// Row-band pass: pass 1 of factored matrices of 8 to 16384 columns (Eq. 1 and the update
+// Row-band pass: pass 1 of factored matrices up to 16384 columns (Eq. 1 and the update
 // sum of Alg. 1 in one read of G).
 //
 // A work-group owns a band of whole rows, so R_i <- b2 R_i + a2 mean_j g_ij^2 is final as
@@ -621,10 +621,13 @@ __device__ __forceinline__ double rsq_d(double x) {
 
 // MODE 0: the whole pass; 1: the sums of g^2 alone (row sums to ainv; no momentum needed);
 // 2: z, the floored sum and the band statistics of the scaled gradient, with R folded
-template <int NSEG, int RB, bool MOM, int MODE>
+// NARROW: rows of fewer than 8 columns, one column per lane in the first of its 8 places (no 16-byte
+// load of the row's last 8 columns exists; the other places are zeros)
+template <int NSEG, int RB, bool MOM, int MODE, bool NARROW = false>
 __device__ __forceinline__ void p1z_body(const DevTensor &t, int band, const StepConsts &k, double *colbuf,
                                          double *rowsh, double *sh, float *rstash) {
   static_assert(MODE != 1 || !MOM, "the sums pass reads no momentum");
+  static_assert(!NARROW || NSEG == 1, "a narrow row is one chunk");
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int64_t m = t.m, ld = t.ld;
   const int zcw = t.zcw;
@@ -663,9 +666,9 @@ __device__ __forceinline__ void p1z_body(const DevTensor &t, int band, const Ste
 #pragma unroll
   for (int s = 0; s < NSEG; s++) {
     chs[s] = wg + s * wpr;
-    const int64_t col = (int64_t)chs[s] * kChunk + lane * 8;
+    const int64_t col = NARROW ? lane : (int64_t)chs[s] * kChunk + lane * 8;
     const bool ok = active && chs[s] < zcw && col < m;
-    const int64_t over = col + 8 > m ? col + 8 - m : 0;
+    const int64_t over = !NARROW && col + 8 > m ? col + 8 - m : 0;
     if (ok && over) tail = (int)over;
 #pragma unroll
     for (int b = 0; b < RB; b++) {
@@ -674,7 +677,7 @@ __device__ __forceinline__ void p1z_body(const DevTensor &t, int band, const Ste
       if constexpr (VM) vm[b][s] = ok ? (uint32_t)((row * m + col - over) * 4) : 0x80000000u;
     }
   }
-  const bool ragged = (m & 7) != 0;
+  const bool ragged = !NARROW && (m & 7) != 0;
 
   double cacc[NSEG][8], zacc[NSEG][8];
 #pragma unroll
@@ -697,7 +700,12 @@ __device__ __forceinline__ void p1z_body(const DevTensor &t, int band, const Ste
 #pragma unroll
     for (int b = 0; b < RB; b++)
 #pragma unroll
-      for (int s = 0; s < NSEG; s++) dst[b][s] = __builtin_amdgcn_raw_buffer_load_b128(rs, vo[b][s], 0, 0);
+      for (int s = 0; s < NSEG; s++) {
+        if constexpr (NARROW)
+          dst[b][s] = u32x4_t{(uint32_t)__builtin_amdgcn_raw_buffer_load_b16(rs, vo[b][s], 0, 0), 0u, 0u, 0u};
+        else
+          dst[b][s] = __builtin_amdgcn_raw_buffer_load_b128(rs, vo[b][s], 0, 0);
+      }
     if constexpr (MODE != 1) {
       const int64_t i = rbase + rfold;
       rold = ldg(t.R + (i < t.n ? i : t.n - 1));
@@ -721,8 +729,13 @@ __device__ __forceinline__ void p1z_body(const DevTensor &t, int band, const Ste
             asm volatile("" : "+v"(o));   // formed here, not kept in a register of its own
             o = (o << 1) | (o & 0x80000000u);
           }
-          dst[b][s][0] = __builtin_amdgcn_raw_buffer_load_b128(rs, o, 0, 0);
-          dst[b][s][1] = __builtin_amdgcn_raw_buffer_load_b128(rs, o + 16u, 0, 0);
+          if constexpr (NARROW) {
+            dst[b][s][0] = u32x4_t{(uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rs, o, 0, 0), 0u, 0u, 0u};
+            dst[b][s][1] = u32x4_t{0u, 0u, 0u, 0u};
+          } else {
+            dst[b][s][0] = __builtin_amdgcn_raw_buffer_load_b128(rs, o, 0, 0);
+            dst[b][s][1] = __builtin_amdgcn_raw_buffer_load_b128(rs, o + 16u, 0, 0);
+          }
         }
     }
   };
@@ -917,7 +930,7 @@ __device__ __forceinline__ void p1z_body(const DevTensor &t, int band, const Ste
       const int64_t cend = m - (int64_t)c0 * kChunk < (int64_t)nc * kChunk ? m - (int64_t)c0 * kChunk
                                                                           : (int64_t)nc * kChunk;
       for (int c = threadIdx.x; c < (int)cend; c += kZThreads) {
-        const double *p = colbuf + ((c >> 9) * 8 + (c & 7)) * kColPad + ((c >> 3) & 63);
+        const double *p = NARROW ? colbuf + c : colbuf + ((c >> 9) * 8 + (c & 7)) * kColPad + ((c >> 3) & 63);
         double v = p[0];
         for (int g = 1; g < rpi; g++) v += p[g * nc * 8 * kColPad];
         stg(dst + (int64_t)band * t.ldp + (int64_t)c0 * kChunk + c, v);
@@ -996,14 +1009,18 @@ __global__ __launch_bounds__(kZThreads) void p1z_kernel(const DevTensor *__restr
   const DevTensor &t = TT[it.tensor];
   if (MODE != 1 && t.momentum) {
     constexpr bool M = MODE != 1;
-    if (t.nseg == 1)
+    if (t.m < kZMinCols)
+      p1z_body<1, zrows_per_group(1, true, MODE), M, MODE, true>(t, it.tile, k, colbuf, rowsh, sh, rstash);
+    else if (t.nseg == 1)
       p1z_body<1, zrows_per_group(1, true, MODE), M, MODE>(t, it.tile, k, colbuf, rowsh, sh, rstash);
     else if (t.nseg == 2)
       p1z_body<2, zrows_per_group(2, true, MODE), M, MODE>(t, it.tile, k, colbuf, rowsh, sh, rstash);
     else
       p1z_body<4, zrows_per_group(4, true, MODE), M, MODE>(t, it.tile, k, colbuf, rowsh, sh, rstash);
   } else {   // (mode 1 reads no momentum: its rows per group do not depend on it)
-    if (t.nseg == 1)
+    if (t.m < kZMinCols)
+      p1z_body<1, zrows_per_group(1, false, MODE), false, MODE, true>(t, it.tile, k, colbuf, rowsh, sh, rstash);
+    else if (t.nseg == 1)
       p1z_body<1, zrows_per_group(1, false, MODE), false, MODE>(t, it.tile, k, colbuf, rowsh, sh, rstash);
     else if (t.nseg == 2)
       p1z_body<2, zrows_per_group(2, false, MODE), false, MODE>(t, it.tile, k, colbuf, rowsh, sh, rstash);

@@ -20,10 +20,15 @@ static int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // 260 with three); else four. A block is rpi * zrb rows, zrb (rows per group) as many as the registers hold: two
 // blocks (bf16 gradient, and fp32 momentum where kept) beside the band's double sums.
 // zrb = 0: no row band.
+// Rows of fewer than 8 columns: a matrix of up to kNarrowRows of them takes the tiled passes (step of 100
+// matrices of 64 x 3: 55 us tiled, 59 by row bands; of 64 slices of 64 x 7: 64, 69). Their fold and
+// update sums go over the partials of every 128 rows: longer ones take row bands (16384 x 4: 100 us
+// tiled, 62 by row bands; 1e6 x 5: 4210, 739; 2^25 x 1: 193 ms, 16.8).
+constexpr int64_t kNarrowRows = 2048;
 struct RowBandShape {
   int64_t zcw, nseg, rpi, zrb;
 };
-static RowBandShape rowband_shape(int64_t m, int64_t ld, bool momentum) {
+static RowBandShape rowband_shape(int64_t n, int64_t m, int64_t ld, bool momentum, bool compact) {
   RowBandShape r;
   r.zcw = ceil_div(m, kChunk);
   r.nseg = r.zcw <= 1 ? 1 : (r.zcw <= 2 * kZWaves ? 2 : (!momentum && r.zcw <= 3 * kZWaves ? 3 : 4));
@@ -35,13 +40,18 @@ static RowBandShape rowband_shape(int64_t m, int64_t ld, bool momentum) {
   const int64_t wpr = ceil_div(r.zcw, r.nseg);
   r.rpi = wpr <= kZWaves ? kZWaves / wpr : 0;
   r.zrb = zrows_per_group((int)r.nseg, momentum, 0);
-  // rows too short for the row's end to be one 16-byte load, too long for the work-group, or so
-  // far apart that the byte offsets of a block (of the mode with the longest blocks) pass 31 bits
-  // take the tiled passes
-  if (m < kZMinCols || r.rpi < 1 || ld > 0x7FFFFFFF / 2 / (r.rpi * zrows_per_group_max((int)r.nseg, momentum)))
+  // rows too long for the work-group, or so far apart that the byte offsets of a block (of the mode
+  // with the longest blocks) pass 31 bits, take the tiled passes
+  if (r.rpi < 1 || ld > 0x7FFFFFFF / 2 / (r.rpi * zrows_per_group_max((int)r.nseg, momentum)))
     r.zrb = 0;
+  if (m < kZMinCols && n <= kNarrowRows && !compact) r.zrb = 0;
   return r;
 }
+
+// A row of a few columns takes a wave as long as one of a whole chunk, and counts as one in the band
+// size (bands of 2048 rows whatever the width would be 64 waits for memory one after the other)
+constexpr int64_t kZMinRowCost = 128;
+static int64_t row_cost(int64_t m) { return m < kZMinCols ? kZMinRowCost : m; }
 
 // Rows per band for bands of about `band_elems` elements (fewer with momentum, whose elements
 // take kMomCost times as long): whole blocks, at most kZMaxBandRows
@@ -49,7 +59,7 @@ constexpr double kMomCost = 3.3;
 static int64_t band_rows(const RowBandShape &r, int64_t m, bool momentum, int64_t band_elems) {
   const int64_t rows_block = r.rpi * r.zrb;
   const int64_t e = momentum ? (int64_t)((double)band_elems / kMomCost) : band_elems;
-  const int64_t rows = ceil_div(std::max<int64_t>(1, e / m), rows_block) * rows_block;
+  const int64_t rows = ceil_div(std::max<int64_t>(1, e / row_cost(m)), rows_block) * rows_block;
   return std::min<int64_t>(rows, kZMaxBandRows / rows_block * rows_block);
 }
 
@@ -78,10 +88,10 @@ static int64_t choose_band_elems(const skew_tensor_desc *d, int n) {
     if (x.ndim == 1 || x.rows <= 0 || x.cols <= 0 || (x.ndim == 3 && x.batch <= 0)) continue;
     if (x.tier == SKEW_TIER_ROUTER && !(x.state_flags & SKEW_STATE_FACTORED)) continue;
     const bool mom = x.tier == SKEW_TIER_BACKBONE || (x.state_flags & SKEW_STATE_MOMENTUM) != 0;
-    const RowBandShape r = rowband_shape(x.cols, x.ld, mom);
+    const RowBandShape r = rowband_shape(x.rows, x.cols, x.ld, mom, false);
     if (r.zrb < 1) continue;
     const double E = x.ndim == 3 ? (double)x.batch : 1.0;
-    cost += E * (double)x.rows * (double)x.cols * (mom ? kMomCost : 1.0) * kElemUs;
+    cost += E * (double)x.rows * (double)row_cost(x.cols) * (mom ? kMomCost : 1.0) * kElemUs;
     grad_bytes += E * (double)x.rows * (double)x.cols * 2.0;
     bool found = false;
     for (size_t j = shapes.size(); j-- > 0 && j + 8 >= shapes.size() && !found;) {
@@ -257,7 +267,7 @@ static int plan_sized(const skew_tensor_desc *d, int n, const PlanSize &size, Pl
     // columns of every band, which at a power of two distance all fall on the same memory channels
     tp.ldp = tp.m + (!compact && tp.m % 512 == 0 ? 32 : 0);
     // the row-band pass (see rowband_shape)
-    const RowBandShape rbs = rowband_shape(tp.m, tp.ld, tp.momentum != 0);
+    const RowBandShape rbs = rowband_shape(tp.n, tp.m, tp.ld, tp.momentum != 0, compact);
     const int64_t zcw = rbs.zcw, nseg = rbs.nseg, rpi = rbs.rpi, zrb = rbs.zrb;
     tp.zpath = (tp.kind == kFactored && rpi > 0 && zrb >= 1) ? 1 : 0;
     if (tp.zpath) {

@@ -483,6 +483,25 @@ int main() {
       check_one_plan("static", p);
     }
   }
+  // rows of fewer than 8 columns: few of them by tiles, many by row bands (the tiled passes' time grows
+  // with the square of the rows), and always by row bands where the workspace is short: 7.5e6 x 4
+  // fits the static one
+  for (int64_t m = 1; m < 8; m++)
+    for (int64_t n : {1, 2047, 2048, 2049, 100003}) {
+      const std::vector<skew_tensor_desc> d = {mk(1, 2, n, m, m + 1, id), mk(0, 2, n, m, m, id + 1)};
+      check_plan("narrow " + std::to_string(n) + " x " + std::to_string(m), d);
+      Plan p, least;
+      plan_build(d.data(), 2, &p);
+      plan_build_within(d.data(), 2, 0, &least);
+      for (int k = 0; k < 2; k++)
+        CHECK(p.t[k].zpath == (n > 2048) && least.t[k].zpath == 1, "narrow %lld x %lld", (long long)n, (long long)m);
+    }
+  {
+    const skew_tensor_desc d = mk(1, 2, 7500000, 4, 4, id);
+    Plan p;
+    CHECK(plan_build_within(&d, 1, static_workspace_bytes(), &p) == SKEW_OK && p.ws_bytes <= static_workspace_bytes(),
+          "7.5e6 x 4: %zu bytes of workspace", p.ws_bytes);
+  }
   // row strides around the largest span of a block of rows, for every number of chunks per wave,
   // with and without momentum
   for (int tier : {0, 1})

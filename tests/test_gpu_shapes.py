@@ -83,6 +83,26 @@ def test_narrow_chunks_taken_several_rows_at_a_time(tier):
     assert pr.stats.ok(), pr.stats
 
 
+@pytest.mark.parametrize("hp", [oracle.DEFAULTS, dict(oracle.DEFAULTS, weight_decay=0.05, max_grad_norm=1e-2)],
+                         ids=["plain", "gnorm+decay"])
+@pytest.mark.parametrize("pad,shift", [(0, 0), (3, 1)], ids=["dense", "unaligned"])
+@pytest.mark.parametrize("tier", [W.BACKBONE, W.EXPERT], ids=["momentum", "expert"])
+def test_rows_of_fewer_than_8_columns(tier, pad, shift, hp):
+    """Up to 2048 of them take the tiled passes, more the row-band pass, one column per lane: every width,
+    with numbers of rows on both sides, and a stack."""
+    specs = [W.Spec(f"w{n}x{m}", tier, (n, m), 10 * n + m) for m in range(1, 8) for n in (1, 2, 31, 33, 530, 2048, 2049, 4099)]
+    specs.append(W.Spec("stack", tier, (5, 77, 3), 9))
+    ws, gs, bufs = _views(specs, pad, shift)
+    log(f"[parity] widths 1 to 7, tier {tier}, row stride width + {pad}, {hp}; 3 steps")
+    pr = ParityRun(W.Workload("narrow_rows", specs, 3), weights=ws, grads=gs, hp=hp)
+    for t in (1, 2, 3):
+        pr.step(t)
+    assert pr.stats.ok(), pr.stats
+    for s, (wb, w) in zip(specs, bufs):   # nothing outside the views was written
+        w.fill_(3.0)
+        assert bool((wb == 3.0).all()), s.name
+
+
 @pytest.mark.parametrize("flags", [0, 2], ids=["plain", "exact_ulp"])
 @pytest.mark.parametrize("fp32", [False, True], ids=["bf16", "fp32"])
 def test_exact_moment_tensors_at_row_ends(fp32, flags):
