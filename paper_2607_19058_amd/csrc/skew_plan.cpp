@@ -130,24 +130,35 @@ static int64_t choose_band_elems(const skew_tensor_desc *d, int n) {
 // with its column factors). Update pass at tiles of 2^16 / 2^13 / 2^12 / 2^11 elements: 4.5e6
 // elements 39 / 18 / 21 / 29 us; 5.0e7 odd-width ones 142 us at 2^16, 110 at 2^14, 129 at 2^13.
 constexpr int64_t kMinTileElems = 1 << 13, kTileCount = 2048;
-static int64_t choose_tile_elems(const skew_tensor_desc *d, int n) {
+// Tiles of the tiled passes: a tile costs a row of column partials and the column factors of the update
+// sums, and two work-groups of pass 1 fit a compute unit, so kWideTileCount of them are enough
+// (counted over the tensors of those passes alone). Step of one 20000-column matrix at tiles of
+// 2^16 / 2^14 / 2^13 elements: 3.4e7 elements 148 / 194 / - us; 1.7e7 96 / - / 117; 8e6 (2^15) 70 / - / 79.
+constexpr int64_t kWideTileCount = 256;
+static bool tiled(const skew_tensor_desc &x) {   // a factored matrix that the row-band pass does not take
+  const bool mom = x.tier == SKEW_TIER_BACKBONE || (x.state_flags & SKEW_STATE_MOMENTUM) != 0;
+  return x.ndim != 1 && (x.tier != SKEW_TIER_ROUTER || (x.state_flags & SKEW_STATE_FACTORED) != 0) &&
+         rowband_shape(x.rows, x.cols, x.ld, mom, false).zrb < 1;
+}
+static int64_t choose_tile_elems(const skew_tensor_desc *d, int n, bool wide) {
+  const double count = (double)(wide ? kWideTileCount : kTileCount);
   double total = 0.0;
   for (int i = 0; i < n; i++)
-    if (d[i].rows > 0 && d[i].cols > 0)
+    if (d[i].rows > 0 && d[i].cols > 0 && (!wide || tiled(d[i])))
       total += (double)d[i].rows * (double)d[i].cols * (d[i].ndim == 3 ? (double)std::max<int64_t>(d[i].batch, 0) : 1.0);
   int64_t t = kTileElems;
-  while (t > kMinTileElems && total < (double)t * (double)kTileCount) t >>= 1;
+  while (t > kMinTileElems && total < (double)t * count) t >>= 1;
   return t;
 }
 
 // What trades workspace for time: elements per row band and per update tile, and (`compact` unset)
 // padded column partials and flat exact-moment tensors
 struct PlanSize {
-  int64_t band_elems, tile_elems;
+  int64_t band_elems, tile_elems, wide_tile_elems;
   bool compact;
 };
 static int plan_sized(const skew_tensor_desc *d, int n, const PlanSize &size, Plan *out) {
-  const int64_t band_elems = size.band_elems, tile_elems = size.tile_elems;
+  const int64_t band_elems = size.band_elems;
   const bool compact = size.compact;
   Plan p;
   // descriptors -> sub-tensors: a stacked (ndim 3) descriptor of E matrices becomes E
@@ -237,6 +248,11 @@ static int plan_sized(const skew_tensor_desc *d, int n, const PlanSize &size, Pl
       }
     }
 
+    // the row-band pass (see rowband_shape)
+    const RowBandShape rbs = rowband_shape(tp.n, tp.m, tp.ld, tp.momentum != 0, compact);
+    const int64_t zcw = rbs.zcw, nseg = rbs.nseg, rpi = rbs.rpi, zrb = rbs.zrb;
+    tp.zpath = (tp.kind == kFactored && rpi > 0 && zrb >= 1) ? 1 : 0;
+
     // tile grid: tr rows x (512 * cw) columns, about kTileElems elements; cw in {1, 2, 4}
     // so that the four waves of a work-group map onto (chunk, row) pairs statically. The widest
     // strip that fits; a narrower one when the last strip would leave more than 1/16 of the
@@ -251,6 +267,7 @@ static int plan_sized(const skew_tensor_desc *d, int n, const PlanSize &size, Pl
     const int64_t tc = (int64_t)kChunk * tp.cw;
     // (exact-moment tensors take a quarter of that: their element-by-element path is the
     // slowest per element, and their few tiles would otherwise finish last)
+    const int64_t tile_elems = tp.kind == kFactored && !tp.zpath ? size.wide_tile_elems : size.tile_elems;
     tp.tr = std::max<int64_t>(1, tile_elems / tc / (tp.kind == kExact ? 4 : 1));
     const int64_t ntc = ceil_div(tp.m, tc), ntr = ceil_div(tp.n, tp.tr);
     if (ntc * ntr > INT32_MAX / 2 / kSub) return SKEW_EINVAL;   // tile * kSub + part fits an int32
@@ -266,10 +283,6 @@ static int plan_sized(const skew_tensor_desc *d, int n, const PlanSize &size, Pl
     // Column partials of successive bands lie 256 bytes off a multiple of 4 KiB: the fold reads a few
     // columns of every band, which at a power of two distance all fall on the same memory channels
     tp.ldp = tp.m + (!compact && tp.m % 512 == 0 ? 32 : 0);
-    // the row-band pass (see rowband_shape)
-    const RowBandShape rbs = rowband_shape(tp.n, tp.m, tp.ld, tp.momentum != 0, compact);
-    const int64_t zcw = rbs.zcw, nseg = rbs.nseg, rpi = rbs.rpi, zrb = rbs.zrb;
-    tp.zpath = (tp.kind == kFactored && rpi > 0 && zrb >= 1) ? 1 : 0;
     if (tp.zpath) {
       tp.zcw = (int32_t)zcw;
       tp.nseg = (int32_t)nseg;
@@ -367,7 +380,7 @@ static int plan_sized(const skew_tensor_desc *d, int n, const PlanSize &size, Pl
 
 int plan_build(const skew_tensor_desc *d, int n, Plan *out) {
   if (n < 0 || (n > 0 && d == nullptr) || out == nullptr) return SKEW_EINVAL;
-  return plan_sized(d, n, {choose_band_elems(d, n), choose_tile_elems(d, n), false}, out);
+  return plan_sized(d, n, {choose_band_elems(d, n), choose_tile_elems(d, n, false), choose_tile_elems(d, n, true), false}, out);
 }
 
 // A row band costs two rows of column partials, so most of a large table's workspace shrinks as the
@@ -379,7 +392,7 @@ int plan_build_within(const skew_tensor_desc *d, int n, size_t limit, Plan *out)
   constexpr int64_t kLast = (int64_t)kZMaxBandRows * kZWaves * kZMaxSeg * kChunk;
   for (bool last = false; rc == SKEW_OK && out->ws_bytes > limit && !last; band += band / 2) {
     last = band >= kLast;
-    rc = plan_sized(d, n, {last ? kLast * 4 : band, kTileElems, true}, out);   // (4 > kMomCost)
+    rc = plan_sized(d, n, {last ? kLast * 4 : band, kTileElems, kTileElems, true}, out);   // (4 > kMomCost)
   }
   return rc;
 }

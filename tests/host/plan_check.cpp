@@ -502,6 +502,25 @@ int main() {
     CHECK(plan_build_within(&d, 1, static_workspace_bytes(), &p) == SKEW_OK && p.ws_bytes <= static_workspace_bytes(),
           "7.5e6 x 4: %zu bytes of workspace", p.ws_bytes);
   }
+  // the tiled passes' tiles stay large enough for their column partials (a row of doubles per tile) to be
+  // a fraction of the gradient, alone and beside smaller matrices; few rows take smaller tiles
+  for (int64_t n : {838, 1677, 6710})
+    for (int more : {0, 20}) {
+      std::vector<skew_tensor_desc> d = {mk(1, 2, n, 20000, 20000, id)};
+      for (int k = 0; k < more; k++) d.push_back(mk(1, 2, 64, 128, 128, id + 1 + k));
+      Plan p;
+      CHECK(plan_build(d.data(), (int)d.size(), &p) == SKEW_OK && p.t[0].tr >= 32, "wide, %lld rows: %lld per tile",
+            (long long)n, (long long)p.t[0].tr);
+      CHECK(p.ws_bytes < (size_t)n * 20000 * 2 / 3, "wide, %lld rows: %zu bytes of workspace", (long long)n, p.ws_bytes);
+      check_plan("wide " + std::to_string(n), d);
+    }
+  for (int big : {0, 20}) {
+    std::vector<skew_tensor_desc> d = {mk(0, 2, 100, 20000, 20000, id)};
+    for (int k = 0; k < big; k++) d.push_back(mk(1, 2, 1024, 1024, 1024, id + 1 + k));
+    Plan p;
+    CHECK(plan_build(d.data(), (int)d.size(), &p) == SKEW_OK && p.t[0].tr == 4, "wide, 100 rows: %lld per tile",
+          (long long)p.t[0].tr);
+  }
   // row strides around the largest span of a block of rows, for every number of chunks per wave,
   // with and without momentum
   for (int tier : {0, 1})
