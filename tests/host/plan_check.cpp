@@ -504,7 +504,7 @@ int main() {
   }
   // the tiled passes' tiles stay large enough for their column partials (a row of doubles per tile) to be
   // a fraction of the gradient, alone and beside smaller matrices; few rows take smaller tiles
-  for (int64_t n : {838, 1677, 6710})
+  for (int64_t n : {839, 1677, 6710})
     for (int more : {0, 20}) {
       std::vector<skew_tensor_desc> d = {mk(1, 2, n, 20000, 20000, id)};
       for (int k = 0; k < more; k++) d.push_back(mk(1, 2, 64, 128, 128, id + 1 + k));
