@@ -223,9 +223,10 @@ static int plan_sized(const skew_tensor_desc *d, int n, const PlanSize &size, Pl
     if (tp.fp32 && tp.kind != kExact) return SKEW_EINVAL;   // float32 masters: exact-moment tensors
     if (tp.empty) continue;
     // exact-moment tensors are elementwise: where the rows follow each other they are taken as rows
-    // of 2048 elements, or as one row (a 2048 x 128 router would leave three lanes of four idle)
-    if (tp.kind == kExact && tp.ld == tp.m && !compact) {
-      constexpr int64_t kRow = kChunk * kMaxCw;
+    // of 2048 elements, or as one row (a 2048 x 128 router would leave three lanes of four idle) while
+    // its tiles of one row of 2048 are not too many for a launch (2^32 threads: 2^34 elements)
+    constexpr int64_t kRow = kChunk * kMaxCw, kMaxOneRow = int64_t(1) << 31;
+    if (tp.kind == kExact && tp.ld == tp.m && !compact && (N % kRow == 0 || N <= kMaxOneRow)) {
       tp.n = N % kRow == 0 ? N / kRow : 1;
       tp.m = tp.ld = N / tp.n;
     }

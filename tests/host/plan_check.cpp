@@ -521,6 +521,13 @@ int main() {
     CHECK(plan_build(d.data(), (int)d.size(), &p) == SKEW_OK && p.t[0].tr == 4, "wide, 100 rows: %lld per tile",
           (long long)p.t[0].tr);
   }
+  // a router of more than 2^34 elements, no multiple of 2048 of them: each launch below 2^32 threads
+  {
+    const skew_tensor_desc d = mk(2, 2, (int64_t(1) << 22) + 1, 4099, 4099, id);
+    Plan p;
+    CHECK(plan_build(&d, 1, &p) == SKEW_OK && std::max(p.p2.size(), p.p3.size()) * kThreads < (size_t(1) << 32),
+          "%zu and %zu work-groups", p.p2.size(), p.p3.size());
+  }
   // row strides around the largest span of a block of rows, for every number of chunks per wave,
   // with and without momentum
   for (int tier : {0, 1})
