@@ -14,11 +14,10 @@
 using namespace skew;
 
 namespace {
-constexpr int kLaunches = 10;
-const char *const kLaunchNames[kLaunches] = {"p1z_rowband_stats", "p1z_rowband_stats_momentum", "p1_rowcol_sumsq",
-                                             "fold_rc_ema", "p2_update_sumsq", "clip_factor",
-                                             "recheck_update_sumsq", "clip_factor_recheck", "p3_apply_dither",
-                                             "grad_norm"};
+constexpr int kLaunches = 9;
+const char *const kLaunchNames[kLaunches] = {"p1z_rowband_stats", "p1_rowcol_sumsq", "fold_rc_ema",
+                                             "p2_update_sumsq", "clip_factor", "recheck_update_sumsq",
+                                             "clip_factor_recheck", "p3_apply_dither", "grad_norm"};
 }  // namespace
 
 // a contiguous list of work items in the workspace
@@ -32,11 +31,10 @@ struct skew_ctx {
   char *ws = nullptr;   // workspace base (device)
   DevTensor *d_table = nullptr;
   RecheckLists *lists = nullptr;
-  ItemList p1, fold, p2, p3, clip, clip_slices, fold_rows;
+  ItemList p1, z, fold, p2, p3, clip, clip_slices, fold_rows;
   int ragged = 0;            // a factored tensor has unaligned rows
   float *gscale = nullptr;   // device: the gradient-norm mode's scale
   double *gsq = nullptr;     // device: per-tensor sums of g^2
-  ItemList z[kZVariants];    // row-band pass items, one list per kernel variant
   int static_dev = -1;       // >= 0: the workspace is the library's static one on this device
   // diagnostics: per recorded step, (launch kind, start event, end event) of every launch
   struct Timed {
@@ -184,7 +182,6 @@ int init_ctx(skew_ctx **ctx, Plan &p, skew_tensor_desc *d, int n, void *state, s
     x.ssum = reinterpret_cast<double *>(ws + tp.off_ssum);
     x.qsum = reinterpret_cast<double *>(ws + tp.off_qsum);
     x.sc = reinterpret_cast<TensorScalars *>(ws + tp.off_sc);
-    x.zeros = reinterpret_cast<const uint16_t *>(ws + p.off_zero);
     auto wsp = [&](size_t off) { return off == SIZE_MAX ? nullptr : static_cast<void *>(ws + off); };
     x.rowpart = static_cast<double *>(wsp(tp.off_rowpart));
     x.colpart = static_cast<double *>(wsp(tp.off_colpart));
@@ -198,8 +195,6 @@ int init_ctx(skew_ctx **ctx, Plan &p, skew_tensor_desc *d, int n, void *state, s
     x.zcw = tp.zcw;
     x.zrpi = tp.zrpi;
     x.nzb = tp.nzb;
-    x.zrb = tp.zrb;
-    x.zrows = tp.zrows;
     x.n = tp.n;
     x.m = tp.m;
     x.ld = tp.ld;
@@ -216,13 +211,6 @@ int init_ctx(skew_ctx **ctx, Plan &p, skew_tensor_desc *d, int n, void *state, s
     x.vec = !tp.fp32 && aligned16(x.w) && aligned16(x.g) && (tp.ld % 8 == 0) && (tp.m % 8 == 0);
     x.tensor_id = dd.tensor_id;
   }
-  // row-band pass items by variant (16-byte aligned rows are known only here, from the pointers)
-  std::vector<Item> zv[kZVariants];
-  for (const Item &it : p.z) {
-    const DevTensor &x = table[it.tensor];
-    const int lg = x.nseg == 1 ? 0 : (x.nseg == 2 ? 1 : (x.nseg == 4 ? 2 : 3));
-    zv[lg * 4 + (x.vec ? 0 : 2) + (x.momentum ? 1 : 0)].push_back(it);
-  }
   skew_ctx *c = new (std::nothrow) skew_ctx;
   if (c == nullptr) return SKEW_ENOMEM;
   c->d_table = reinterpret_cast<DevTensor *>(ws + p.off_table);
@@ -237,9 +225,7 @@ int init_ctx(skew_ctx **ctx, Plan &p, skew_tensor_desc *d, int n, void *state, s
     items.insert(items.end(), v.begin(), v.end());
   };
   add(c->p1, p.p1);
-  // (the variants share a launch: the momentum ones, whose bands take longest, go first)
-  for (int mom = 1; mom >= 0; mom--)
-    for (int v = mom; v < kZVariants; v += 2) add(c->z[v], zv[v]);
+  add(c->z, p.z);
   add(c->fold, p.fold);
   add(c->p2, p.p2);
   add(c->p3, p.p3);
@@ -349,57 +335,41 @@ int skew_step(skew_ctx *ctx, const skew_hparams *hp, void *stream) {
   const DevTensor *T = ctx->d_table;
   const int nt = (int)p.t.size();
   RecheckLists *L = ctx->lists;
-  k.zlast = -1;
-  k.zcount = 0;
-  k.zitems = nullptr;
-  for (int v = 0; v < kZVariants; v++) {
-    if (ctx->z[v].n == 0) continue;
-    if (k.zitems == nullptr || ctx->z[v].d < k.zitems) k.zitems = ctx->z[v].d;
-    k.zcount += (int32_t)ctx->z[v].n;
-    k.zlast = v;
-  }
   auto rowband = [&](int mode) {
-    for (int v = 0; v < kZVariants; v++) {
-      if (ctx->z[v].n == 0) continue;
-      auto launch = [&] { return launch_p1z(T, ctx->z[v].d, ctx->z[v].n, k, v, mode, s); };
-      if (v == k.zlast)
-        run(0, launch);
-      else if (e == 0)
-        e = launch();   // launched with the last variant's
-    }
+    if (ctx->z.n > 0) run(0, [&] { return launch_p1z(T, ctx->z.d, ctx->z.n, k, mode, s); });
   };
   if (!k.gclip) {
     // statistics: the row-band pass, pass 1 of wide factored tensors, the fold
     rowband(0);
-    if (ctx->p1.n > 0) run(2, [&] { return launch_p1(T, ctx->p1.d, ctx->p1.n, s); });
-    if (ctx->fold.n > 0) run(3, [&] { return launch_fold(T, ctx->fold.d, ctx->fold.n, k, 0, s); });
+    if (ctx->p1.n > 0) run(1, [&] { return launch_p1(T, ctx->p1.d, ctx->p1.n, s); });
+    if (ctx->fold.n > 0) run(2, [&] { return launch_fold(T, ctx->fold.d, ctx->fold.n, k, 0, s); });
   } else {
     // gradient-norm mode: the scale needs every tensor's sum of g^2 before any statistic,
     // so the row-band pass runs twice: sums, then z with R folded
     rowband(1);
-    if (ctx->p1.n > 0) run(2, [&] { return launch_p1(T, ctx->p1.d, ctx->p1.n, s); });
-    if (ctx->p2.n > 0) run(9, [&] { return launch_gsq(T, ctx->p2.d, ctx->p2.n, s); });
-    run(9, [&] { return launch_gnorm(T, nt, k, s); });
-    if (ctx->fold_rows.n > 0) run(3, [&] { return launch_fold(T, ctx->fold_rows.d, ctx->fold_rows.n, k, 1, s); });
+    if (ctx->p1.n > 0) run(1, [&] { return launch_p1(T, ctx->p1.d, ctx->p1.n, s); });
+    if (ctx->p2.n > 0) run(8, [&] { return launch_gsq(T, ctx->p2.d, ctx->p2.n, s); });
+    run(8, [&] { return launch_gnorm(T, nt, k, s); });
+    if (ctx->fold_rows.n > 0) run(2, [&] { return launch_fold(T, ctx->fold_rows.d, ctx->fold_rows.n, k, 1, s); });
     rowband(2);
-    if (ctx->fold.n > 0) run(3, [&] { return launch_fold(T, ctx->fold.d, ctx->fold.n, k, 2, s); });
+    if (ctx->fold.n > 0) run(2, [&] { return launch_fold(T, ctx->fold.d, ctx->fold.n, k, 2, s); });
   }
   // update sums of wide and exact tensors, the clip stage and its re-checks (launches with
   // empty lists exit at once), then the update
-  if (ctx->p2.n > 0) run(4, [&] { return launch_p2(T, ctx->p2.d, ctx->p2.n, k, s); });
+  if (ctx->p2.n > 0) run(3, [&] { return launch_p2(T, ctx->p2.d, ctx->p2.n, k, s); });
   if (ctx->clip.n > 0) {
     if (ctx->clip_slices.n > 0)
-      run(5, [&] { return launch_clip_slices(T, ctx->clip_slices.d, ctx->clip_slices.n, k, s); });
-    run(5, [&] { return launch_clip(T, ctx->clip.d, ctx->clip.n, k, L, nt, s); });
+      run(4, [&] { return launch_clip_slices(T, ctx->clip_slices.d, ctx->clip_slices.n, k, s); });
+    run(4, [&] { return launch_clip(T, ctx->clip.d, ctx->clip.n, k, L, nt, s); });
     // (only factored tensors are ever listed: a group of routers and norm vectors alone has none)
     if (ctx->fold.n > 0) {
-      run(6, [&] { return launch_recheck(T, L, nt, k, 1, s); });
-      run(7, [&] { return launch_clip_recheck(T, L, nt, k, 1, s); });
-      run(6, [&] { return launch_recheck(T, L, nt, k, 2, s); });
-      run(7, [&] { return launch_clip_recheck(T, L, nt, k, 2, s); });
+      run(5, [&] { return launch_recheck(T, L, nt, k, 1, s); });
+      run(6, [&] { return launch_clip_recheck(T, L, nt, k, 1, s); });
+      run(5, [&] { return launch_recheck(T, L, nt, k, 2, s); });
+      run(6, [&] { return launch_clip_recheck(T, L, nt, k, 2, s); });
     }
   }
-  if (ctx->p3.n > 0) run(8, [&] { return launch_p3(T, ctx->p3.d, ctx->p3.n, k, L, s); });
+  if (ctx->p3.n > 0) run(7, [&] { return launch_p3(T, ctx->p3.d, ctx->p3.n, k, L, s); });
   return e == 0 ? SKEW_OK : SKEW_EHIP;
 }
 
@@ -410,8 +380,7 @@ int skew_timing_enable(skew_ctx *ctx, int max_steps) {
   ctx->timed.clear();
   ctx->ev_steps = ctx->ev_used = 0;
   ctx->ev_next = 0;
-  // at most one launch of each kind per step (the row-band variants share two kinds)
-  const size_t per_step = (size_t)(kLaunches + 2 * kZVariants + 8) * 2;
+  constexpr size_t per_step = 2 * 15;   // a step has at most 15 launches (the gradient-norm mode)
   const size_t n = (size_t)max_steps * per_step;
   ctx->ev_pool.reserve(n);
   for (size_t i = 0; i < n; i++) {

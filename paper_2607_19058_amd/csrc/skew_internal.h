@@ -28,10 +28,7 @@ constexpr int kZMinCols = 8;             // the lane at a row's end loads the ro
                                          // rows: one column per lane)
 constexpr int64_t kZBandElems = 1 << 22; // elements per row band, at most: 8 MiB of bf16 gradient
 constexpr int64_t kZMinBandElems = 1 << 14;   // ... and at least (unless one block of rows is longer)
-constexpr int kZVariants = 16;           // item lists: lg(nseg) * 4 + (unaligned rows ? 2 : 0) + momentum,
-                                         // lg = 0, 1, 2, 3 for nseg = 1, 2, 4, 3 (3: no momentum)
-constexpr int kZLdsBytes = 96 * 1024;    // bytes of one staged block of rows, at most
-constexpr int kZMaxBlockRows = 64;       // rows staged per block, at most
+constexpr int kZMaxBlockRows = 64;       // rows per block, at most
 constexpr int kZMaxBandRows = 2048;      // rows per band, at most (their R are staged in LDS)
 
 // Rows per group and block of the row-band pass in each of its modes (0: the whole pass; 1: the sums
@@ -134,7 +131,6 @@ struct DevTensor {
   double *ssum;           // [ntr*ntc]  per-tile sums of squares of the unclipped update
   double *qsum;           // [ntr*ntc]  per-tile sums of U_hat^4 over the approximated elements
   TensorScalars *sc;      // this step's clip factor and reconstruction clamp
-  const uint16_t *zeros;  // 256 zero bytes (never written): the source of padding loads
   int64_t n, m, ld;       // rows, columns, row stride (elements)
   int64_t ldp;            // row stride of colpart and zpart (elements)
   int64_t tr;             // rows per tile
@@ -150,14 +146,12 @@ struct DevTensor {
   int32_t zrpi;           // row-band pass: row groups per work-group (rows side by side); a group
                           // is wpr = ceil(zcw / nseg) waves, wave w of it takes chunks w, w + wpr
   int32_t nzb;            // row-band pass: row bands
-  int32_t zrb;            // row-band pass: rows per group and block
   int32_t decay;          // the decoupled weight decay applies (every tier but the router)
-  int64_t zrows;
   int64_t idx0;           // element index of this (sub-)tensor's first element in the caller's
                           // tensor: a stacked tensor's slices are sub-tensors (dither index)
   int32_t grp0, ngrp;     // the sub-tensors that share one clip factor: [grp0, grp0 + ngrp)
   int32_t fp32;           // w and g are float32 (float32 masters: no dither, no cast)
-  int32_t pad3;          // row-band pass: rows per band
+  int32_t pad;
   uint64_t tensor_id;
 };
 
@@ -178,9 +172,6 @@ struct StepConsts {
   int32_t ragged;           // a factored tensor of the table has unaligned rows (DevTensor::vec == 0)
   float *gscale;            // device: the factor c (written by the norm stage)
   double *gsq;              // device [ntensors]: each tensor's sum of g^2 (norm stage)
-  const Item *zitems;       // device: the row-band items of all variants, and their count
-  int32_t zcount;
-  int32_t zlast;            // the last variant with items: its call launches all of them
 };
 
 // Host-side plan of a descriptor table.
@@ -208,7 +199,6 @@ struct Plan {
   std::vector<TensorPlan> t;                  // sub-tensors (the device table's entries)
   std::vector<int32_t> desc_sub0, desc_nsub;  // per descriptor: its first sub-tensor and their count
   size_t off_lists = 0;                       // workspace offset of the RecheckLists
-  size_t off_zero = 0;                        // workspace offset of 256 zero bytes
   size_t off_gscale = 0;                      // workspace offset of the gradient scale (float)
   size_t off_gsq = 0;                         // workspace offset of the per-tensor sums of g^2
   std::vector<Item> p1, fold, p2, p3, clip;   // clip: one item per non-empty tensor
@@ -216,7 +206,7 @@ struct Plan {
   // fold items of the gradient-norm mode's first fold: rows and columns of every factored
   // tensor (row-band tensors: rows [0, ceil(n / kFold)), then columns)
   std::vector<Item> fold_rows;
-  std::vector<Item> z;                        // row-band pass items (split by kernel variant at init)
+  std::vector<Item> z;                        // row-band pass items (bands with momentum first)
   size_t state_bytes = 0;
   size_t ws_bytes = 0;
   size_t off_table = 0, off_items = 0;   // workspace offsets of the device table and item lists
@@ -238,11 +228,9 @@ constexpr size_t static_workspace_bytes() { return (size_t)SKEW_STATIC_WORKSPACE
 
 // Kernel launchers (skew_kernels.hip). Return a hipError_t value.
 int launch_p1(const DevTensor *T, const Item *items, int64_t count, void *stream);
-// row-band pass, the items of variant lg(nseg) * 4 + (unaligned rows ? 2 : 0) + (momentum ? 1 : 0)
-// mode 0: the whole pass; 1: sums of g^2 only (row sums to ainv); 2: z, floored sum and
+// row-band pass, mode 0: the whole pass; 1: sums of g^2 only (row sums to ainv); 2: z, floored sum and
 // band statistics from the R already folded (the gradient-norm mode's two passes)
-int launch_p1z(const DevTensor *T, const Item *items, int64_t count, const StepConsts &k, int variant, int mode,
-               void *stream);
+int launch_p1z(const DevTensor *T, const Item *items, int64_t count, const StepConsts &k, int mode, void *stream);
 
 // fold phase 0: the step without gradient-norm scaling; 1: its first fold (R and C of every
 // factored tensor from the sums of g^2, scaled by c^2); 2: its second fold (row-band tensors:

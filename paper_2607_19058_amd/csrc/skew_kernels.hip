@@ -2459,14 +2459,11 @@ int launch_p1(const DevTensor *T, const Item *items, int64_t count, void *stream
   hipLaunchKernelGGL(p1_kernel, dim3((uint32_t)count), dim3(kThreads), 0, (hipStream_t)stream, T, items);
   return (int)hipGetLastError();
 }
-// The items of all variants lie one after another in the device's list (k.zitems): the call of
-// the step's last variant launches them together.
-int launch_p1z(const DevTensor *T, const Item *, int64_t count, const StepConsts &k, int variant, int mode,
-               void *stream) {
-  if (count <= 0 || variant != k.zlast) return hipSuccess;
-  const dim3 grid((uint32_t)k.zcount), block(kZThreads);
+int launch_p1z(const DevTensor *T, const Item *items, int64_t count, const StepConsts &k, int mode, void *stream) {
+  if (count <= 0) return hipSuccess;
+  const dim3 grid((uint32_t)count), block(kZThreads);
   auto *kern = mode == 0 ? p1z_kernel<0> : (mode == 1 ? p1z_kernel<1> : p1z_kernel<2>);
-  hipLaunchKernelGGL(kern, grid, block, 0, (hipStream_t)stream, T, k.zitems, k);
+  hipLaunchKernelGGL(kern, grid, block, 0, (hipStream_t)stream, T, items, k);
   return (int)hipGetLastError();
 }
 int launch_fold(const DevTensor *T, const Item *items, int64_t count, const StepConsts &k, int phase, void *stream) {

@@ -5,6 +5,7 @@
 #include <algorithm>
 #include <climits>
 #include <cmath>
+#include <utility>
 
 #include "skew_internal.h"
 
@@ -348,9 +349,15 @@ static int plan_sized(const skew_tensor_desc *d, int n, const PlanSize &size, Pl
     };
     order(p.p3);
     order(p.p2);
+    // row bands: those with momentum, which take longest, first; each of the kernel's bodies together
+    auto body = [&](const Item &it) {
+      const TensorPlan &tp = p.t[(size_t)it.tensor];
+      return std::make_pair(!tp.momentum, tp.nseg == 3 ? 5 : tp.nseg);
+    };
+    std::stable_sort(p.z.begin(), p.z.end(), [&](const Item &a, const Item &b) { return body(a) < body(b); });
   }
   p.state_bytes = st;
-  // workspace: [device tensor table][items p1|z (by variant)|fold|p2|p3|clip][re-check lists][partials]
+  // workspace: [device tensor table][items p1|z|fold|p2|p3|clip][re-check lists][partials]
   size_t ws = 0;
   p.off_table = ws; ws = align_up(ws + sizeof(DevTensor) * (size_t)std::max(nt, 1));
   // the item lists as the device keeps them
@@ -359,8 +366,6 @@ static int plan_sized(const skew_tensor_desc *d, int n, const PlanSize &size, Pl
                                      p.clip.size() + p.clip_slices.size() + p.fold_rows.size() + 1));
   p.off_lists = ws;
   ws = align_up(ws + sizeof(RecheckLists) + sizeof(int32_t) * 2 * (size_t)std::max(nt, 1));
-  p.off_zero = ws;   // zero-filled with the workspace at set-up and never written
-  ws = align_up(ws + 256);
   p.off_gscale = ws;
   ws = align_up(ws + sizeof(float));
   p.off_gsq = ws;

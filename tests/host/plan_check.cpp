@@ -9,8 +9,8 @@
 //     (p3), and in exactly one row band (row-band pass) or pass-1 tile (wide tensors);
 //     a tile is a set of rows times a set of columns, so this covers every element, also
 //     for tensors of more than 2^31 elements (64-bit tiling, Sec. 3 "Memory model" footnote);
-//   * the row-band geometry fits the kernel: a block fits one LDS staging buffer, a band
-//     holds whole blocks, every 512-column chunk of a row has exactly one wave;
+//   * the row-band geometry fits the kernel in each of its modes: a block's offsets and rows stay in
+//     range, a band holds whole blocks, every 512-column chunk of a row has exactly one wave;
 //   * every state and workspace region is 256-byte aligned, lies inside its buffer and
 //     overlaps no other region;
 //   * the set-up and a step over the table launch exactly the planned items, each naming a
@@ -102,14 +102,10 @@ int launch_p1(const DevTensor *T, const Item *items, int64_t count, void *) {
   check_items("p1", T, items, count);
   return 0;
 }
-int launch_p1z(const DevTensor *T, const Item *items, int64_t count, const StepConsts &, int variant, int mode,
-               void *) {
+int launch_p1z(const DevTensor *T, const Item *items, int64_t count, const StepConsts &, int mode, void *) {
   check_items(mode == 0 ? "z0" : (mode == 1 ? "z1" : "z2"), T, items, count);
-  for (int64_t q = 0; q < count; q++) {
-    const DevTensor &t = T[items[q].tensor];
-    const int lg = t.nseg == 1 ? 0 : (t.nseg == 2 ? 1 : (t.nseg == 4 ? 2 : 3));
-    CHECK(variant == lg * 4 + (t.vec ? 0 : 2) + (t.momentum ? 1 : 0), "row-band variant %d", variant);
-  }
+  for (int64_t q = 1; q < count; q++)
+    CHECK(T[items[q - 1].tensor].momentum >= T[items[q].tensor].momentum, "bands with momentum go first");
   return 0;
 }
 int launch_fold(const DevTensor *T, const Item *items, int64_t count, const StepConsts &, int phase, void *) {
@@ -250,8 +246,6 @@ static void check_one_plan(const std::string &name, const Plan &p) {
       CHECK(tp.zcw == cdiv(tp.m, kChunk) && wpr * tp.zrpi <= kZWaves && tp.zcw <= wpr * tp.nseg &&
                 tp.nseg <= kZMaxSeg,
             "%s: chunk layout zcw %d nseg %d rpi %d", tn.c_str(), tp.zcw, tp.nseg, tp.zrpi);
-      const int64_t block_bytes = blk * tp.zcw * 1024 * (tp.momentum ? 3 : 1);
-      CHECK(block_bytes <= kZLdsBytes, "%s: block of %lld bytes", tn.c_str(), (long long)block_bytes);
       CHECK(tp.nseg != 3 || (!tp.momentum && tp.zrb <= 2), "%s: three chunks per wave without momentum, 2 rows",
             tn.c_str());
       for (int b = 0; b < tp.nzb; b++) {
@@ -267,8 +261,8 @@ static void check_one_plan(const std::string &name, const Plan &p) {
         n_fold++;
       }
       CHECK(tp.nfc == cdiv(tp.m, kFold), "%s: fold chunks", tn.c_str());
-      ws.push_back({tp.off_colpart, tp.off_colpart + (size_t)tp.nzb * tp.m * 8, tn + ".colpart"});
-      ws.push_back({tp.off_zpart, tp.off_zpart + (size_t)tp.nzb * tp.m * 8, tn + ".zpart"});
+      ws.push_back({tp.off_colpart, tp.off_colpart + (size_t)tp.nzb * tp.ldp * 8, tn + ".colpart"});
+      ws.push_back({tp.off_zpart, tp.off_zpart + (size_t)tp.nzb * tp.ldp * 8, tn + ".zpart"});
       ws.push_back({tp.off_ainv, tp.off_ainv + (size_t)tp.n * 8, tn + ".ainv"});
       ws.push_back({tp.off_bst, tp.off_bst + (size_t)tp.nzb * sizeof(BandStats), tn + ".bst"});
       ws.push_back({tp.off_cst, tp.off_cst + (size_t)tp.nfc * sizeof(ColStats), tn + ".cst"});
@@ -281,7 +275,7 @@ static void check_one_plan(const std::string &name, const Plan &p) {
       CHECK(tp.nfr == cdiv(tp.n, kFold) && tp.nfc == cdiv(tp.m, kFold), "%s: fold chunks", tn.c_str());
       for (int c = 0; c < tp.nfr + tp.nfc; c++) n_fold += fold.count({i, c});
       ws.push_back({tp.off_rowpart, tp.off_rowpart + (size_t)tp.ntc * tp.n * 8, tn + ".rowpart"});
-      ws.push_back({tp.off_colpart, tp.off_colpart + (size_t)tp.ntr * tp.m * 8, tn + ".colpart"});
+      ws.push_back({tp.off_colpart, tp.off_colpart + (size_t)tp.ntr * tp.ldp * 8, tn + ".colpart"});
       ws.push_back({tp.off_ainv, tp.off_ainv + (size_t)tp.n * 8, tn + ".ainv"});
       ws.push_back({tp.off_rsum, tp.off_rsum + (size_t)tp.nfr * 8, tn + ".rsum"});
       ws.push_back({tp.off_cst, tp.off_cst + (size_t)(tp.nfr + tp.nfc) * sizeof(ColStats), tn + ".cst"});
@@ -300,7 +294,6 @@ static void check_one_plan(const std::string &name, const Plan &p) {
   ws.push_back({p.off_table, p.off_table + sizeof(DevTensor) * nt1, "table"});
   ws.push_back({p.off_items, p.off_lists, "items"});
   ws.push_back({p.off_lists, p.off_lists + sizeof(RecheckLists) + 8 * nt1, "lists"});
-  ws.push_back({p.off_zero, p.off_zero + 256, "zero"});
   ws.push_back({p.off_gscale, p.off_gscale + 4, "gscale"});
   ws.push_back({p.off_gsq, p.off_gsq + 8 * nt1, "gsq"});
   check_regions(ws, p.ws_bytes, (name + " workspace").c_str());
@@ -357,8 +350,7 @@ static void check_init_and_step(const std::string &name, std::vector<skew_tensor
     CHECK(in_state(t.M, (size_t)tp.N) && in_state(t.V, (size_t)tp.N) && in_state(t.R, (size_t)tp.n) &&
               in_state(t.C, (size_t)tp.m),
           "%s[%d]: state pointers", name.c_str(), i);
-    CHECK(in_ws(t.ssum, (size_t)t.ntr * t.ntc * kSub * 8) && in_ws(t.sc, sizeof(TensorScalars)) &&
-              in_ws(t.zeros, 256),
+    CHECK(in_ws(t.ssum, (size_t)t.ntr * t.ntc * kSub * 8) && in_ws(t.sc, sizeof(TensorScalars)),
           "%s[%d]: workspace pointers", name.c_str(), i);
     CHECK(t.n == tp.n && t.m == tp.m && t.ld == tp.ld && t.zpath == tp.zpath && t.nzb == tp.nzb,
           "%s[%d]: table fields", name.c_str(), i);
