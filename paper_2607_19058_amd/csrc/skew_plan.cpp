@@ -74,7 +74,8 @@ static int64_t band_rows(const RowBandShape &r, int64_t m, bool momentum, int64_
 // below 256 MiB or 1/40 of the gradients.
 constexpr double kCus = 256.0, kElemUs = 1.07e-4, kBandUs = 3.0, kFoldBytesPerUs = 2.0e6,
                  kFoldMaxBytes = 268435456.0;
-static int64_t choose_band_elems(const skew_tensor_desc *d, int n) {
+static int64_t choose_band_elems(const skew_tensor_desc *d, int n, int64_t most = kZBandElems,
+                                 double max_bytes = HUGE_VAL) {
   struct Shape {
     RowBandShape r;
     int64_t n, m;
@@ -104,10 +105,10 @@ static int64_t choose_band_elems(const skew_tensor_desc *d, int n) {
     }
     if (!found) shapes.push_back({r, x.rows, x.cols, mom, E});
   }
-  int64_t best = kZBandElems;
+  int64_t best = most;
   double best_us = HUGE_VAL;
   for (int step = 0;; step++) {
-    const int64_t b = (int64_t)((double)kZBandElems * std::exp2(-step / 8.0));
+    const int64_t b = (int64_t)((double)most * std::exp2(-step / 8.0));
     if (b < kZMinBandElems) break;
     double bands = 0.0, bytes = 0.0;
     for (const Shape &s : shapes) {
@@ -115,7 +116,8 @@ static int64_t choose_band_elems(const skew_tensor_desc *d, int n) {
       bands += nb;
       bytes += nb * 16.0 * (double)s.m;
     }
-    if (bands <= 0.0 || (step > 0 && bytes > std::max(kFoldMaxBytes, grad_bytes / 40.0))) break;
+    if (bands <= 0.0 || (step > 0 && bytes > std::min(max_bytes, std::max(kFoldMaxBytes, grad_bytes / 40.0))))
+      break;
     const double us = std::ceil(bands / kCus) * (cost / bands + kBandUs) + bytes / kFoldBytesPerUs;
     if (us < best_us) {
       best_us = us;
@@ -152,11 +154,12 @@ static int64_t choose_tile_elems(const skew_tensor_desc *d, int n, bool wide) {
   return t;
 }
 
-// What trades workspace for time: elements per row band and per update tile, and (`compact` unset)
-// padded column partials and flat exact-moment tensors
+// What trades workspace for time: elements per row band and per tile, and (`compact` unset) padded
+// column partials, flat exact-moment tensors and tiles for short narrow matrices; `least`: nothing else
+// fits
 struct PlanSize {
   int64_t band_elems, tile_elems, wide_tile_elems;
-  bool compact;
+  bool compact, least;
 };
 static int plan_sized(const skew_tensor_desc *d, int n, const PlanSize &size, Plan *out) {
   const int64_t band_elems = size.band_elems;
@@ -250,11 +253,6 @@ static int plan_sized(const skew_tensor_desc *d, int n, const PlanSize &size, Pl
       }
     }
 
-    // the row-band pass (see rowband_shape)
-    const RowBandShape rbs = rowband_shape(tp.n, tp.m, tp.ld, tp.momentum != 0, compact);
-    const int64_t zcw = rbs.zcw, nseg = rbs.nseg, rpi = rbs.rpi, zrb = rbs.zrb;
-    tp.zpath = (tp.kind == kFactored && rpi > 0 && zrb >= 1) ? 1 : 0;
-
     // tile grid: tr rows x (512 * cw) columns, about kTileElems elements; cw in {1, 2, 4}
     // so that the four waves of a work-group map onto (chunk, row) pairs statically. The widest
     // strip that fits; a narrower one when the last strip would leave more than 1/16 of the
@@ -267,6 +265,17 @@ static int plan_sized(const skew_tensor_desc *d, int n, const PlanSize &size, Pl
           if (waste(cw) < waste(tp.cw)) tp.cw = cw;
     }
     const int64_t tc = (int64_t)kChunk * tp.cw;
+    // the row-band pass (see rowband_shape)
+    const RowBandShape rbs = rowband_shape(tp.n, tp.m, tp.ld, tp.momentum != 0, compact);
+    const int64_t zcw = rbs.zcw, nseg = rbs.nseg, rpi = rbs.rpi, zrb = rbs.zrb;
+    tp.zpath = (tp.kind == kFactored && rpi > 0 && zrb >= 1) ? 1 : 0;
+    // (where workspace is shortest: few rows of more than kMaxMomChunks chunks with momentum, whose tiles
+    // keep fewer rows of column partials than the two of each band: half the workspace for 42 x 13259)
+    constexpr int64_t kMaxMomChunks = 21;
+    if (tp.zpath && size.least && tp.momentum && zcw > kMaxMomChunks &&
+        ceil_div(tp.n, std::max<int64_t>(1, size.wide_tile_elems / tc)) <
+            2 * ceil_div(tp.n, band_rows(rbs, tp.m, true, band_elems)))
+      tp.zpath = 0;
     // (exact-moment tensors take a quarter of that: their element-by-element path is the
     // slowest per element, and their few tiles would otherwise finish last)
     const int64_t tile_elems = tp.kind == kFactored && !tp.zpath ? size.wide_tile_elems : size.tile_elems;
@@ -386,19 +395,22 @@ static int plan_sized(const skew_tensor_desc *d, int n, const PlanSize &size, Pl
 
 int plan_build(const skew_tensor_desc *d, int n, Plan *out) {
   if (n < 0 || (n > 0 && d == nullptr) || out == nullptr) return SKEW_EINVAL;
-  return plan_sized(d, n, {choose_band_elems(d, n), choose_tile_elems(d, n, false), choose_tile_elems(d, n, true), false}, out);
+  return plan_sized(d, n, {choose_band_elems(d, n), choose_tile_elems(d, n, false), choose_tile_elems(d, n, true), false, false}, out);
 }
 
-// A row band costs two rows of column partials, so most of a large table's workspace shrinks as the
-// bands grow: the smallest bands that fit are taken (they fill the chip best), up to those of
+// Most of a large table's workspace are the row bands' column partials: the band size is chosen again with
+// fewer bytes for them until the plan fits, up to bands of 4 * kZBandElems elements and at last of
 // kZMaxBandRows rows
 int plan_build_within(const skew_tensor_desc *d, int n, size_t limit, Plan *out) {
   int rc = plan_build(d, n, out);
-  int64_t band = choose_band_elems(d, n);
-  constexpr int64_t kLast = (int64_t)kZMaxBandRows * kZWaves * kZMaxSeg * kChunk;
-  for (bool last = false; rc == SKEW_OK && out->ws_bytes > limit && !last; band += band / 2) {
-    last = band >= kLast;
-    rc = plan_sized(d, n, {last ? kLast * 4 : band, kTileElems, kTileElems, true}, out);   // (4 > kMomCost)
+  double bytes = (double)limit;   // for the column partials
+  for (bool last = false; rc == SKEW_OK && out->ws_bytes > limit && !last;) {
+    constexpr int64_t kMost = 4 * kZBandElems;   // (kMomCost times fewer with momentum)
+    constexpr int64_t kLast = (int64_t)kZMaxBandRows * kZWaves * kZMaxSeg * kChunk * 4;
+    last = bytes <= 0.0;
+    const int64_t band = last ? kLast : choose_band_elems(d, n, kMost, bytes);
+    rc = plan_sized(d, n, {band, kTileElems, kTileElems, true, last}, out);
+    bytes = band >= kMost ? 0.0 : bytes - std::max((double)out->ws_bytes - (double)limit, (double)limit / 16);
   }
   return rc;
 }

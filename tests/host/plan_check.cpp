@@ -478,6 +478,12 @@ int main() {
   // rows of fewer than 8 columns: few of them by tiles, many by row bands (the tiled passes' time grows
   // with the square of the rows), and always by row bands where the workspace is short: 7.5e6 x 4
   // fits the static one
+  {
+    const std::vector<skew_tensor_desc> d = {mk(0, 2, 42, 13259, 13267, id), mk(0, 2, 4096, 11008, 11008, id + 1)};
+    Plan least;
+    plan_build_within(d.data(), 2, 0, &least);
+    CHECK(least.t[0].zpath == 0 && least.t[1].zpath == 1, "long rows with momentum, least workspace");
+  }
   for (int64_t m = 1; m < 8; m++)
     for (int64_t n : {1, 2047, 2048, 2049, 100003}) {
       const std::vector<skew_tensor_desc> d = {mk(1, 2, n, m, m + 1, id), mk(0, 2, n, m, m, id + 1)};
