@@ -1166,6 +1166,7 @@ struct FoldShared {
   double stat[kFoldThreads / 64][8];
   float nb[kFold];
   double rsum[kWaves];
+  int dup[kFoldThreads / 64];
 };
 // The sums of a[p * stride + x0 + c] over p = 0 .. n - 1 (and of b) for the columns x0 + c < xn of
 // a chunk: two columns per thread (16-byte loads), the p split in kFoldParts runs of their own,
@@ -1264,25 +1265,37 @@ __device__ __forceinline__ void chunk_stats(ColStats *out, double *sum_out, floa
 
 // Repeated row factors of a row-band tensor: in rows [chunk kZMaxBandRows, ...), those whose R_i > 0
 // equals R_{i-1}. (A band's blocks of rows lie apart, so the row-band pass cannot tell: its blocks
-// are single rows where a row takes the whole work-group.)
-__device__ __forceinline__ void count_equal_rows(const DevTensor &t, int chunk, FoldShared &f) {
-  const int64_t i0 = (int64_t)chunk * kZMaxBandRows;
-  int n = 0;   // of the wave (uniform)
+// are single rows where a row takes the whole work-group.) A tensor of one such run has it counted
+// by its first column chunk: the loads go out before those of its partials and are waited for after
+// them (work-groups of their own took the fold of 512 slices of 16 x 512 from 6.9 to 10.2 us).
+struct EqualRows {
+  static constexpr int kPer = kZMaxBandRows / kFoldThreads;
+  float a[kPer], b[kPer];
+  __device__ __forceinline__ void load(const DevTensor &t, int chunk) {
 #pragma unroll
-  for (int r = 0; r < kZMaxBandRows; r += kFoldThreads) {
-    const int64_t i = i0 + r + threadIdx.x;
-    const bool in = i > 0 && i < t.n;
-    const float a = ldg(t.R + (in ? i : 0)), b = ldg(t.R + (in ? i - 1 : 0));
-    n += __popcll(__ballot(in && a > 0.f && a == b));
+    for (int q = 0; q < kPer; q++) {
+      const int64_t i0 = (int64_t)chunk * kZMaxBandRows + q * kFoldThreads, i = i0 + threadIdx.x;
+      a[q] = b[q] = 0.f;
+      if (i0 < t.n) {   // (uniform)
+        const bool in = i > 0 && i < t.n;
+        a[q] = ldg(t.R + (in ? i : 0));
+        b[q] = in ? ldg(t.R + (in ? i - 1 : 0)) : -1.f;
+      }
+    }
   }
-  if ((threadIdx.x & 63) == 0) f.stat[threadIdx.x >> 6][0] = (double)n;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double all = 0.0;
-    for (int w = 0; w < kFoldThreads / 64; w++) all += f.stat[w][0];
+  // each wave's share goes to f.dup; a barrier later thread 0 stores their sum
+  __device__ __forceinline__ void count(FoldShared &f) const {
+    int n = 0;   // of the wave (uniform)
+#pragma unroll
+    for (int q = 0; q < kPer; q++) n += __popcll(__ballot(a[q] > 0.f && a[q] == b[q]));
+    if ((threadIdx.x & 63) == 0) f.dup[threadIdx.x >> 6] = n;
+  }
+  static __device__ __forceinline__ void store(const DevTensor &t, int chunk, const FoldShared &f) {
+    int all = 0;
+    for (int w = 0; w < kFoldThreads / 64; w++) all += f.dup[w];
     stg(&t.bst[chunk].rdup, (int32_t)all);
   }
-}
+};
 
 __global__ __launch_bounds__(kFoldThreads) __attribute__((amdgpu_waves_per_eu(8))) void fold_kernel(const DevTensor *__restrict__ TT,
                                                             const Item *__restrict__ items, StepConsts k, int phase) {
@@ -1296,7 +1309,11 @@ __global__ __launch_bounds__(kFoldThreads) __attribute__((amdgpu_waves_per_eu(8)
   const int nrows = t.zpath ? (phase == 1 ? (int)((t.n + kFold - 1) / kFold) : 0) : t.nfr;
   if (phase == 2 && !t.zpath) return;
   if (t.zpath && phase != 1 && it.tile >= t.nfc) {   // (R is final: from the row-band pass or from phase 1)
-    count_equal_rows(t, it.tile - t.nfc, f);
+    EqualRows eq;
+    eq.load(t, it.tile - t.nfc);
+    eq.count(f);
+    __syncthreads();
+    if (threadIdx.x == 0) EqualRows::store(t, it.tile - t.nfc, f);
     return;
   }
   const int c = threadIdx.x & (kFold - 1);   // the row or column of the chunk that an `own` thread ends with
@@ -1331,6 +1348,9 @@ __global__ __launch_bounds__(kFoldThreads) __attribute__((amdgpu_waves_per_eu(8)
     // row-band tensor: C_j (phase 0; phase 2 has it from phase 1), c'_j = C_j / max(mean R,
     // eps) and sum_j z_j / c'_j over the chunk; the first waves add the sums of R while the
     // partials load (fold_sum's barrier covers theirs)
+    const bool count = it.tile == 0 && t.n <= kZMaxBandRows;
+    EqualRows eq;
+    if (count) eq.load(t, 0);
     if (threadIdx.x < kThreads) {
       const double sr = wave_sum_d(sum_r_part(t, k, (int)threadIdx.x));
       if ((threadIdx.x & 63) == 0) f.rsum[threadIdx.x >> 6] = sr;
@@ -1369,6 +1389,7 @@ __global__ __launch_bounds__(kFoldThreads) __attribute__((amdgpu_waves_per_eu(8)
         bad = 1;   // NaN, or a nonzero column whose C underflowed
       }
     }
+    if (count) eq.count(f);
     // repeated column factors: C_j equal to the previous column's (within the chunk)
     if (own) f.nb[c] = Cj;
     __syncthreads();
@@ -1406,6 +1427,7 @@ __global__ __launch_bounds__(kFoldThreads) __attribute__((amdgpu_waves_per_eu(8)
       stg(&o->cmin, (float)mn);
       stg(&o->cmax, (float)mx);
       stg(&o->bad, (int32_t)(b != 0.0));
+      if (count) EqualRows::store(t, 0, f);
     }
   }
 }

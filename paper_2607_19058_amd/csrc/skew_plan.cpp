@@ -26,6 +26,7 @@ static int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // update sums go over the partials of every 128 rows: longer ones take row bands (16384 x 4: 100 us
 // tiled, 62 by row bands; 1e6 x 5: 4210, 739; 2^25 x 1: 193 ms, 16.8).
 constexpr int64_t kNarrowRows = 2048;
+constexpr int64_t kMaxMomChunks = 21;
 struct RowBandShape {
   int64_t zcw, nseg, rpi, zrb;
 };
@@ -271,7 +272,6 @@ static int plan_sized(const skew_tensor_desc *d, int n, const PlanSize &size, Pl
     tp.zpath = (tp.kind == kFactored && rpi > 0 && zrb >= 1) ? 1 : 0;
     // (where workspace is shortest: few rows of more than kMaxMomChunks chunks with momentum, whose tiles
     // keep fewer rows of column partials than the two of each band: half the workspace for 42 x 13259)
-    constexpr int64_t kMaxMomChunks = 21;
     if (tp.zpath && size.least && tp.momentum && zcw > kMaxMomChunks &&
         ceil_div(tp.n, std::max<int64_t>(1, size.wide_tile_elems / tc)) <
             2 * ceil_div(tp.n, band_rows(rbs, tp.m, true, band_elems)))
@@ -315,8 +315,9 @@ static int plan_sized(const skew_tensor_desc *d, int n, const PlanSize &size, Pl
       tp.off_rsum = ws_part; ws_part = align_up(ws_part + (size_t)nzr * 8);
       for (int32_t k = 0; k < tp.nzb; k++) p.z.push_back({i, k});
       // fold items: the column chunks, then runs of kZMaxBandRows rows, whose repeated factors are
-      // counted (no more of them than bands: each has a band's statistics to write to)
-      const int64_t nrd = ceil_div(tp.n, kZMaxBandRows);
+      // counted (no more of them than bands: each has a band's statistics to write to; one alone is
+      // left to the first column chunk)
+      const int64_t nrd = tp.n > kZMaxBandRows ? ceil_div(tp.n, kZMaxBandRows) : 0;
       for (int32_t k = 0; k < (int32_t)nrd + tp.nfc; k++) p.fold.push_back({i, k});
       for (int32_t k = 0; k < (int32_t)nzr + tp.nfc; k++) p.fold_rows.push_back({i, k});
       items_total += nzb + nfc + nrd + nzr + nfc;

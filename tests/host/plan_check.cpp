@@ -254,7 +254,8 @@ static void check_one_plan(const std::string &name, const Plan &p) {
       }
       // the fold's items: the column chunks, then runs of rows whose repeated factors are counted into
       // as many bands' statistics
-      const int nrd = (int)cdiv(tp.n, kZMaxBandRows);
+      // (one run alone is the first column chunk's)
+      const int nrd = tp.n > kZMaxBandRows ? (int)cdiv(tp.n, kZMaxBandRows) : 0;
       CHECK(nrd <= tp.nzb, "%s: %d runs of rows, %d bands", tn.c_str(), nrd, tp.nzb);
       for (int c = 0; c < tp.nfc + nrd; c++) {
         CHECK(fold.count({i, c}) == 1, "%s: fold item %d", tn.c_str(), c);
