@@ -26,7 +26,7 @@ static int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // update sums go over the partials of every 128 rows: longer ones take row bands (16384 x 4: 100 us
 // tiled, 62 by row bands; 1e6 x 5: 4210, 739; 2^25 x 1: 193 ms, 16.8).
 constexpr int64_t kNarrowRows = 2048;
-constexpr int64_t kMaxMomChunks = 21;
+constexpr int64_t kMaxMomChunks = 21, kFewRows = 8;
 struct RowBandShape {
   int64_t zcw, nseg, rpi, zrb;
 };
@@ -47,6 +47,9 @@ static RowBandShape rowband_shape(int64_t n, int64_t m, int64_t ld, bool momentu
   if (r.rpi < 1 || ld > 0x7FFFFFFF / 2 / (r.rpi * zrows_per_group_max((int)r.nseg, momentum)))
     r.zrb = 0;
   if (m < kZMinCols && n <= kNarrowRows && !compact) r.zrb = 0;
+  // up to 8 rows of more than 21 chunks with momentum: a work-group per row leaves the chip idler than
+  // tiles do (4 x 16384 in the gradient-norm mode: 47 us tiled, 54 by row bands; 12 rows: equal)
+  if (momentum && r.zcw > kMaxMomChunks && n <= kFewRows) r.zrb = 0;
   return r;
 }
 

@@ -485,6 +485,15 @@ int main() {
     plan_build_within(d.data(), 2, 0, &least);
     CHECK(least.t[0].zpath == 0 && least.t[1].zpath == 1, "long rows with momentum, least workspace");
   }
+  // few long rows with momentum: by tiles up to 8 of them
+  for (int64_t m : {10752, 10753, 16384})
+    for (int64_t n : {1, 8, 9}) {
+      const std::vector<skew_tensor_desc> d = {mk(0, 2, n, m, m, id), mk(1, 2, n, m, m, id + 1)};
+      Plan p;
+      plan_build(d.data(), 2, &p);
+      CHECK(p.t[0].zpath == (m <= 10752 || n > 8) && p.t[1].zpath == 1, "%lld x %lld", (long long)n, (long long)m);
+      check_plan("few rows " + std::to_string(n) + " x " + std::to_string(m), d);
+    }
   for (int64_t m = 1; m < 8; m++)
     for (int64_t n : {1, 2047, 2048, 2049, 100003}) {
       const std::vector<skew_tensor_desc> d = {mk(1, 2, n, m, m + 1, id), mk(0, 2, n, m, m, id + 1)};
