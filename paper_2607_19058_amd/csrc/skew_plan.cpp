@@ -61,9 +61,10 @@ static int64_t row_cost(int64_t m) { return m < kZMinCols ? kZMinRowCost : m; }
 // Rows per band for bands of about `band_elems` elements (fewer with momentum, whose elements
 // take kMomCost times as long): whole blocks, at most kZMaxBandRows
 constexpr double kMomCost = 3.3;
-static int64_t band_rows(const RowBandShape &r, int64_t m, bool momentum, int64_t band_elems) {
+static int64_t band_rows(const RowBandShape &r, int64_t m, bool momentum, int64_t band_elems,
+                         double mom_cost = kMomCost) {
   const int64_t rows_block = r.rpi * r.zrb;
-  const int64_t e = momentum ? (int64_t)((double)band_elems / kMomCost) : band_elems;
+  const int64_t e = momentum ? (int64_t)((double)band_elems / mom_cost) : band_elems;
   const int64_t rows = ceil_div(std::max<int64_t>(1, e / row_cost(m)), rows_block) * rows_block;
   return std::min<int64_t>(rows, kZMaxBandRows / rows_block * rows_block);
 }
@@ -78,8 +79,7 @@ static int64_t band_rows(const RowBandShape &r, int64_t m, bool momentum, int64_
 // below 256 MiB or 1/40 of the gradients.
 constexpr double kCus = 256.0, kElemUs = 1.07e-4, kBandUs = 3.0, kFoldBytesPerUs = 2.0e6,
                  kFoldMaxBytes = 268435456.0;
-static int64_t choose_band_elems(const skew_tensor_desc *d, int n, int64_t most = kZBandElems,
-                                 double max_bytes = HUGE_VAL) {
+static int64_t choose_band_elems(const skew_tensor_desc *d, int n, double max_bytes = HUGE_VAL) {
   struct Shape {
     RowBandShape r;
     int64_t n, m;
@@ -109,10 +109,10 @@ static int64_t choose_band_elems(const skew_tensor_desc *d, int n, int64_t most 
     }
     if (!found) shapes.push_back({r, x.rows, x.cols, mom, E});
   }
-  int64_t best = most;
+  int64_t best = kZBandElems;
   double best_us = HUGE_VAL;
   for (int step = 0;; step++) {
-    const int64_t b = (int64_t)((double)most * std::exp2(-step / 8.0));
+    const int64_t b = (int64_t)((double)kZBandElems * std::exp2(-step / 8.0));
     if (b < kZMinBandElems) break;
     double bands = 0.0, bytes = 0.0;
     for (const Shape &s : shapes) {
@@ -158,6 +158,8 @@ static int64_t choose_tile_elems(const skew_tensor_desc *d, int n, bool wide) {
   return t;
 }
 
+// (the longest bands with momentum: 2.2e6 elements)
+constexpr double kLeastMomCost = 1.9;
 // What trades workspace for time: elements per row band and per tile, and (`compact` unset) padded
 // column partials, flat exact-moment tensors and tiles for short narrow matrices; `least`: nothing else
 // fits
@@ -168,6 +170,7 @@ struct PlanSize {
 static int plan_sized(const skew_tensor_desc *d, int n, const PlanSize &size, Plan *out) {
   const int64_t band_elems = size.band_elems;
   const bool compact = size.compact;
+  const double mom_cost = size.least ? kLeastMomCost : kMomCost;
   Plan p;
   // descriptors -> sub-tensors: a stacked (ndim 3) descriptor of E matrices becomes E
   // sub-tensors (one per slice, factored on its own, Sec. 3 footnote) that share one clip
@@ -277,7 +280,7 @@ static int plan_sized(const skew_tensor_desc *d, int n, const PlanSize &size, Pl
     // keep fewer rows of column partials than the two of each band: half the workspace for 42 x 13259)
     if (tp.zpath && size.least && tp.momentum && zcw > kMaxMomChunks &&
         ceil_div(tp.n, std::max<int64_t>(1, size.wide_tile_elems / tc)) <
-            2 * ceil_div(tp.n, band_rows(rbs, tp.m, true, band_elems)))
+            2 * ceil_div(tp.n, band_rows(rbs, tp.m, true, band_elems, mom_cost)))
       tp.zpath = 0;
     // (exact-moment tensors take a quarter of that: their element-by-element path is the
     // slowest per element, and their few tiles would otherwise finish last)
@@ -302,7 +305,7 @@ static int plan_sized(const skew_tensor_desc *d, int n, const PlanSize &size, Pl
       tp.nseg = (int32_t)nseg;
       tp.zrpi = (int32_t)rpi;
       tp.zrb = (int32_t)zrb;
-      tp.zrows = band_rows(rbs, tp.m, tp.momentum != 0, band_elems);
+      tp.zrows = band_rows(rbs, tp.m, tp.momentum != 0, band_elems, mom_cost);
       const int64_t nzb = ceil_div(tp.n, tp.zrows), nfc = ceil_div(tp.m, kFold);
       if (nzb > INT32_MAX / 2 || nfc > INT32_MAX / 2) return SKEW_EINVAL;
       tp.nzb = (int32_t)nzb;
@@ -403,18 +406,16 @@ int plan_build(const skew_tensor_desc *d, int n, Plan *out) {
 }
 
 // Most of a large table's workspace are the row bands' column partials: the band size is chosen again with
-// fewer bytes for them until the plan fits, up to bands of 4 * kZBandElems elements and at last of
-// kZMaxBandRows rows
+// fewer bytes for them until the plan fits, up to bands of kZBandElems elements (at last also with
+// momentum, or about)
 int plan_build_within(const skew_tensor_desc *d, int n, size_t limit, Plan *out) {
   int rc = plan_build(d, n, out);
   double bytes = (double)limit;   // for the column partials
   for (bool last = false; rc == SKEW_OK && out->ws_bytes > limit && !last;) {
-    constexpr int64_t kMost = 4 * kZBandElems;   // (kMomCost times fewer with momentum)
-    constexpr int64_t kLast = (int64_t)kZMaxBandRows * kZWaves * kZMaxSeg * kChunk * 4;
     last = bytes <= 0.0;
-    const int64_t band = last ? kLast : choose_band_elems(d, n, kMost, bytes);
+    const int64_t band = last ? kZBandElems : choose_band_elems(d, n, bytes);
     rc = plan_sized(d, n, {band, kTileElems, kTileElems, true, last}, out);
-    bytes = band >= kMost ? 0.0 : bytes - std::max((double)out->ws_bytes - (double)limit, (double)limit / 16);
+    bytes = band >= kZBandElems ? 0.0 : bytes - std::max((double)out->ws_bytes - (double)limit, (double)limit / 16);
   }
   return rc;
 }
