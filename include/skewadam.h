@@ -90,8 +90,8 @@ enum { SKEW_STATE_MOMENTUM = 1, SKEW_STATE_FACTORED = 2, SKEW_STATE_FP32 = 4 };
  *             stacked: m, v [batch][rows][cols], r [batch][rows], c [batch][cols].
  *   batch     ndim 3: the number of slices (>= 0; 0 = no elements); otherwise 0 or 1.
  *   state_flags  0 or SKEW_STATE_* bits (tier variants, Table 3).
- * w and g may have any alignment; 16-byte-aligned rows (w, g aligned and ld a
- * multiple of 8) take the vectorised path. */
+ * w and g may have any alignment; 16-byte-aligned rows (w, g aligned and ld a multiple
+ * of 8) are the fastest. */
 typedef struct skew_tensor_desc {
   int32_t tier;
   int32_t ndim;
@@ -216,14 +216,14 @@ int skew_abi_version(void);
 
 /* ---- Diagnostics: per-launch timing (not part of the step's definition) ----
  * skew_timing_enable(ctx, max_steps) creates HIP events for up to max_steps later
- * calls of skew_step on ctx, which then record one event before its first kernel and
- * one after each kernel on the step's stream (no synchronisation, no work skipped).
+ * calls of skew_step on ctx, which then record one event before and one after each
+ * launch on the step's stream (no synchronisation, no work skipped).
  * max_steps = 0 frees the events and stops recording. Errors: SKEW_EINVAL, SKEW_EHIP.
  * skew_timing_read(ctx, ms, max_launches, launches, steps) waits for the recorded
  * events, writes into ms[j] (host array of max_launches doubles) the summed duration
- * in milliseconds of the step's j-th kernel over the recorded steps, sets *launches
- * to the number of kernels per step and *steps to the number of steps recorded, and
- * restarts recording. skew_launch_name(ctx, j) names kernel j (static string). */
+ * in milliseconds of the launches of kind j over the recorded steps, sets *launches
+ * to the number of kinds and *steps to the number of steps recorded, and restarts
+ * recording. skew_launch_name(ctx, j) names kind j (static string). */
 int skew_timing_enable(skew_ctx *ctx, int max_steps);
 int skew_timing_read(skew_ctx *ctx, double *ms, int max_launches, int *launches, int *steps);
 const char *skew_launch_name(skew_ctx *ctx, int j);

@@ -1002,7 +1002,7 @@ __device__ __forceinline__ void p1z_body(const DevTensor &t, int band, const Ste
 }
 
 // One launch covers the bands of every shape: a work-group fills a compute unit in all of
-// them (two waves of up to 256 VGPRs per SIMD), so the variants share a launch at no cost in
+// them (two waves of up to 256 VGPRs per SIMD), so the bodies share a launch at no cost in
 // occupancy, and the bands of a few small tensors run beside the others instead of after them.
 template <int MODE>
 __global__ __launch_bounds__(kZThreads) void p1z_kernel(const DevTensor *__restrict__ TT,

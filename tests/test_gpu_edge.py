@@ -119,9 +119,8 @@ def test_expert_rows_always_zero():
                          ids=["plain", "gnorm+decay"])
 def test_row_band_widths_with_partial_chunks(hp):
     """Row-band matrices whose rows end inside a 512-column chunk, with and without momentum:
-    the block loads mask the lanes past the row (for M, each of its two 1 KiB halves on its
-    own) and the last block of a band holds rows past the band's end. Widths of 2, 4, 9 and
-    17 chunks take one to four chunks per wave (17: the general load loop); every tensor
+    the lanes past the row load zeros, and the last block holds rows past the matrix's end.
+    Widths of 2, 4, 9 and 17 chunks take one to four chunks per wave; every tensor
     compared. Also the widest row-band rows: 11008 columns (22 chunks, the ragged mix's
     experts) and 16384 columns (32 chunks, the row-band limit), with and without momentum,
     and 16392 columns, the first width past it (pass 1 by tiles instead)."""
@@ -141,10 +140,9 @@ def test_row_band_widths_with_partial_chunks(hp):
 
 
 def test_row_strides_past_a_32_bit_block_span():
-    """Aligned expert rows whose stride makes one block of rows span 2^31 bytes or more: the
-    row-band pass addresses a block by 32-bit offsets in its aligned variant, so such a tensor
-    takes the element-load variant. Beside it, a large stride below that limit keeps the
-    aligned one. Both against the oracle (the last block of each band is partial), and the
+    """Expert rows whose stride makes one block of rows span 2^31 bytes or more: the row-band pass
+    addresses a block by 31-bit offsets, so such a tensor takes the tiled passes. Beside it, a
+    large stride below that limit keeps the row-band pass. Both against the oracle (the last block of each band is partial), and the
     memory between the rows stays untouched."""
     dev = torch.device("cuda")
     specs = [W.Spec("ex.far", W.EXPERT, (5, 8192), 0), W.Spec("ex.near", W.EXPERT, (6, 8192), 1)]

@@ -4,8 +4,10 @@
   code (``skew_api.cpp``): the HIP runtime calls act on host memory and the kernel launchers
   check the items they receive. It checks that every element of the unit, ragged, >2^31 and
   stacked tables lies in exactly one update tile and one row band or pass-1 tile, that the
-  row-band geometry fits the kernel, that state and workspace regions are 256-byte aligned,
-  in bounds and disjoint, and that a step launches exactly the planned items.
+  row-band geometry fits the kernel in each of its modes, that state and workspace regions are
+  256-byte aligned, in bounds and disjoint, of each table's plan and of its plan with the least
+  workspace, which routes shapes on both sides of a rule's line take, and that a step launches
+  exactly the planned items.
 * ``tests/host/oracle_check.c`` with the CPU oracle: every tier and option, checking the
   clip bound on the way.
 Both are compiled here with g++/gcc (host code only) and run as child processes.

@@ -4,7 +4,8 @@ skew_state_init_static swaps the caller's workspace for the library's static one
 kernels are the same, so every weight and state bit must equal the ordinary set-up's on
 the same inputs. Two set-ups in a row share the one static array: the second, with a
 smaller table, must still match (the set-up clears what its table uses), and the first
-context is then refused (SKEW_ESTALE) instead of stepping on the array.
+context is then refused (SKEW_ESTALE) instead of stepping on the array. A table whose own
+plan is larger than the array is planned with larger bands: against the oracle.
 """
 import numpy as np
 import pytest
