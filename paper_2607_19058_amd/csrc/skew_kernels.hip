@@ -1267,8 +1267,9 @@ __device__ __forceinline__ void chunk_stats(ColStats *out, double *sum_out, floa
 // Repeated row factors of a row-band tensor: in rows [chunk kZMaxBandRows, ...), those whose R_i > 0
 // equals R_{i-1}. (A band's blocks of rows lie apart, so the row-band pass cannot tell: its blocks
 // are single rows where a row takes the whole work-group.) A tensor of one such run has it counted
-// by its first column chunk: the loads go out before those of its partials and are waited for after
-// them (work-groups of their own took the fold of 512 slices of 16 x 512 from 6.9 to 10.2 us).
+// by its first column chunk: work-groups of their own took the fold of 512 slices of 16 x 512 from
+// 6.9 to 10.2 us (8.5 so). Its loads follow the partials': ahead of them they cost the fold of the
+// 6.78B set 4 us more (79 instead of 75; 71 without the count), for the registers that they hold.
 struct EqualRows {
   static constexpr int kPer = kZMaxBandRows / kFoldThreads;
   float a[kPer], b[kPer];
@@ -1350,8 +1351,6 @@ __global__ __launch_bounds__(kFoldThreads) __attribute__((amdgpu_waves_per_eu(8)
     // eps) and sum_j z_j / c'_j over the chunk; the first waves add the sums of R while the
     // partials load (fold_sum's barrier covers theirs)
     const bool count = it.tile == 0 && t.n <= kZMaxBandRows;
-    EqualRows eq;
-    if (count) eq.load(t, 0);
     if (threadIdx.x < kThreads) {
       const double sr = wave_sum_d(sum_r_part(t, k, (int)threadIdx.x));
       if ((threadIdx.x & 63) == 0) f.rsum[threadIdx.x >> 6] = sr;
@@ -1359,6 +1358,8 @@ __global__ __launch_bounds__(kFoldThreads) __attribute__((amdgpu_waves_per_eu(8)
     const int64_t j = (int64_t)it.tile * kFold + c;
     double cs, zs;
     fold_sum<true>(t.colpart, t.zpart, t.nzb, t.ldp, j - c, t.m, f, cs, zs);
+    EqualRows eq;
+    if (count) eq.load(t, 0);
     double sr = 0.0;
     for (int w = 0; w < kWaves; w++) sr += f.rsum[w];
     const float q = mean_r_from(t, k, sr);
